@@ -947,15 +947,33 @@ __global__ void k_validate(const double* __restrict__ xs, const double* __restri
 
 // ------------------------------------------------------------------ shapes --
 // Launch shapes of the symmetric pass (waves per workgroup W, offsets per
-// chunk L) that coulomb_autotune chooses from; the first is the default.
-// make_plan clamps each to the kernel's launch bound (W <= kSymWaves) and to
-// the 64 KiB j window.
+// chunk L) that coulomb_autotune chooses from; index 0 stands for the default
+// of the size (default_shape).  make_plan clamps each to the kernel's launch
+// bound (W <= kSymWaves) and to the 64 KiB j window.
 struct SymShape {
   int W, L;
 };
-constexpr SymShape kShapes[] = {{kSymWaves, kSymChunk}, {8, 6}, {8, 12}, {8, 16}, {8, 20},
+constexpr SymShape kShapes[] = {{0, 0}, {8, 6}, {8, 12}, {8, 16}, {8, 20},
                                 {4, 8}, {4, 12}, {4, 16}, {4, 24}, {2, 24}};
 constexpr int kNumShapes = sizeof(kShapes) / sizeof(kShapes[0]);
+
+// Default shape by the number of offsets hmax = ns / 2.  A wave runs 2 L block
+// passes of about 3 us each in sequence, and the ns hmax / L waves have to
+// fill 1024 SIMDs, so a small problem takes short chunks; a longer chunk
+// writes fewer partial sums (1/L + (L + W - 1)/(W L) of the pairs of
+// super-blocks).  Forces call, us, against (8, 8) (sweep over W 1..8, L 1..12):
+// N = 2000 59 / 181, 7000 74 / 184 with (4, 1); 14 000 115 / 193, 40 003
+// 398 / 505 with (4, 2); 60 000 772 / 796, 80 000 1293 / 1320 with (4, 4);
+// at 1e5 (4, 4) takes 1965 and (8, 8) 1935.  The lines lie where the sweep's
+// best two shapes are within 2% of each other.  The FP32 partials of a block
+// pair do not depend on the shape, only the order of the FP64 sums does.
+static SymShape default_shape(int ns) {
+  const int hmax = ns / 2;
+  if (hmax <= 40) return {4, 1};
+  if (hmax <= 160) return {4, 2};
+  if (hmax <= 320) return {4, 4};
+  return {kSymWaves, kSymChunk};
+}
 // offsets per chunk that keep the j window (S = W + L - 1 super-blocks of
 // NI KiB each, forces and HVP) within 64 KiB
 constexpr int max_chunk(int W) { return 64 / NI - W + 1; }
@@ -992,7 +1010,7 @@ bool make_plan(int op, int64_t n64, int precision, char* base, Plan& P, int shap
     // W waves per workgroup, L offsets per chunk; S = L + W - 1 <= ns keeps
     // the j window from wrapping onto itself
     if (shape < 0 || shape >= kNumShapes) shape = 0;
-    const SymShape sh = kShapes[shape];
+    const SymShape sh = shape > 0 ? kShapes[shape] : default_shape(P.ns);
     P.shape = shape;
     const int w = sh.W < kSymWaves ? sh.W : kSymWaves;  // the kernel's launch bound
     P.W = P.ns < w ? P.ns : w;
@@ -1483,8 +1501,9 @@ int coulomb_autotune(const double* x, const double* y, int64_t n, int op, void* 
     g_tuned[std::make_tuple(current_device(), op, n)] = best;
   }
   shape_out[0] = best;
-  shape_out[1] = kShapes[best].W;
-  shape_out[2] = kShapes[best].L;
+  const SymShape sh = best > 0 ? kShapes[best] : default_shape((int)((n + SB - 1) / SB));
+  shape_out[1] = sh.W;
+  shape_out[2] = sh.L;
   return CD_OK;
 }
 

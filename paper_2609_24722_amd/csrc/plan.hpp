@@ -7,8 +7,9 @@
 namespace cd {
 
 // Symmetric pass launch shape (compile-time settings): blocks of 64 charges
-// per super-block (the i charges of one lane), waves per workgroup, offsets
-// per chunk, and the waves per SIMD the register budget is held to.  The j
+// per super-block (the i charges of one lane), waves per workgroup (at most,
+// and the large sizes' default), offsets per chunk of the large sizes, and
+// the waves per SIMD the register budget is held to.  The j
 // window needs (kSymWaves + kSymChunk - 1) x kSymBlocks x 1 KiB of LDS.
 #ifndef CD_SYM_BLOCKS
 #define CD_SYM_BLOCKS 2
