@@ -659,6 +659,11 @@ struct SymReduceArgs {
   int n, ns, npad, W, L, C, G, S;
   int c0, nc, Cb, mj;  // batch: first chunk, chunks, stride; list entries per chunk
   int first, last;     // first batch writes the outputs, later ones add to them
+  const double* ep;    // kForces, kRiesz: energy partials of this batch (null: no total wanted)
+  int em;              //   and their number; summed by one more workgroup
+  double* eb;          // [batches] their sums; the last batch's workgroup adds them up
+  int batch;
+  double* etot;
   double* out0;        // fx | hx | e_local (caller order)
   double* out1;        // fy | hy
   double* eblk;        // per-super-block sum of e_local (last batch)
@@ -667,8 +672,33 @@ struct SymReduceArgs {
 template <int MODE>
 __global__ __launch_bounds__(2 * SB) void k_sym_reduce(SymReduceArgs a) {
   extern __shared__ int32_t lst[];  // [nc][mj]: j partial slots, -1 for none
-  __shared__ double red[SB / 64];
+  __shared__ double red[2 * SB / 64];
   const int B = blockIdx.x;
+  if ((MODE == kForces || MODE == kRiesz) && B == a.ns) {
+    // total energy: the batch's partials in a fixed order, loads in groups of 8
+    double v = 0.0;
+    int k = threadIdx.x;
+    for (; k + 7 * 2 * SB < a.em; k += 8 * 2 * SB) {
+      double t[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) t[q] = a.ep[k + q * 2 * SB];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v += t[q];
+    }
+    for (; k < a.em; k += 2 * SB) v += a.ep[k];
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      double t = 0.0;
+      if (a.last)
+        for (int q = 0; q < a.batch; ++q) t += a.eb[q];
+      for (int q = 0; q < 2 * SB / 64; ++q) t += red[q];
+      if (a.last) *a.etot = t;
+      else a.eb[a.batch] = t;
+    }
+    return;
+  }
   for (int cl = threadIdx.x; cl < a.nc; cl += blockDim.x) {
     // workgroup (g, c) holds super-block J in slot (J - gW - cL - 1) mod ns
     // when that is < S; with u = (B - cL - 1) mod ns the bases gW that
@@ -1163,24 +1193,29 @@ static void run_sym(const Plan& P, hipStream_t st, double* out0, double* out1, d
     const int grid = P.G * nc + (c0 == 0 ? P.ns : 0);  // + the super-diagonal workgroups
     hipLaunchKernelGGL((k_sym<MODE, LOCAL>), dim3(grid), dim3(64 * P.W), lds, st, a);
     if (c0 + nc >= P.C) mark(g_ev_stop, st);
-    if (ESUM && e_total) {
-      // the first batch's sum includes the super-diagonal sums stored before it
-      const double* part = b == 0 ? P.ep : P.ep + P.ns;
-      const int m = P.G * nc + (b == 0 ? P.ns : 0);
-      sum_blocks(part, m, nbatch == 1 ? e_total : P.eb + b, st);
-    }
+    // energy partials: the first batch's include the super-diagonal sums
+    // stored before them
+    const double* part = b == 0 ? P.ep : P.ep + P.ns;
+    const int m = P.G * nc + (b == 0 ? P.ns : 0);
     if (JSIDE) {
       r.c0 = c0;
       r.nc = nc;
       r.first = c0 == 0;
       r.last = c0 + nc >= P.C;
-      hipLaunchKernelGGL((k_sym_reduce<MODE>), dim3(P.ns), dim3(2 * SB),
+      r.ep = ESUM && e_total ? part : nullptr;
+      r.em = m;
+      r.eb = P.eb;
+      r.batch = b;
+      r.etot = e_total;
+      hipLaunchKernelGGL((k_sym_reduce<MODE>), dim3(P.ns + (r.ep ? 1 : 0)), dim3(2 * SB),
                          (size_t)nc * P.mj * sizeof(int32_t), st, r);
+    } else if (ESUM && e_total) {
+      sum_blocks(part, m, nbatch == 1 ? e_total : P.eb + b, st);
     }
   }
   if (e_total) {
     if (MODE == kEnergy && LOCAL) sum_blocks(P.eblk, P.ns, e_total, st);
-    else if (ESUM && nbatch > 1) sum_blocks(P.eb, nbatch, e_total, st);
+    else if (ESUM && !JSIDE && nbatch > 1) sum_blocks(P.eb, nbatch, e_total, st);
   }
 }
 
