@@ -7,9 +7,10 @@
 //                  gather into sorted SoA arrays padded to whole 64-charge
 //                  blocks (128-charge super-blocks for CD_MIXED), per-block
 //                  bounding box;
-//   2. pair pass   CD_MIXED: symmetric FP32 kernel over super-block pairs
-//                  (each unordered pair evaluated once, Newton's third law);
-//                  CD_FP64: one-sided FP64 kernel over (i block, j range);
+//   2. pair pass   symmetric kernels over super-block pairs (each unordered
+//                  pair evaluated once, Newton's third law), FP32 pairs on
+//                  CD_MIXED, FP64 on CD_FP64 (Riesz pairs on CD_FP64: a
+//                  one-sided kernel over (i block, j range));
 //   3. reduction   fixed-order sums of the partial results, scattered back
 //                  to the caller's order; energy by a fixed-shape tree.
 #include <map>
@@ -774,7 +775,8 @@ __global__ __launch_bounds__(2 * SB) void k_sym_reduce(SymReduceArgs a) {
 }
 
 // ---------------------------------------------------- one-sided FP64 pass --
-// Wave = one i block (charges in registers), grid.y = j range split.  The j
+// The Riesz pairs, and the forces of coulomb_forces_noalloc at sizes whose
+// symmetric partial sums do not fit its scratch.  Wave = one i block (charges in registers), grid.y = j range split.  The j
 // charges are wave-uniform, read through the scalar cache and broadcast from
 // SGPRs.  The block containing i masks the self pair by index.
 struct OneArgs {
@@ -927,6 +929,365 @@ __global__ __launch_bounds__(256) void k_one64_reduce(OneReduceArgs a) {
   }
 }
 
+// ------------------------------------------------- symmetric FP64 pair pass --
+// The decomposition of the FP32 pass (super-blocks of NI x 64 charges, offsets
+// o = 1..ns/2, a workgroup owning W super-blocks and a chunk of L offsets), in
+// FP64 throughout: every unordered pair once, 20 issue slots for energy and
+// both sides' forces against 18 per ordered pair when each side is summed on
+// its own (v_rsq_f64 takes four).
+//
+// A pass is the NI x 64 i charges of a wave (NI per lane, in registers)
+// against 64 j charges.  FP64 subtractions take no DPP operand, so the j
+// charges come from LDS, where the wave has stored the block twice in a row:
+// in step k lane l reads entry l + 64 - k, j = (l - k) mod 64, one read for
+// its NI pairs.  The j sums travel with the j charge by a rotation of the wave
+// by one lane per step (four moves per NI pairs) and are home after 64.
+//
+// The j sums of a step go to a ring of W + 1 super-block slots in LDS: slot
+// w + t belongs to wave w in step t, is complete after step t = slot, and is
+// written to memory during the next step, so the LDS does not grow with L.
+//
+// Sums: a chunk's partials of one charge are added first, then the chunks in
+// order, so the results do not depend on how the chunks are batched.
+//
+// Pads: passes that meet the last super-block (when it has pads) zero the
+// terms of pad charges (MASK).
+//
+// Bound: FP64 issue.  At 1e5 charges energy and forces take 3.14 ms a call, 21
+// slots per unordered pair at the measured 3.75e13 lane instructions/s make
+// 2.8 (one-sided 5.4 ms); local energies 2.27 ms (3.98 one-sided).
+template <int MODE, bool LOCAL>
+struct Sym64 {
+  static constexpr bool kJ = MODE != kEnergy || LOCAL;     // j-side sums are kept
+  static constexpr int kNJ = MODE == kEnergy ? (LOCAL ? 1 : 0) : 2;
+  static constexpr bool kV = MODE == kHvp;
+};
+
+struct Sym64Args {
+  const double* xs;
+  const double* ys;
+  const double* vxs;
+  const double* vys;
+  int n, ns, npad, W, L, G, S;
+  int c0, nc, Cb;  // first chunk and chunks of this launch; chunks per batch
+  int nd;          // workgroups of the pairs inside the super-blocks (first launch)
+  double* ip0;     // i-side partials [Cb][npad]: fx | hx | e_local
+  double* ip1;     //                             fy | hy
+  double* jp0;     // j-side partials [Cb][G][S][SB]
+  double* jp1;
+  double* ep;      // per-workgroup energy partials [Cb][G] (total energy)
+  double* dp0;     // sums of the pairs inside each super-block [npad]
+  double* dp1;
+  double* dep;     // their energy, per block [nb]
+};
+
+// Rotation of the wave by one lane: lane l takes lane l - 1.
+__device__ __forceinline__ double wave_ror1(double v) {
+  const int2 b = __builtin_bit_cast(int2, v);
+  return __builtin_bit_cast(
+      double, make_int2(__builtin_amdgcn_update_dpp(0, b.x, 0x13C, 0xf, 0xf, false),
+                        __builtin_amdgcn_update_dpp(0, b.y, 0x13C, 0xf, 0xf, false)));
+}
+
+template <int MODE, bool LOCAL, int NI, bool MASK>
+__device__ __forceinline__ void sym64_pass(const double (&x)[NI], const double (&y)[NI],
+                                           const double (&vx)[NI], const double (&vy)[NI],
+                                           double (&A)[NI][2], double& E, double& b0, double& b1,
+                                           const double2* sj, const double2* sv, int lane,
+                                           int in, int jn) {
+  // in: real charges of the i super-block, jn: of the j block (MASK only)
+#pragma unroll(MODE == kHvp ? 2 : 4)
+  for (int k = 0; k < 64; ++k) {
+    const double2 r = sj[lane + 64 - k];
+    double2 v{};
+    if (MODE == kHvp) v = sv[lane + 64 - k];
+#pragma unroll
+    for (int q = 0; q < NI; ++q) {
+      const double dx = x[q] - r.x, dy = y[q] - r.y;
+      const double r2 = __builtin_fma(dx, dx, dy * dy);
+      double inv = rsqrt64(r2);
+      if (MASK) inv = q * kBlk + lane < in && ((lane - k) & 63) < jn ? inv : 0.0;
+      if (MODE == kEnergy) {
+        if (LOCAL) {
+          A[q][0] += inv;
+          b0 += inv;
+        } else {
+          E += inv;
+        }
+      } else if (MODE == kForces) {
+        E += inv;
+        const double i3 = inv * inv * inv;
+        A[q][0] = __builtin_fma(dx, i3, A[q][0]);
+        A[q][1] = __builtin_fma(dy, i3, A[q][1]);
+        b0 = __builtin_fma(-dx, i3, b0);
+        b1 = __builtin_fma(-dy, i3, b1);
+      } else {
+        const double wx = vx[q] - v.x, wy = vy[q] - v.y;
+        const double i2 = inv * inv;
+        const double i3 = i2 * inv;
+        const double s = __builtin_fma(dx, wx, dy * wy) * (3.0 * i3 * i2);
+        const double kx = __builtin_fma(dx, s, -wx * i3);
+        const double ky = __builtin_fma(dy, s, -wy * i3);
+        A[q][0] += kx;
+        A[q][1] += ky;
+        b0 -= kx;
+        b1 -= ky;
+      }
+    }
+    if (Sym64<MODE, LOCAL>::kJ) b0 = wave_ror1(b0);
+    if (MODE != kEnergy) b1 = wave_ror1(b1);
+  }
+}
+
+template <int MODE, bool LOCAL, int NI>
+__global__ __launch_bounds__(64 * kSym64Waves) __attribute__((amdgpu_waves_per_eu(4))) void
+k_sym64(Sym64Args a) {
+  using T = Sym64<MODE, LOCAL>;
+  constexpr int SBN = NI * kBlk;
+  extern __shared__ double lds[];  // [W][128] positions (, v), then the ring [W + 1][NJ][SBN]
+  __shared__ double ered[kSym64Waves];
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  int bid = blockIdx.x;
+  if (a.c0 == 0) {
+    if (bid < a.nd) {
+      // the ordered pairs inside the super-blocks: a wave per block of 64,
+      // the j charges wave-uniform; pads never enter
+      const int B = bid * a.W + w, I = B / NI;
+      if (B >= a.ns * NI) return;
+      const int si = B * kBlk + lane;
+      const double xi = a.xs[si], yi = a.ys[si];
+      const double vxi = T::kV ? a.vxs[si] : 0.0, vyi = T::kV ? a.vys[si] : 0.0;
+      double A0 = 0.0, A1 = 0.0, A2 = 0.0;
+      for (int J = I * NI; J < (I + 1) * NI; ++J) {
+        const size_t o = (size_t)J * kBlk;
+        const int jn = min(kBlk, a.n - J * kBlk);
+        const double* vxb = T::kV ? a.vxs + o : nullptr;
+        const double* vyb = T::kV ? a.vys + o : nullptr;
+        if (J == B)
+          one64_block<MODE, true>(a.xs + o, a.ys + o, vxb, vyb, jn, xi, yi, vxi, vyi, lane, A0,
+                                  A1, A2, 0.0, 0, 0);
+        else
+          one64_block<MODE, false>(a.xs + o, a.ys + o, vxb, vyb, jn, xi, yi, vxi, vyi, lane, A0,
+                                   A1, A2, 0.0, 0, 0);
+      }
+      if (MODE == kEnergy && LOCAL) {
+        a.dp0[si] = A2;
+      } else if (MODE != kEnergy) {
+        a.dp0[si] = A0;
+        a.dp1[si] = A1;
+      }
+      if (MODE != kHvp && !LOCAL) {
+        const double e = wave_sum(si < a.n ? A2 : 0.0);
+        if (lane == 0) a.dep[B] = 0.5 * e;
+      }
+      return;
+    }
+    bid -= a.nd;
+  }
+  const int cl = bid / a.G, g = bid % a.G;
+  const int c = a.c0 + cl;
+  const int I = g * a.W + w;
+  const bool wave_ok = I < a.ns;
+  const int hmax = a.ns / 2;
+  double2* const sj = reinterpret_cast<double2*>(lds) + w * 128;
+  double2* const sv = sj + a.W * 128;
+  double* const ring = lds + (T::kV ? 512 : 256) * a.W;
+  const int R = a.W + 1;
+  if (T::kJ)
+    for (int e = threadIdx.x; e < R * T::kNJ * SBN; e += blockDim.x) ring[e] = 0.0;
+  double x[NI], y[NI], vx[NI], vy[NI], A[NI][2], E = 0.0;
+#pragma unroll
+  for (int q = 0; q < NI; ++q) {
+    const size_t s = (size_t)(wave_ok ? I : 0) * SBN + q * kBlk + lane;
+    x[q] = a.xs[s];
+    y[q] = a.ys[s];
+    vx[q] = T::kV ? a.vxs[s] : 0.0;
+    vy[q] = T::kV ? a.vys[s] : 0.0;
+    A[q][0] = A[q][1] = 0.0;
+  }
+  const int last = a.n % SBN ? a.ns - 1 : a.ns;  // the super-block with pads (none: ns)
+  if (T::kJ) __syncthreads();
+  const size_t task = ((size_t)cl * a.G + g) * a.S;
+  // slot s of the chunk's window, complete: to memory, and its entry cleared
+  auto flush = [&](int s) {
+    double* e = ring + (s % R) * T::kNJ * SBN;
+    for (int l = threadIdx.x; l < SBN; l += blockDim.x) {
+      a.jp0[(task + s) * SBN + l] = e[l];
+      e[l] = 0.0;
+      if (T::kNJ > 1) {
+        a.jp1[(task + s) * SBN + l] = e[SBN + l];
+        e[SBN + l] = 0.0;
+      }
+    }
+  };
+#pragma unroll 1
+  for (int t = 0; t < a.L; ++t) {
+    const int o = c * a.L + 1 + t;
+    if (wave_ok && o <= hmax && (2 * o < a.ns || I < hmax)) {
+      int J = I + o;
+      if (J >= a.ns) J -= a.ns;
+      const bool mask = I == last || J == last;
+      double* const slot = ring + ((w + t) % R) * T::kNJ * SBN + lane;
+#pragma unroll 1
+      for (int h = 0; h < NI; ++h) {
+        const int J0 = J * SBN + h * kBlk;
+        const double2 r = make_double2(a.xs[J0 + lane], a.ys[J0 + lane]);
+        sj[lane] = r;
+        sj[lane + 64] = r;
+        if (T::kV) {
+          const double2 v = make_double2(a.vxs[J0 + lane], a.vys[J0 + lane]);
+          sv[lane] = v;
+          sv[lane + 64] = v;
+        }
+        // the other lanes' entries are read below: order the wave's LDS accesses
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        double b0 = 0.0, b1 = 0.0;
+        if (mask)
+          sym64_pass<MODE, LOCAL, NI, true>(x, y, vx, vy, A, E, b0, b1, sj, sv, lane,
+                                            a.n - I * SBN, a.n - J0);
+        else
+          sym64_pass<MODE, LOCAL, NI, false>(x, y, vx, vy, A, E, b0, b1, sj, sv, lane, 0, 0);
+        if (T::kJ) slot[h * kBlk] += b0;
+        if (T::kNJ > 1) slot[SBN + h * kBlk] += b1;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+    if (T::kJ) {
+      __syncthreads();
+      flush(t);
+    }
+  }
+  if (T::kJ)
+    for (int s = a.L; s < a.S; ++s) flush(s);
+  if ((MODE != kEnergy || LOCAL) && wave_ok) {
+    const size_t si = (size_t)cl * a.npad + (size_t)I * SBN + lane;
+#pragma unroll
+    for (int q = 0; q < NI; ++q) {
+      a.ip0[si + q * kBlk] = A[q][0];
+      if (MODE != kEnergy) a.ip1[si + q * kBlk] = A[q][1];
+    }
+  }
+  if (MODE != kHvp && !LOCAL) {
+    const double e = wave_sum(wave_ok ? E : 0.0);
+    if (lane == 0) ered[w] = e;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      double t = 0.0;
+      for (int q = 0; q < a.W; ++q) t += ered[q];
+      a.ep[(size_t)cl * a.G + g] = t;
+    }
+  }
+}
+
+// Sum of a batch's partials for each charge, then out (+)= it: per chunk the
+// i-side partial and the j slots that hold the charge's super-block (at most
+// mj, -1 for none), then the chunks in order.  A workgroup takes 128 charges
+// (two components, or one for the energies); workgroup nblk128 sums the
+// total energy, per chunk and then the chunks in order.
+struct Sym64ReduceArgs {
+  const double* ip0;
+  const double* ip1;
+  const double* jp0;
+  const double* jp1;
+  const double* dp0;
+  const double* dp1;
+  const double* ep;   // per-workgroup energies [Cb][G] (null: no total wanted here)
+  const double* dep;  // [nd64] the super-blocks' own
+  const int32_t* perm;
+  int n, ns, npad, W, L, G, S;
+  int c0, nc, mj, nd64;
+  int first, last;
+  double* out0;
+  double* out1;
+  double* etot;
+  double* eblk;  // per-workgroup sum of e_local (last batch)
+};
+
+template <int MODE, bool LOCAL, int NI>
+__global__ __launch_bounds__(256) void k_sym64_reduce(Sym64ReduceArgs a) {
+  extern __shared__ int32_t lst[];  // [nc][mj]
+  constexpr int SBN = NI * kBlk;
+  __shared__ double red[4];
+  const int t = threadIdx.x;
+  if (MODE != kHvp && !LOCAL && a.etot && blockIdx.x == gridDim.x - 1) {
+    // a wave per chunk, the chunks' sums added in order
+    double* const sum = reinterpret_cast<double*>(lst);  // [nc], mj >= 2 entries each
+    for (int cl = t >> 6; cl < a.nc; cl += 4) {
+      double v = 0.0;
+      for (int k = t & 63; k < a.G; k += 64) v += a.ep[(size_t)cl * a.G + k];
+      v = wave_sum(v);
+      if ((t & 63) == 0) sum[cl] = v;
+    }
+    double v = 0.0;
+    if (a.first)
+      for (int k = t; k < a.nd64; k += 256) v += a.dep[k];
+    v = wave_sum(v);
+    if ((t & 63) == 0) red[t >> 6] = v;
+    __syncthreads();
+    if (t == 0) {
+      v = a.first ? (red[0] + red[1]) + (red[2] + red[3]) : *a.etot;
+      for (int cl = 0; cl < a.nc; ++cl) v += sum[cl];
+      *a.etot = v;
+    }
+    return;
+  }
+  const int s0 = blockIdx.x * 128, B = s0 / SBN;
+  for (int cl = t; cl < a.nc; cl += 256) {
+    // the workgroups (g, c) that hold super-block B, as in k_sym_reduce
+    const int c = a.c0 + cl;
+    int32_t* out = lst + cl * a.mj;
+    int e = 0;
+    int u = (B - c * a.L - 1) % a.ns;
+    if (u < 0) u += a.ns;
+    for (int k = 0; k < 3; ++k) {
+      const int hi = u + k * a.ns, lo = hi - a.S + 1;
+      const int g0 = lo <= 0 ? 0 : (lo + a.W - 1) / a.W;
+      const int g1 = min(hi / a.W, a.G - 1);
+      for (int g = g0; g <= g1 && e < a.mj; ++g) out[e++] = (cl * a.G + g) * a.S + (hi - g * a.W);
+    }
+    for (; e < a.mj; ++e) out[e] = -1;
+  }
+  __syncthreads();
+  const int comp = t >> 7, s = s0 + (t & 127), l = s % SBN;
+  double v = 0.0;
+  if (MODE != kEnergy || comp == 0) {
+    const double* ip = comp ? a.ip1 : a.ip0;
+    const double* jp = comp ? a.jp1 : a.jp0;
+    double* out = comp ? a.out1 : a.out0;
+    const int p = s < a.n ? a.perm[s] : -1;
+    if (a.first) v = (comp ? a.dp1 : a.dp0)[s];
+    else if (p >= 0) v = out[p];
+    // chunk by chunk, four chunks' loads at a time
+    for (int c = 0; c < a.nc; c += 4) {
+      double vc[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) vc[q] = c + q < a.nc ? ip[(size_t)(c + q) * a.npad + s] : 0.0;
+      for (int m = 0; m < a.mj; ++m) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int j = c + q < a.nc ? lst[(c + q) * a.mj + m] : -1;
+          if (j >= 0) vc[q] += jp[(size_t)j * SBN + l];
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (c + q < a.nc) v += vc[q];
+    }
+    if (MODE == kEnergy && a.last) v *= 0.5;
+    if (p >= 0) out[p] = v;
+    else v = 0.0;
+  }
+  if (MODE == kEnergy && a.last) {
+    const double ws = wave_sum(v);
+    if ((t & 63) == 0) red[t >> 6] = ws;
+    __syncthreads();
+    if (t == 0) a.eblk[blockIdx.x] = red[0] + red[1];
+  }
+}
+
 // Final energy: one workgroup of 1024 threads sums the m partials in a fixed
 // order (per thread the elements t, t + 1024, ... in order, loads issued in
 // groups of 8; then the waves' sums in order).
@@ -1024,12 +1385,32 @@ static int tuned_shape(int op, int64_t n) {
   return it == g_tuned.end() ? 0 : it->second;
 }
 
+// Launch shape of the symmetric FP64 pass.  A workgroup of 4 waves (one per
+// SIMD) balances best over the CUs: at 1e5 charges forces took 3.14 ms with 4
+// waves and 3.28 with 8 (both with their best L).  Two i charges per lane give
+// more, shorter passes: at 20 000 charges 206 us with two and 4 offsets, 243
+// and more with four; from 60 000 on four i per lane halve the moves (80 000:
+// 2118 against 2154 with 4 to 6 offsets, 64 000: 1329 against 1407).  Offsets
+// per chunk: one while even so the waves do not fill the chip (4000: 44 us
+// against 55 with two), two at 10 000 (92 against 98 with one and with four),
+// four above (25 000: 282 against 303 with one, 299 with ten; 150 000: 6952
+// against 7010 with ten).
+struct Sym64Shape {
+  int ni, W, L;
+};
+static Sym64Shape sym64_shape(int n) {
+  if (n >= kSym64Wide) return {4, kSym64Waves, 4};
+  return {2, kSym64Waves, n <= 8000 ? 1 : n <= 14000 ? 2 : 4};
+}
+
 // ---------------------------------------------------------------- planning --
-bool make_plan(int op, int64_t n64, int precision, char* base, Plan& P, int shape, int max_cb) {
+bool make_plan(int op, int64_t n64, int precision, char* base, Plan& P, int shape, int max_cb,
+               bool one_sided) {
   if (n64 < 1 || n64 > (int64_t)1 << 26) return false;
   if (precision != CD_FP64 && precision != CD_MIXED) return false;
   const int n = (int)n64;
   P.n = n;
+  P.ni = 0;
   P.nb = (n + kBlk - 1) / kBlk;
   P.npad = P.nb * kBlk;
   const int mode = op == CD_OP_ENERGY ? kEnergy : op == CD_OP_FORCES ? kForces : kHvp;
@@ -1060,6 +1441,28 @@ bool make_plan(int op, int64_t n64, int precision, char* base, Plan& P, int shap
     if (max_cb > 0 && cb > (size_t)max_cb) cb = max_cb;
     P.Cb = cb < (size_t)P.C ? (int)cb : P.C;
     P.chunk_bytes = per;
+  } else if (op != CD_OP_VALIDATE && !one_sided) {
+    const Sym64Shape sh = sym64_shape(n);
+    P.ni = sh.ni;
+    const int sb = sh.ni * kBlk;
+    P.ns = (n + sb - 1) / sb;
+    P.nb = sh.ni * P.ns;
+    P.npad = P.nb * kBlk;
+    // S = L + W - 1 <= ns keeps the j window from wrapping onto itself
+    P.W = P.ns < sh.W ? P.ns : sh.W;
+    P.L = sh.L < P.ns + 1 - P.W ? sh.L : P.ns + 1 - P.W;
+    P.C = (P.ns / 2 + P.L - 1) / P.L;  // 0: everything lies in one super-block
+    P.G = (P.ns + P.W - 1) / P.W;
+    P.S = P.L + P.W - 1;
+    P.mj = (P.S + P.W - 1) / P.W + 1;
+    const size_t per = ((size_t)P.npad + (size_t)P.G * P.S * sb) * sizeof(double) *
+                       (mode == kEnergy ? 1 : 2);
+    size_t cb = kSymBatchBytes / per;
+    if (cb < 1) cb = 1;
+    if (cb > (size_t)kSymBatchMax) cb = kSymBatchMax;
+    if (max_cb > 0 && cb > (size_t)max_cb) cb = max_cb;
+    P.Cb = cb < (size_t)P.C ? (int)cb : P.C;
+    P.chunk_bytes = per;
   } else {
     // enough waves to fill 256 CUs several times over
     int sp = (16384 + P.nb - 1) / P.nb;
@@ -1068,7 +1471,7 @@ bool make_plan(int op, int64_t n64, int precision, char* base, Plan& P, int shap
     P.jb = (P.nb + sp - 1) / sp;
     P.splits = (P.nb + P.jb - 1) / P.jb;
   }
-  P.nred = (n + 255) / 256;
+  P.nred = P.ni ? (P.npad + 127) / 128 : (n + 255) / 256;
   Carve cv;
   cv.base = base;
   P.keys = cv.take<uint32_t>(n);
@@ -1098,6 +1501,18 @@ bool make_plan(int op, int64_t n64, int precision, char* base, Plan& P, int shap
         P.eb = cv.take<double>((P.C + P.Cb - 1) / P.Cb);
       }
       P.eblk = cv.take<double>(P.ns);
+    } else if (P.ni) {
+      const size_t q = (size_t)P.Cb * P.npad, jq = (size_t)P.Cb * P.G * P.S * P.ni * kBlk;
+      P.q0 = cv.take<double>(q);
+      P.j0 = cv.take<double>(jq);
+      P.dp0 = cv.take<double>(P.npad);
+      if (mode != kEnergy) {
+        P.q1 = cv.take<double>(q);
+        P.j1 = cv.take<double>(jq);
+        P.dp1 = cv.take<double>(P.npad);
+      }
+      P.ep = cv.take<double>((size_t)P.nb + (size_t)P.G * P.Cb);  // the blocks', then a batch's
+      P.eblk = cv.take<double>(P.nred);
     } else {
       const size_t q = (size_t)P.splits * P.npad;
       P.q0 = cv.take<double>(q);
@@ -1262,6 +1677,85 @@ static void run_one64(const Plan& P, hipStream_t st, double* out0, double* out1,
 }
 
 
+template <int MODE, bool LOCAL, int NI>
+static void run_sym64n(const Plan& P, hipStream_t st, double* out0, double* out1,
+                       double* e_total) {
+  using T = Sym64<MODE, LOCAL>;
+  Sym64Args a;
+  a.xs = P.xs;
+  a.ys = P.ys;
+  a.vxs = P.vxs;
+  a.vys = P.vys;
+  a.n = P.n;
+  a.ns = P.ns;
+  a.npad = P.npad;
+  a.W = P.W;
+  a.L = P.L;
+  a.G = P.G;
+  a.S = P.S;
+  a.Cb = P.Cb;
+  a.nd = (P.nb + P.W - 1) / P.W;
+  a.ip0 = P.q0;
+  a.ip1 = P.q1;
+  a.jp0 = P.j0;
+  a.jp1 = P.j1;
+  a.dp0 = P.dp0;
+  a.dp1 = P.dp1;
+  a.dep = P.ep;
+  a.ep = P.ep + P.nb;
+  const size_t lds = (size_t)P.W * 128 * sizeof(double2) * (T::kV ? 2 : 1) +
+                     (size_t)(P.W + 1) * T::kNJ * NI * kBlk * sizeof(double);
+  Sym64ReduceArgs r;
+  r.ip0 = P.q0;
+  r.ip1 = P.q1;
+  r.jp0 = P.j0;
+  r.jp1 = P.j1;
+  r.dp0 = P.dp0;
+  r.dp1 = P.dp1;
+  r.ep = a.ep;
+  r.dep = P.ep;
+  r.perm = P.perm;
+  r.n = P.n;
+  r.ns = P.ns;
+  r.npad = P.npad;
+  r.W = P.W;
+  r.L = P.L;
+  r.G = P.G;
+  r.S = P.S;
+  r.mj = P.mj;
+  r.nd64 = P.nb;
+  r.out0 = out0;
+  r.out1 = out1;
+  r.etot = e_total;
+  r.eblk = P.eblk;
+  constexpr bool ESUM = MODE != kHvp && !LOCAL;  // total energy from the per-workgroup sums
+  const int parts = T::kJ ? P.nred : 0;
+  mark(g_ev_start, st);
+  for (int c0 = 0; c0 == 0 || c0 < P.C; c0 += P.Cb) {
+    const int nc = P.C - c0 < P.Cb ? P.C - c0 : P.Cb;
+    a.c0 = r.c0 = c0;
+    a.nc = r.nc = nc;
+    r.first = c0 == 0;
+    r.last = c0 + nc >= P.C;
+    hipLaunchKernelGGL((k_sym64<MODE, LOCAL, NI>), dim3(P.G * nc + (c0 == 0 ? a.nd : 0)),
+                       dim3(64 * P.W), lds, st, a);
+    if (r.last) mark(g_ev_stop, st);
+    const int grid = parts + (ESUM && e_total ? 1 : 0);
+    if (grid)
+      hipLaunchKernelGGL((k_sym64_reduce<MODE, LOCAL, NI>), dim3(grid), dim3(256),
+                         (size_t)nc * P.mj * sizeof(int32_t), st, r);
+    if (r.last) break;
+  }
+  if (e_total && MODE == kEnergy && LOCAL) sum_blocks(P.eblk, P.nred, e_total, st);
+}
+
+template <int MODE, bool LOCAL>
+static void run_sym64(const Plan& P, hipStream_t st, double* out0, double* out1,
+                      double* e_total) {
+  if (P.ni == 4) run_sym64n<MODE, LOCAL, 4>(P, st, out0, out1, e_total);
+  else run_sym64n<MODE, LOCAL, 2>(P, st, out0, out1, e_total);
+}
+
 // v in caller order -> sorted, padded copies (pads carry v = 0)
 __global__ void k_gather_v(const double* __restrict__ vx, const double* __restrict__ vy,
                            const int32_t* __restrict__ perm, int n, int npad,
@@ -1293,7 +1787,7 @@ int hvp64_apply(const Plan& P, const double* vx, const double* vy, double* hx, d
                 hipStream_t st) {
   hipLaunchKernelGGL(k_gather_v, dim3((P.npad + 255) / 256), dim3(256), 0, st, vx, vy, P.perm,
                      P.n, P.npad, P.vxs, P.vys);
-  run_one64<kHvp>(P, st, hx, hy);
+  run_sym64<kHvp, false>(P, st, hx, hy, nullptr);
   return hip_status(hipGetLastError());
 }
 
@@ -1323,6 +1817,11 @@ size_t coulomb_workspace_bytes(int op, int64_t n, int32_t n_patches, int64_t tot
       if (!make_plan(op, n, prec, nullptr, P, sh)) return 0;
       most = P.total > most ? P.total : most;
     }
+    if (op == CD_OP_FORCES && prec == CD_FP64) {  // coulomb_riesz's one-sided pass
+      Plan P;
+      if (!make_plan(op, n, prec, nullptr, P, -1, 0, true)) return 0;
+      most = P.total > most ? P.total : most;
+    }
     return most;
   }
   if (op == CD_OP_LANCZOS) return cd::lanczos_workspace_bytes(n, n_patches);
@@ -1343,13 +1842,13 @@ size_t coulomb_workspace_bytes(int op, int64_t n, int32_t n_patches, int64_t tot
 namespace cd {
 
 static int check_ws(int op, int64_t n, int precision, void* ws, size_t ws_bytes, Plan& P,
-                    int shape = -1) {
+                    int shape = -1, bool one_sided = false) {
   if (!ws) return CD_ERR_WORKSPACE;
   if (shape < 0 && precision == CD_MIXED) shape = tuned_shape(op, n);
-  if (!make_plan(op, n, precision, nullptr, P, shape)) return CD_ERR_INVALID_ARG;
+  if (!make_plan(op, n, precision, nullptr, P, shape, 0, one_sided)) return CD_ERR_INVALID_ARG;
   if (ws_bytes < P.total) return CD_ERR_WORKSPACE;
   char* base = reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(ws) + 255) & ~uintptr_t(255));
-  make_plan(op, n, precision, base, P, shape);
+  make_plan(op, n, precision, base, P, shape, 0, one_sided);
   return CD_OK;
 }
 
@@ -1365,8 +1864,8 @@ static int energy_impl(const double* x, const double* y, int64_t n, int precisio
     if (e_local) run_sym<kEnergy, true>(P, st, e_local, nullptr, e_total);
     else run_sym<kEnergy, false>(P, st, nullptr, nullptr, e_total);
   } else {
-    run_one64<kEnergy>(P, st, e_local, nullptr);
-    sum_blocks(P.eblk, P.nred, e_total, st);
+    if (e_local) run_sym64<kEnergy, true>(P, st, e_local, nullptr, e_total);
+    else run_sym64<kEnergy, false>(P, st, nullptr, nullptr, e_total);
   }
   return hip_status(hipGetLastError());
 }
@@ -1377,7 +1876,9 @@ static int forces_run(const Plan& P, const double* x, const double* y, int preci
   if (rc) return rc;
   if (precision == CD_MIXED) {
     run_sym<kForces, false>(P, st, fx, fy, e_total);
-  } else {
+  } else if (P.ni) {
+    run_sym64<kForces, false>(P, st, fx, fy, e_total);
+  } else {  // coulomb_forces_noalloc where the symmetric pass's partial sums do not fit
     run_one64<kForces>(P, st, fx, fy);
     if (e_total) sum_blocks(P.eblk, P.nred, e_total, st);
   }
@@ -1394,26 +1895,29 @@ static int forces_impl(const double* x, const double* y, int64_t n, int precisio
   return forces_run(P, x, y, precision, fx, fy, e_total, st);
 }
 
-// Plan of a forces call inside cap bytes: the default plan, or the same
-// shape with fewer chunks per batch.
+// Plan of a forces call inside cap bytes: the default plan, the same shape
+// with fewer chunks per batch, or on CD_FP64, where not even one chunk fits,
+// the one-sided pass.
 static int plan_fixed(int64_t n, int precision, char* base, size_t cap, Plan& P) {
   const int shape = precision == CD_MIXED ? tuned_shape(CD_OP_FORCES, n) : -1;
   if (!make_plan(CD_OP_FORCES, n, precision, nullptr, P, shape)) return CD_ERR_INVALID_ARG;
   int cb = P.Cb;
   if (P.total > cap) {
-    if (precision != CD_MIXED || P.Cb <= 1) return CD_ERR_CAPACITY;
     const size_t over = P.total - cap;  // chunks to drop, rounded up
     const size_t drop = (over + P.chunk_bytes - 1) / P.chunk_bytes;
-    if (drop >= (size_t)P.Cb) return CD_ERR_CAPACITY;
-    cb = P.Cb - (int)drop;
+    cb = drop < (size_t)P.Cb ? P.Cb - (int)drop : 0;
     // the carve aligns each piece, so step down until the plan fits
-    for (;; --cb) {
-      if (cb < 1) return CD_ERR_CAPACITY;
+    for (; cb >= 1; --cb) {
       make_plan(CD_OP_FORCES, n, precision, nullptr, P, shape, cb);
       if (P.total <= cap) break;
     }
+    if (cb < 1) {
+      if (precision == CD_MIXED) return CD_ERR_CAPACITY;
+      make_plan(CD_OP_FORCES, n, precision, nullptr, P, shape, 0, true);
+      if (P.total > cap) return CD_ERR_CAPACITY;
+    }
   }
-  if (base) make_plan(CD_OP_FORCES, n, precision, base, P, shape, cb);
+  if (base) make_plan(CD_OP_FORCES, n, precision, base, P, shape, cb, cb < 1);
   return CD_OK;
 }
 
@@ -1437,7 +1941,7 @@ static int riesz_impl(const double* x, const double* y, int64_t n, double rs, in
   if (!x || !y || !fx || !fy) return CD_ERR_INVALID_ARG;
   if (!(rs > 0.0) || rs > (precision == CD_MIXED ? 6.0 : 64.0)) return CD_ERR_INVALID_ARG;
   Plan P;
-  int rc = check_ws(CD_OP_FORCES, n, precision, ws, ws_bytes, P, -1);
+  int rc = check_ws(CD_OP_FORCES, n, precision, ws, ws_bytes, P, -1, precision == CD_FP64);
   if (rc) return rc;
   if ((rc = stage(P, x, y, nullptr, nullptr, st))) return rc;
   if (precision == CD_MIXED) {
@@ -1458,7 +1962,7 @@ static int hvp_impl(const double* x, const double* y, const double* vx, const do
   if (rc) return rc;
   if ((rc = stage(P, x, y, vx, vy, st))) return rc;
   if (precision == CD_MIXED) run_sym<kHvp, false>(P, st, hx, hy, nullptr);
-  else run_one64<kHvp>(P, st, hx, hy);
+  else run_sym64<kHvp, false>(P, st, hx, hy, nullptr);
   return hip_status(hipGetLastError());
 }
 

@@ -31,6 +31,10 @@ static_assert(kSymBlocks >= 1 && kSymBlocks <= 4, "symmetric pass: 1..4 blocks p
 static_assert(kSymWaves >= 1 && kSymWaves <= 16 && kSymChunk >= 1, "symmetric pass shape");
 static_assert((kSymWaves + kSymChunk - 1) * kSymBlocks * 1024 <= 65536,
               "j window exceeds 64 KiB");
+// Symmetric FP64 pass: waves per workgroup (at most), and the size from
+// which a lane takes four i charges instead of two.
+constexpr int kSym64Waves = 4;
+constexpr int kSym64Wide = 60000;
 // Partial sums of one batch of chunks: at most this many bytes (but at least
 // one chunk), and at most kSymBatchMax chunks.
 constexpr size_t kSymBatchBytes = size_t(512) << 20;
@@ -43,7 +47,8 @@ struct Plan {
   int W = 0, L = 0, C = 0, G = 0, S = 0;  // symmetric pass
   int Cb = 0, mj = 0;                     // chunks per batch, j slots per chunk
   size_t chunk_bytes = 0;                 // partial sums of one chunk (symmetric pass)
-  int splits = 0, jb = 0;                 // one-sided pass
+  int ni = 0;                             // symmetric FP64 pass: blocks per lane (0: not used)
+  int splits = 0, jb = 0;                 // one-sided FP64 pass
   int nred = 0;                           // reduction workgroups
   // workspace pieces
   uint32_t *keys = nullptr, *keys2 = nullptr, *hist = nullptr;
@@ -64,8 +69,9 @@ struct Plan {
 // range: the default); the entry points pass the one coulomb_autotune chose.
 // max_cb > 0 caps the chunks per batch of the symmetric pass (smaller
 // scratch, more batches).
+// one_sided: the plan of the one-sided FP64 pass (CD_FP64 only).
 bool make_plan(int op, int64_t n64, int precision, char* base, Plan& P, int shape = -1,
-               int max_cb = 0);
+               int max_cb = 0, bool one_sided = false);
 
 // Forces and energy (coulomb_forces) with the scratch carved from a fixed
 // region [base, base + cap) (base 256-byte aligned): the symmetric pass's
