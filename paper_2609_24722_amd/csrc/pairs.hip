@@ -775,8 +775,9 @@ __global__ __launch_bounds__(2 * SB) void k_sym_reduce(SymReduceArgs a) {
 }
 
 // ---------------------------------------------------- one-sided FP64 pass --
-// The Riesz pairs, and the forces of coulomb_forces_noalloc at sizes whose
-// symmetric partial sums do not fit its scratch.  Wave = one i block (charges in registers), grid.y = j range split.  The j
+// Small sizes (kSym64Min), the Riesz pairs, and the forces of
+// coulomb_forces_noalloc at sizes whose symmetric partial sums do not fit its
+// scratch.  Wave = one i block (charges in registers), grid.y = j range split.  The j
 // charges are wave-uniform, read through the scalar cache and broadcast from
 // SGPRs.  The block containing i masks the self pair by index.
 struct OneArgs {
@@ -902,6 +903,7 @@ __global__ __launch_bounds__(256) void k_one64_reduce(OneReduceArgs a) {
   const int s = blockIdx.x * blockDim.x + threadIdx.x;
   double v0 = 0.0, v1 = 0.0, ve = 0.0;
   if (s < a.n) {
+#pragma unroll 8
     for (int k = 0; k < a.splits; ++k) {
       const size_t q = (size_t)k * a.npad + s;
       if (MODE == kEnergy) {
@@ -1441,7 +1443,8 @@ bool make_plan(int op, int64_t n64, int precision, char* base, Plan& P, int shap
     if (max_cb > 0 && cb > (size_t)max_cb) cb = max_cb;
     P.Cb = cb < (size_t)P.C ? (int)cb : P.C;
     P.chunk_bytes = per;
-  } else if (op != CD_OP_VALIDATE && !one_sided) {
+  } else if (op != CD_OP_VALIDATE && !one_sided &&
+             n >= (mode == kEnergy ? kSym64MinEnergy : kSym64Min)) {
     const Sym64Shape sh = sym64_shape(n);
     P.ni = sh.ni;
     const int sb = sh.ni * kBlk;
@@ -1787,7 +1790,8 @@ int hvp64_apply(const Plan& P, const double* vx, const double* vy, double* hx, d
                 hipStream_t st) {
   hipLaunchKernelGGL(k_gather_v, dim3((P.npad + 255) / 256), dim3(256), 0, st, vx, vy, P.perm,
                      P.n, P.npad, P.vxs, P.vys);
-  run_sym64<kHvp, false>(P, st, hx, hy, nullptr);
+  if (P.ni) run_sym64<kHvp, false>(P, st, hx, hy, nullptr);
+  else run_one64<kHvp>(P, st, hx, hy);
   return hip_status(hipGetLastError());
 }
 
@@ -1817,7 +1821,7 @@ size_t coulomb_workspace_bytes(int op, int64_t n, int32_t n_patches, int64_t tot
       if (!make_plan(op, n, prec, nullptr, P, sh)) return 0;
       most = P.total > most ? P.total : most;
     }
-    if (op == CD_OP_FORCES && prec == CD_FP64) {  // coulomb_riesz's one-sided pass
+    if (op != CD_OP_VALIDATE && prec == CD_FP64) {  // calls that take the one-sided pass
       Plan P;
       if (!make_plan(op, n, prec, nullptr, P, -1, 0, true)) return 0;
       most = P.total > most ? P.total : most;
@@ -1857,15 +1861,22 @@ static int energy_impl(const double* x, const double* y, int64_t n, int precisio
                        hipStream_t st, int shape) {
   if (!x || !y || !e_total) return CD_ERR_INVALID_ARG;
   Plan P;
-  int rc = check_ws(CD_OP_ENERGY, n, precision, ws, ws_bytes, P, shape);
+  int rc = check_ws(CD_OP_ENERGY, n, precision, ws, ws_bytes, P, shape,
+                    precision == CD_FP64 && e_local && n < kSym64MinLocal);
   if (rc) return rc;
   if ((rc = stage(P, x, y, nullptr, nullptr, st))) return rc;
   if (precision == CD_MIXED) {
     if (e_local) run_sym<kEnergy, true>(P, st, e_local, nullptr, e_total);
     else run_sym<kEnergy, false>(P, st, nullptr, nullptr, e_total);
   } else {
-    if (e_local) run_sym64<kEnergy, true>(P, st, e_local, nullptr, e_total);
-    else run_sym64<kEnergy, false>(P, st, nullptr, nullptr, e_total);
+    if (!P.ni) {
+      run_one64<kEnergy>(P, st, e_local, nullptr);
+      sum_blocks(P.eblk, P.nred, e_total, st);
+    } else if (e_local) {
+      run_sym64<kEnergy, true>(P, st, e_local, nullptr, e_total);
+    } else {
+      run_sym64<kEnergy, false>(P, st, nullptr, nullptr, e_total);
+    }
   }
   return hip_status(hipGetLastError());
 }
@@ -1878,7 +1889,7 @@ static int forces_run(const Plan& P, const double* x, const double* y, int preci
     run_sym<kForces, false>(P, st, fx, fy, e_total);
   } else if (P.ni) {
     run_sym64<kForces, false>(P, st, fx, fy, e_total);
-  } else {  // coulomb_forces_noalloc where the symmetric pass's partial sums do not fit
+  } else {  // small n, or coulomb_forces_noalloc where the symmetric partial sums do not fit
     run_one64<kForces>(P, st, fx, fy);
     if (e_total) sum_blocks(P.eblk, P.nred, e_total, st);
   }
@@ -1962,7 +1973,8 @@ static int hvp_impl(const double* x, const double* y, const double* vx, const do
   if (rc) return rc;
   if ((rc = stage(P, x, y, vx, vy, st))) return rc;
   if (precision == CD_MIXED) run_sym<kHvp, false>(P, st, hx, hy, nullptr);
-  else run_sym64<kHvp, false>(P, st, hx, hy, nullptr);
+  else if (P.ni) run_sym64<kHvp, false>(P, st, hx, hy, nullptr);
+  else run_one64<kHvp>(P, st, hx, hy);
   return hip_status(hipGetLastError());
 }
 

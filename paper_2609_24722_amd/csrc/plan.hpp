@@ -31,6 +31,15 @@ static_assert(kSymBlocks >= 1 && kSymBlocks <= 4, "symmetric pass: 1..4 blocks p
 static_assert(kSymWaves >= 1 && kSymWaves <= 16 && kSymChunk >= 1, "symmetric pass shape");
 static_assert((kSymWaves + kSymChunk - 1) * kSymBlocks * 1024 <= 65536,
               "j window exceeds 64 KiB");
+// FP64: sizes from which the symmetric pass is used.  Below, the one-sided
+// pass, which splits a block's j charges over up to n / 64 waves, fills the
+// chip better.  Calls, us, symmetric against one-sided: forces 39 / 33 at 3000,
+// 63 / 65 at 7000, 128 / 148 at 14 000; products 44 / 36, 72 / 76, 159 / 203;
+// local energies 56 / 53 at 7000, 78 / 76 at 10 000, 97 / 98 at 12 000, 107 / 119 at
+// 14 000; the total energy alone 30 / 31 at 4000, 32 / 39 at 5000.
+constexpr int kSym64Min = 7000;
+constexpr int kSym64MinEnergy = 4500;
+constexpr int kSym64MinLocal = 12000;
 // Symmetric FP64 pass: waves per workgroup (at most), and the size from
 // which a lane takes four i charges instead of two.
 constexpr int kSym64Waves = 4;

@@ -14,8 +14,9 @@ TOL = {FP64: dict(E=1e-13, F=1e-11, H=1e-11, e=1e-12), MIXED: dict(E=1e-7, F=1e-
 # 128- and 256-charge super-blocks: one, one and a charge, two, an odd and an even number of them, and the
 # numbers of offsets (40, 160, 320 of 128 charges) where the shape changes, on both sides
 SIZES = (128, 129, 255, 256, 257, 385, 512, 513, 1023, 1025, 10367, 10369, 41087, 41216, 82176)
-# FP64: the sizes where its shape changes (one, two and four offsets, four i charges per lane)
-SIZES += (8000, 8001, 14000, 14001, 59999, 60000, 60001, 60161)
+# FP64: the sizes where the symmetric pass begins (total energy, forces and products, local energies), and where
+# its shape changes (one, two and four offsets, four i charges per lane)
+SIZES += (4499, 4500, 4609, 6999, 7000, 7041, 8000, 8001, 11999, 12000, 14000, 14001, 59999, 60000, 60001, 60161)
 
 
 def rel_rms(ax, ay, bx, by):
