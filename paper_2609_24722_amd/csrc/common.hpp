@@ -41,6 +41,15 @@ __device__ __forceinline__ double rsqrt64(double r2) {
   return __builtin_fma(y0 * e, p, y0);
 }
 
+// 1/a in FP64 for finite a > 0 of ordinary size: the seed v_rcp_f64 (about
+// 2^-23 relative error) times 1 + e + e^2, e = 1 - a y0; the truncation term
+// e^3 is below 2^-66, so the result is within an ulp or two.
+__device__ __forceinline__ double rcp64(double a) {
+  const double y0 = __builtin_amdgcn_rcp(a);
+  const double e = __builtin_fma(-a, y0, 1.0);
+  return __builtin_fma(y0, __builtin_fma(e, e, e), y0);
+}
+
 // Wave-wide sums (64 lanes) with a fixed butterfly order: deterministic.
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll

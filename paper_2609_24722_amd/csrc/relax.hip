@@ -507,35 +507,61 @@ __global__ void k_geom_commit(RelaxDev R, const double* __restrict__ geom) {
 }
 
 // ------------------------------------------------------ exact FP64 evaluation --
-// Wave = 64 packed actives of one patch (grid.x over the block table), grid.y
-// = split of the N snapshot charges.  Frozen charges come from the snapshot,
-// skipped when the patch mask marks them; active ones from the trial
-// positions of the same patch.  Charges are wave-uniform and read through the
-// scalar cache.
-//   kGrad : energy contribution and gradient at the trial positions
+// Workgroup = 64 packed actives of one patch (grid.x over the block table) and
+// one split of the N snapshot charges (grid.y); its kEW waves take a part of
+// the split each and their sums are added in LDS, in wave order, so that the
+// partial sums in memory are a kEW-th of the waves.  Frozen charges come from
+// the snapshot, skipped when the patch mask marks them; active ones from the
+// trial positions of the same patch, an equal share of them for every wave.
+// Charges are wave-uniform and read through the scalar cache.
+//   kGrad : energy contribution and gradient at the trial positions (and the
+//           Hessian blocks where the patch's update asked for them)
 //   kFar  : far-field gradient and Hessian at the trial positions, which
 //           become the model's expansion point (mask = A + halo)
 //   kDelta: E_sub(trial) - E_sub(snapshot), pair differences without
-//           cancellation: 1/r' - 1/r = (d - d').(d + d') / (r r' (r + r'))
+//           cancellation: with s = 1/r', o = 1/r and m = s o,
+//           s - o = (r^2 - r'^2) m^2 / (s + o), r^2 - r'^2 from the products
+//           of differences and sums of the coordinates
+// Blocks: K = 3 d d^T / r^5 - I / r^3 has trace 1/r^3, so the sums of
+// dx dx / r^5, dx dy / r^5 and 1/r^3 hold all of it.
+// Bound: FP64 issue (v_rsq_f64 and v_rcp_f64 take four slots): 22 slots a pair
+// for kFar, 18 for kGrad (23 with blocks), 43 for kDelta.  32 patches of 200 to
+// 2000 actives at N = 1e5: kFar 2.27 ms (2.76 with three block sums more a pair,
+// a partial sum per wave), the final kGrad 2.12 (3.10 with the blocks), kDelta
+// 4.85 (5.84 with an IEEE division).  In the rounds of a small FP64 batch (24
+// patches, N = 4e4) the evaluation and its sum take 20 + 7 us, 90 + 60 when the
+// partials of every wave were written and all patches' summed each round.
 enum ExactMode { kGrad = 0, kFar = 1, kDelta = 2 };
+constexpr int kEW = 4;
 
+// Whether a patch takes part in a pass (uniform over its actives).
 template <int MODE>
-__global__ __launch_bounds__(256) void k_exact(RelaxDev R) {
-  // the wave index is uniform within a wave; saying so lets the compiler keep
-  // patch data in SGPRs and read the j charges through the scalar cache
-  const int wb = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
-  const int lane = threadIdx.x & 63;
-  if (wb >= R.nblk) return;
-  const int2 bk = R.blk[wb];
-  const int p = bk.x;
-  if (MODE == kGrad && !R.eval_all && (R.st[p].status != kRunning || R.st[p].phase == kPhaseCG))
-    return;
+__device__ __forceinline__ bool exact_takes(const RelaxDev& R, const PState& s) {
+  if (MODE == kGrad) return R.eval_all || (s.status == kRunning && s.phase != kPhaseCG);
   // a re-expansion skips the patches that are finished (their far field is
   // not used again: the final outputs come from a separate exact pass)
-  if (MODE == kFar && (R.st[p].status == kDone || R.st[p].status == kNonFinite)) return;
-  // kGrad takes the Hessian blocks unless the patch's update said it can do
-  // without them this time (plain path, between Newton phases); uniform per wave
-  const bool wk = MODE == kFar || (MODE == kGrad && (R.eval_all || !R.st[p].skip_k));
+  if (MODE == kFar) return s.status != kDone && s.status != kNonFinite;
+  return true;
+}
+// Whether its Hessian blocks are wanted: always with the far field; in the
+// rounds of the plain path unless its update said it can do without them this
+// time; not for the final outputs.
+template <int MODE>
+__device__ __forceinline__ bool exact_blocks(const RelaxDev& R, const PState& s) {
+  return MODE == kFar || (MODE == kGrad && !R.eval_all && !s.skip_k);
+}
+
+template <int MODE>
+__global__ __launch_bounds__(64 * kEW) void k_exact(RelaxDev R) {
+  __shared__ double part[kEW - 1][6][64];
+  // the wave index is uniform within a wave; saying so lets the compiler keep
+  // patch data in SGPRs and read the j charges through the scalar cache
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int2 bk = R.blk[blockIdx.x];
+  const int p = bk.x;
+  if (!exact_takes<MODE>(R, R.st[p])) return;  // the same for the whole workgroup
+  const bool wk = exact_blocks<MODE>(R, R.st[p]);
   const int a0 = R.ptr[p], a1 = R.ptr[p + 1];
   const int a = bk.y + lane;
   const bool ok = a < a1;
@@ -543,11 +569,26 @@ __global__ __launch_bounds__(256) void k_exact(RelaxDev R) {
   const double xi = R.tx[ac];
   const double yi = R.ty[ac];
   const double xo = R.z0x[ac], yo = R.z0y[ac];  // snapshot position (kDelta)
+  const double sx = xo - xi, sy = yo - yi;
   const uint64_t* mask = (MODE == kFar ? R.maskAH : R.maskA) + (size_t)p * R.nbN;
-  double G0 = 0.0, G1 = 0.0, G2 = 0.0, G3 = 0.0, G4 = 0.0, S3 = 0.0, Ee = 0.0, Ec = 0.0;
-  const int J0 = blockIdx.y * R.jb, J1 = min(R.nbN, J0 + R.jb);
+  double G0 = 0.0, G1 = 0.0, G2 = 0.0, G3 = 0.0, S3 = 0.0, Ee = 0.0, Ec = 0.0;
+  const int range = blockIdx.y * kEW + w;
+  const int J0 = min(R.nbN, range * R.jb), J1 = min(R.nbN, J0 + R.jb);
+  const int share = (a1 - a0 + R.splits * kEW - 1) / (R.splits * kEW);
+  const int b0 = min(a1, a0 + range * share), b1 = min(a1, b0 + share);
   auto pairs = [&](auto wk_tag) {
     constexpr bool WK = decltype(wk_tag)::value;
+    auto add = [&](double dx, double dy, double inv) {
+      const double i2 = inv * inv, i3 = i2 * inv;
+      G0 = __builtin_fma(-dx, i3, G0);
+      G1 = __builtin_fma(-dy, i3, G1);
+      if (WK) {
+        const double u = i3 * i2 * dx;
+        G2 = __builtin_fma(u, dx, G2);
+        G3 = __builtin_fma(u, dy, G3);
+        S3 += i3;
+      }
+    };
     for (int J = J0; J < J1; ++J) {
       const uint64_t m = mask[J];  // wave-uniform: charges of the patch (and halo) are skipped
       const int jn = min(64, R.n - J * 64);
@@ -558,7 +599,7 @@ __global__ __launch_bounds__(256) void k_exact(RelaxDev R) {
       // halo); most blocks of a large N hold none
       auto block = [&](auto masked_tag) {
         constexpr bool M = decltype(masked_tag)::value;
-#pragma unroll 8
+#pragma unroll(MODE == kDelta ? 4 : 8)
         for (int jj = 0; jj < jn; ++jj) {
           const bool skip = M && ((m >> jj) & 1ull);
           const double xj = xb[jj], yj = yb[jj];
@@ -567,28 +608,16 @@ __global__ __launch_bounds__(256) void k_exact(RelaxDev R) {
           if (MODE == kDelta) {
             const double ox = xo - xj, oy = yo - yj;
             const double ro2 = __builtin_fma(ox, ox, oy * oy);
-            const double ri = rsqrt64(r2), roi = rsqrt64(ro2);
-            const double rn = r2 * ri, ro = ro2 * roi;
-            const double num = (ox - dx) * (ox + dx) + (oy - dy) * (oy + dy);
-            const double v = num * ri * roi / (rn + ro);
+            const double s = rsqrt64(r2), o = rsqrt64(ro2);
+            const double mm = s * o;
+            const double num = __builtin_fma(sx, ox + dx, sy * (oy + dy));
+            const double v = num * mm * mm * rcp64(s + o);
             eb += skip ? 0.0 : v;
           } else {
             double inv = rsqrt64(r2);
             inv = skip ? 0.0 : inv;
-            const double i3 = inv * inv * inv;
-            G0 = __builtin_fma(-dx, i3, G0);
-            G1 = __builtin_fma(-dy, i3, G1);
             if (MODE == kGrad) eb += inv;
-            if (WK) {
-              // K = 3 d d^T / r^5 - I / r^3: the d d^T part here, the sum of
-              // 1/r^3 (the same for both diagonal entries) apart in S3
-              const double t3 = 3.0 * i3 * (inv * inv);
-              const double u = t3 * dx;
-              G2 = __builtin_fma(u, dx, G2);
-              G3 = __builtin_fma(u, dy, G3);
-              G4 = __builtin_fma(t3 * dy, dy, G4);
-              S3 += i3;
-            }
+            add(dx, dy, inv);
           }
         }
       };
@@ -600,45 +629,30 @@ __global__ __launch_bounds__(256) void k_exact(RelaxDev R) {
       Ec += fabs(Ee) >= fabs(eb) ? (Ee - tt) + eb : (eb - tt) + Ee;
       Ee = tt;
     }
-    if (MODE != kFar && blockIdx.y == 0) {
+    if (MODE != kFar) {
       // active-active pairs at the trial positions (half weight in the energy)
 #pragma unroll 4
-      for (int b = a0; b < a1; ++b) {
+      for (int b = b0; b < b1; ++b) {
         const double xj = R.tx[b], yj = R.ty[b];
         const double dx = xi - xj, dy = yi - yj;
         const double r2 = __builtin_fma(dx, dx, dy * dy);
+        double v;
         if (MODE == kDelta) {
           const double ox = xo - R.z0x[b], oy = yo - R.z0y[b];
           const double ro2 = __builtin_fma(ox, ox, oy * oy);
-          double v = 0.0;
-          if (b != ac) {
-            const double ri = rsqrt64(r2), roi = rsqrt64(ro2);
-            const double rn = r2 * ri, ro = ro2 * roi;
-            const double num = (ox - dx) * (ox + dx) + (oy - dy) * (oy + dy);
-            v = 0.5 * (num * ri * roi / (rn + ro));
-          }
-          const double tt = Ee + v;
-          Ec += fabs(Ee) >= fabs(v) ? (Ee - tt) + v : (v - tt) + Ee;
-          Ee = tt;
+          const double s = rsqrt64(r2), o = rsqrt64(ro2);
+          const double mm = s * o;
+          const double num = __builtin_fma(ox - dx, ox + dx, (oy - dy) * (oy + dy));
+          v = b == ac ? 0.0 : 0.5 * (num * mm * mm * rcp64(s + o));
         } else {
           double inv = rsqrt64(r2);
           inv = (b == ac) ? 0.0 : inv;
-          const double i3 = inv * inv * inv;
-          const double h = 0.5 * inv;
-          const double tt = Ee + h;
-          Ec += fabs(Ee) >= fabs(h) ? (Ee - tt) + h : (h - tt) + Ee;
-          Ee = tt;
-          G0 = __builtin_fma(-dx, i3, G0);
-          G1 = __builtin_fma(-dy, i3, G1);
-          if (WK) {
-            const double t3 = 3.0 * i3 * (inv * inv);
-            const double u = t3 * dx;
-            G2 = __builtin_fma(u, dx, G2);
-            G3 = __builtin_fma(u, dy, G3);
-            G4 = __builtin_fma(t3 * dy, dy, G4);
-            S3 += i3;
-          }
+          v = 0.5 * inv;
+          add(dx, dy, inv);
         }
+        const double tt = Ee + v;
+        Ec += fabs(Ee) >= fabs(v) ? (Ee - tt) + v : (v - tt) + Ee;
+        Ee = tt;
       }
     }
   };
@@ -646,15 +660,25 @@ __global__ __launch_bounds__(256) void k_exact(RelaxDev R) {
     pairs(std::false_type{});
   else
     pairs(std::true_type{});
-  if (!ok) return;
+  double v[6] = {G0, G1, Ee + Ec, G2, G3, S3};
+  if (w > 0) {
+#pragma unroll
+    for (int c = 0; c < 6; ++c) part[w - 1][c][lane] = v[c];
+  }
+  __syncthreads();
+  if (w > 0 || !ok) return;
+  for (int q = 0; q < kEW - 1; ++q) {
+#pragma unroll
+    for (int c = 0; c < 6; ++c) v[c] += part[q][c][lane];
+  }
   const size_t q = (size_t)blockIdx.y * R.ntot + a;
-  R.px[q] = G0;
-  R.py[q] = G1;
-  if (MODE != kFar) R.pe[q] = Ee + Ec;
+  R.px[q] = v[0];
+  R.py[q] = v[1];
+  if (MODE != kFar) R.pe[q] = v[2];
   if (MODE != kDelta && wk) {
-    R.pkxx[q] = G2 - S3;
-    R.pkxy[q] = G3;
-    R.pkyy[q] = G4 - S3;
+    R.pkxx[q] = 3.0 * v[3] - v[5];
+    R.pkxy[q] = 3.0 * v[4];
+    R.pkyy[q] = 2.0 * v[5] - 3.0 * v[3];
   }
   if (MODE == kFar && blockIdx.y == 0) {
     R.zrx[a] = xi;  // the expansion point
@@ -662,32 +686,35 @@ __global__ __launch_bounds__(256) void k_exact(RelaxDev R) {
   }
 }
 
-// Sum the split partials: mode kDelta the energy terms, kGrad also the
-// trial gradient and Hessian blocks, kFar the far-field gradient and Hessian
-// (no energy).  One workgroup per 64 actives: wave w sums the splits w,
-// w + kESW, ... in increasing order, then the wave partials are added in
-// wave order, so the order is fixed and a long split list is read by kESW
-// waves at once.
+// Sum the split partials: kDelta the energy terms, kGrad also the trial
+// gradient and Hessian blocks, kFar the far-field gradient and Hessian (no
+// energy), for the patches that took part.  One workgroup per 64 actives:
+// wave w sums the splits w, w + kESW, ... in increasing order, then the wave
+// partials are added in wave order, so the order is fixed and a long split
+// list is read by kESW waves at once.
 constexpr int kESW = 8;
 
-__global__ __launch_bounds__(64 * kESW) void k_exact_sum(RelaxDev R, int mode) {
-  const bool grad = mode != kDelta;
+template <int MODE>
+__global__ __launch_bounds__(64 * kESW) void k_exact_sum(RelaxDev R) {
   __shared__ double part[kESW - 1][6][64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int a = blockIdx.x * 64 + lane;
-  int ps = kRunning;
-  if (a < R.ntot && mode == kFar) ps = R.st[R.pid[a]].status;
-  // finished patches were left out of the re-expansion (see k_exact)
-  const bool ok = a < R.ntot && ps != kDone && ps != kNonFinite;
-  // the Hessian blocks were taken for this active's patch (see k_exact)
-  const bool wk = ok && (mode == kFar || (mode == kGrad && (R.eval_all || !R.st[R.pid[a]].skip_k)));
+  bool ok = a < R.ntot, wk = false;
+  if (MODE != kDelta && ok) {
+    const PState& s = R.st[R.pid[a]];
+    ok = exact_takes<MODE>(R, s);
+    wk = ok && exact_blocks<MODE>(R, s);
+  }
+  if (!__syncthreads_or(ok)) return;
   double v[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   if (ok) {
     for (int sp = w; sp < R.splits; sp += kESW) {
       const size_t q = (size_t)sp * R.ntot + a;
-      v[0] += R.px[q];
-      v[1] += R.py[q];
-      if (mode != kFar) v[2] += R.pe[q];
+      if (MODE != kDelta) {
+        v[0] += R.px[q];
+        v[1] += R.py[q];
+      }
+      if (MODE != kFar) v[2] += R.pe[q];
       if (wk) {
         v[3] += R.pkxx[q];
         v[4] += R.pkxy[q];
@@ -705,7 +732,7 @@ __global__ __launch_bounds__(64 * kESW) void k_exact_sum(RelaxDev R, int mode) {
 #pragma unroll
     for (int c = 0; c < 6; ++c) v[c] += part[q][c][lane];
   }
-  if (mode == kFar) {
+  if (MODE == kFar) {
     R.fgx[a] = v[0];
     R.fgy[a] = v[1];
     R.fhxx[a] = v[3];
@@ -713,7 +740,7 @@ __global__ __launch_bounds__(64 * kESW) void k_exact_sum(RelaxDev R, int mode) {
     R.fhyy[a] = v[5];
     return;
   }
-  if (grad) {
+  if (MODE == kGrad) {
     R.hgx[a] = v[0];
     R.hgy[a] = v[1];
     if (wk) {  // else the last blocks taken stay (the preconditioner may lag)
@@ -2210,9 +2237,10 @@ struct RPlan {
 };
 
 // The exact passes split the N charges into j ranges so that a pass launches
-// about kExactWaves waves (one per 64-active block and range): at 4 waves per
-// SIMD that is 16 rounds of the chip, enough to even out blocks of unequal
-// patches.  A quarter of it left a 64-patch FP64 batch 47% slower per pass.
+// about kExactWaves waves (one per 64-active block and range, kEW of them a
+// workgroup): at 4 waves per SIMD that is 16 rounds of the chip, enough to even
+// out blocks of unequal patches.  A quarter of it left a 64-patch FP64 batch
+// 47% slower per pass.
 constexpr int kExactWaves = 65536;
 
 static bool rplan(int64_t n64, int P, int64_t ntot64, int precision, int m, char* base, RPlan& R) {
@@ -2227,20 +2255,21 @@ static bool rplan(int64_t n64, int P, int64_t ntot64, int precision, int m, char
   R.nblk = R.ntot / 64 + P;  // upper bound of the block table length
   int sp = (kExactWaves + R.nblk - 1) / R.nblk;
   sp = sp < 1 ? 1 : (sp > R.nbN ? R.nbN : sp);
-  R.jb = (R.nbN + sp - 1) / sp;
-  R.splits = (R.nbN + R.jb - 1) / R.jb;
+  R.jb = (R.nbN + sp - 1) / sp;  // per wave
+  R.splits = (R.nbN + R.jb * kEW - 1) / (R.jb * kEW);
   R.hcap = precision == CD_MIXED ? 6 * R.ntot + 4096 * P : 0;
   R.running = P;
   Carve cv;
   cv.base = base;
   RelaxDev& D = R.D;
   const size_t nt = R.ntot;
-  // split partials hold nt * splits values; since splits <= ceil(kExactWaves /
-  // nblk), nblk > nt / 64 and splits <= nbN, that is below both
-  // kExactWaves * 64 + nt and nt * nbN, bounds that grow with nt, so the
-  // workspace of a larger batch covers every smaller one (the greedy commit
-  // sizes its scratch for the largest patch)
-  const size_t pcap = std::min((size_t)kExactWaves * 64 + nt, nt * (size_t)R.nbN);
+  // split partials hold nt * splits values; since splits <= ceil(r / kEW) with
+  // r = ceil(kExactWaves / nblk) ranges, nblk > nt / 64 and r <= nbN, that is
+  // below both kExactWaves * 64 / kEW + nt and nt * ceil(nbN / kEW), bounds that
+  // grow with nt, so the workspace of a larger batch covers every smaller one
+  // (the greedy commit sizes its scratch for the largest patch)
+  const size_t pcap = std::min((size_t)kExactWaves * 64 / kEW + nt,
+                               nt * (size_t)((R.nbN + kEW - 1) / kEW));
   D.pid = cv.take<int32_t>(nt);
   D.blk = cv.take<int2>(R.nblk);
   D.maskA = cv.take<uint64_t>((size_t)P * R.nbN);
@@ -2721,12 +2750,12 @@ int relax_subdomains(const double* x, const double* y, int64_t n, int32_t n_patc
     if (herr) return CD_ERR_INVALID_ARG;
   }
   hipLaunchKernelGGL(k_patch_geom, dim3(n_patches), dim3(256), 0, st, D);
-  const dim3 eg((D.nblk + 3) / 4, R.splits), eb(256);
+  const dim3 eg(D.nblk, R.splits), eb(64 * kEW);
   auto exact_grad_on = [&](int all, hipStream_t s) {
     RelaxDev E = D;
     E.eval_all = all;
     hipLaunchKernelGGL(k_exact<kGrad>, eg, eb, 0, s, E);
-    hipLaunchKernelGGL(k_exact_sum, dim3(tb64), dim3(64 * kESW), 0, s, E, (int)kGrad);
+    hipLaunchKernelGGL(k_exact_sum<kGrad>, dim3(tb64), dim3(64 * kESW), 0, s, E);
   };
   auto exact_grad = [&](int all) { exact_grad_on(all, st); };
   RoundGraphs graphs;
@@ -2823,7 +2852,7 @@ int relax_subdomains(const double* x, const double* y, int64_t n, int32_t n_patc
       }
       hipLaunchKernelGGL(k_copy_z_to_t, dim3(tb), dim3(256), 0, st, D);
       hipLaunchKernelGGL(k_exact<kFar>, eg, eb, 0, st, Df);
-      hipLaunchKernelGGL(k_exact_sum, dim3(tb64), dim3(64 * kESW), 0, st, Df, (int)kFar);
+      hipLaunchKernelGGL(k_exact_sum<kFar>, dim3(tb64), dim3(64 * kESW), 0, st, Df);
       model(1);
       hipLaunchKernelGGL(k_check, dim3(n_patches), dim3(kUpd), 0, st, D, o.gtol, 0.01, tol32,
                          ptol_ws);
@@ -2857,7 +2886,7 @@ int relax_subdomains(const double* x, const double* y, int64_t n, int32_t n_patc
   }
   if (dE) {
     hipLaunchKernelGGL(k_exact<kDelta>, eg, eb, 0, st, D);
-    hipLaunchKernelGGL(k_exact_sum, dim3(tb64), dim3(64 * kESW), 0, st, D, (int)kDelta);
+    hipLaunchKernelGGL(k_exact_sum<kDelta>, dim3(tb64), dim3(64 * kESW), 0, st, D);
     hipLaunchKernelGGL(k_finish_delta, dim3(n_patches), dim3(kUpd), 0, st, D, dE);
   }
   rc = hip_status(hipGetLastError());
