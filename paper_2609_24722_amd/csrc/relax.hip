@@ -205,7 +205,7 @@ struct RelaxDev {
   double *hkxx, *hkxy, *hkyy;  // the same at the trial
   double *pkxx, *pkxy, *pkyy;  // [splits][ntot] split partials of the blocks
   double *dx, *dy;         // search direction (coordinates: held -> angle in dx)
-  double *Sx, *Sy, *Yx, *Yy;  // L-BFGS history [m][ntot]
+  void* hist;              // L-BFGS history: Hist<HT> [m][ntot + 1], the last column zero
   double* rho;             // [P][m]
   int32_t* held;           // [ntot] optimisation coordinates: 0 (x, y); 1 the polar angle
                            // on the circle; kHeldTU the (t, u) of Sec. II.D
@@ -229,6 +229,7 @@ struct RelaxDev {
   // options
   double tol, step0, c1, noise_rel;
   int max_iter, eval_all;
+  int hist32;              // the history is stored in FP32 (mixed path)
   int32_t* ptr_w;          // [P+1] device copy of the patch offsets (in the workspace)
   double* ptol;            // [P] per-patch stage tolerance (null: tol)
   int32_t* err;            // [1] argument error found on the device
@@ -299,6 +300,12 @@ __global__ void k_setup_actives(RelaxDev R, const double* __restrict__ xs,
                                 const double* __restrict__ ys) {
   const int a = blockIdx.x * blockDim.x + threadIdx.x;
   if (a >= R.ntot) return;
+  // the zero column of the history (either storage type)
+  for (int q = a; q < 4 * R.m; q += R.ntot) {
+    const size_t e = ((size_t)(q >> 2) * (R.ntot + 1) + R.ntot) * 4 + (q & 3);
+    if (R.hist32) static_cast<float*>(R.hist)[e] = 0.f;
+    else static_cast<double*>(R.hist)[e] = 0.0;
+  }
   // patch of a: binary search in ptr
   int lo = 0, hi = R.P;
   while (hi - lo > 1) {
@@ -1039,22 +1046,25 @@ constexpr int kUpdWaves = kUpd / 64;
 // in a call with a patch above kRegJ * kUpd actives (one more register-held
 // element per thread, so that a large patch's actives 4097 to 5120 are loaded
 // one step ahead like the others instead of inside each step; for smaller
-// patches it would only add masked work).  Both variants sum in the same
-// order: the results are the same bit for bit.
+// patches it would only add masked work).
 constexpr int kRegJ = 4;
 constexpr int kRegJWide = 5;
 
-// Workgroup reductions of a kUpd-thread workgroup: each wave reduces by DPP
-// (wave_sum_rows, wave_max_rows), the wave results go to LDS and every
-// thread adds them in wave order.  The LDS partials alternate between two
-// buffers, so one barrier per reduction suffices: a buffer is written again
-// two reductions later, after every thread has passed the barrier of the
-// reduction in between (and so has finished reading it).  Every thread of
-// the workgroup must take part in every reduction, in the same order.
+// Workgroup reductions over the first nw waves: each wave reduces by DPP (rows
+// of 16, then row 15 -> 31 -> 63), its last lane stores the result in LDS,
+// and after a barrier every wave reads the nw results, one per lane of a row,
+// and reduces them by DPP within the rows: about 35 instructions a wave, where
+// adding up 16 LDS reads and four row results took 70 (0.46 us for 16 waves).
+// The LDS partials alternate between two buffers, so one barrier per
+// reduction suffices: a buffer is written again two reductions later, after
+// every thread has passed the barrier of the reduction in between (and so has
+// finished reading it).  Every thread of the nw waves takes part in every
+// reduction, in the same order; the other waves of the workgroup execute the
+// same number of barriers.
 struct WgRed {
   double* buf;  // LDS, 2 * 3 * kUpdWaves doubles
-  int par;
-  __device__ explicit WgRed(double* b) : buf(b), par(0) {}
+  int par, nw;
+  __device__ explicit WgRed(double* b) : buf(b), par(0), nw(kUpdWaves) {}
   __device__ double* next() {
     double* r = buf + par * 3 * kUpdWaves;
     par ^= 1;
@@ -1063,85 +1073,80 @@ struct WgRed {
 };
 #define WG_RED_LDS(name) __shared__ double name##_buf[2 * 3 * kUpdWaves]; WgRed name(name##_buf)
 
-__device__ double block_sum(double v, WgRed& R) {
-  v = wave_sum_rows(v);
-  double* r = R.next();
-  if ((threadIdx.x & 63) == 0) r[threadIdx.x >> 6] = v;
-  __syncthreads();
-  double t = 0.0;
-  for (int q = 0; q < kUpdWaves; ++q) t += r[q];
-  return t;
+// DPP move of the rows in ROWS (others: `off`).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_rows(double v, double off) {
+  const int2 b = __builtin_bit_cast(int2, v), o = __builtin_bit_cast(int2, off);
+  return __builtin_bit_cast(
+      double, make_int2(__builtin_amdgcn_update_dpp(o.x, b.x, CTRL, ROWS, 0xf, false),
+                        __builtin_amdgcn_update_dpp(o.y, b.y, CTRL, ROWS, 0xf, false)));
 }
-__device__ double block_max(double v, WgRed& R) {
-  v = wave_max_rows(v);
+struct OpSum {
+  __device__ static double id() { return 0.0; }
+  __device__ static double of(double a, double b) { return a + b; }
+};
+struct OpMax {  // of values >= 0
+  __device__ static double id() { return 0.0; }
+  __device__ static double of(double a, double b) { return fmax(a, b); }
+};
+// every lane: its row's result
+template <class Op>
+__device__ __forceinline__ double row_all(double v) {
+  v = Op::of(v, dpp_f64<0xB1>(v));
+  v = Op::of(v, dpp_f64<0x4E>(v));
+  v = Op::of(v, dpp_f64<0x141>(v));
+  return Op::of(v, dpp_f64<0x140>(v));
+}
+// lane 63: the wave's result (row_bcast:15 into rows 1 and 3, row_bcast:31
+// into rows 2 and 3)
+template <class Op>
+__device__ __forceinline__ double wave_last(double v) {
+  v = row_all<Op>(v);
+  v = Op::of(v, dpp_rows<0x142, 0xa>(v, Op::id()));
+  return Op::of(v, dpp_rows<0x143, 0xc>(v, Op::id()));
+}
+template <class A, class B, class C, int N>
+__device__ __forceinline__ void block_red(double& a, double& b, double& c, WgRed& R) {
+  const double wa = wave_last<A>(a), wb = N > 1 ? wave_last<B>(b) : 0.0,
+               wc = N > 2 ? wave_last<C>(c) : 0.0;
   double* r = R.next();
-  if ((threadIdx.x & 63) == 0) r[threadIdx.x >> 6] = v;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  if (lane == 63) {
+    r[w] = wa;
+    if (N > 1) r[kUpdWaves + w] = wb;
+    if (N > 2) r[2 * kUpdWaves + w] = wc;
+  }
   __syncthreads();
-  double t = r[0];
-  for (int q = 1; q < kUpdWaves; ++q) t = fmax(t, r[q]);
-  return t;
+  const int q = lane & 15;
+  const bool in = q < R.nw;
+  const double ra = r[q], rb = N > 1 ? r[kUpdWaves + q] : 0.0, rc = N > 2 ? r[2 * kUpdWaves + q] : 0.0;
+  a = row_all<A>(in ? ra : A::id());
+  if (N > 1) b = row_all<B>(in ? rb : B::id());
+  if (N > 2) c = row_all<C>(in ? rc : C::id());
+}
+__device__ __forceinline__ double block_sum(double v, WgRed& R) {
+  double x = 0.0, y = 0.0;
+  block_red<OpSum, OpSum, OpSum, 1>(v, x, y, R);
+  return v;
+}
+__device__ __forceinline__ double block_max(double v, WgRed& R) {
+  double x = 0.0, y = 0.0;
+  block_red<OpMax, OpMax, OpMax, 1>(v, x, y, R);
+  return v;
 }
 // three sums in one pass
-__device__ void block_sum3(double& a, double& b, double& c, WgRed& R) {
-  a = wave_sum_rows(a);
-  b = wave_sum_rows(b);
-  c = wave_sum_rows(c);
-  double* r = R.next();
-  if ((threadIdx.x & 63) == 0) {
-    const int w = threadIdx.x >> 6;
-    r[3 * w] = a;
-    r[3 * w + 1] = b;
-    r[3 * w + 2] = c;
-  }
-  __syncthreads();
-  double ta = 0.0, tb = 0.0, tc = 0.0;
-  for (int q = 0; q < kUpdWaves; ++q) {
-    ta += r[3 * q];
-    tb += r[3 * q + 1];
-    tc += r[3 * q + 2];
-  }
-  a = ta;
-  b = tb;
-  c = tc;
+__device__ __forceinline__ void block_sum3(double& a, double& b, double& c, WgRed& R) {
+  block_red<OpSum, OpSum, OpSum, 3>(a, b, c, R);
 }
 // a sum and a maximum in one pass
-__device__ void block_sum_max(double& sm, double& mx, WgRed& R) {
-  sm = wave_sum_rows(sm);
-  mx = wave_max_rows(mx);
-  double* r = R.next();
-  if ((threadIdx.x & 63) == 0) {
-    const int w = threadIdx.x >> 6;
-    r[3 * w] = sm;
-    r[3 * w + 1] = mx;
-  }
-  __syncthreads();
-  double ts = 0.0, tm = r[1];
-  for (int q = 0; q < kUpdWaves; ++q) {
-    ts += r[3 * q];
-    tm = fmax(tm, r[3 * q + 1]);
-  }
-  sm = ts;
-  mx = tm;
+__device__ __forceinline__ void block_sum_max(double& sm, double& mx, WgRed& R) {
+  double x = 0.0;
+  block_red<OpSum, OpMax, OpSum, 2>(sm, mx, x, R);
 }
-
 // two maxima in one pass
-__device__ void block_max2(double& a, double& b, WgRed& R) {
-  a = wave_max_rows(a);
-  b = wave_max_rows(b);
-  double* r = R.next();
-  if ((threadIdx.x & 63) == 0) {
-    const int w = threadIdx.x >> 6;
-    r[3 * w] = a;
-    r[3 * w + 1] = b;
-  }
-  __syncthreads();
-  double ta = r[0], tb = r[1];
-  for (int q = 1; q < kUpdWaves; ++q) {
-    ta = fmax(ta, r[3 * q]);
-    tb = fmax(tb, r[3 * q + 1]);
-  }
-  a = ta;
-  b = tb;
+__device__ __forceinline__ void block_max2(double& a, double& b, WgRed& R) {
+  double x = 0.0;
+  block_red<OpMax, OpMax, OpMax, 2>(a, b, x, R);
 }
 
 // Many sums at once.  rows_sum: each 16-lane row adds every one of the N
@@ -1207,7 +1212,7 @@ __device__ __forceinline__ void coord_grad(bool h, double px, double py, double 
   }
 }
 
-__device__ void take_step(bool h, double px, double py, double d0, double d1, double al,
+__device__ __forceinline__ void take_step(bool h, double px, double py, double d0, double d1, double al,
                           double& nx, double& ny, int pin, double sig) {
   if (h) {
     double sn, cs;
@@ -1228,7 +1233,7 @@ __device__ __forceinline__ void prec2x2(double a, double b, double c, double q0,
 // block for a free charge; d2E/dtheta2 = t.K.t - g.r_hat for a held one),
 // with |eigenvalues| floored at 1e-3 of the largest when the block is not
 // positive definite.  r = H0 q.
-__device__ void apply_prec(bool held, double px, double py, double g0, double g1, double a,
+__device__ __forceinline__ void apply_prec(bool held, double px, double py, double g0, double g1, double a,
                            double b, double c, double q0, double q1, double& r0, double& r1) {
   if (held) {
     const double rr = px * px + py * py;
@@ -1284,7 +1289,7 @@ __device__ __forceinline__ void prec2x2(double a, double b, double c, double q0,
 // The same for an interior charge in (t, u): J^T B J with J = d(x, y)/d(t, u)
 // (columns sigma sin 2t (cos u, sin u) and r (-sin u, cos u)) and B the
 // charge's own Cartesian block.
-__device__ void tu_prec(double sig, double t, double u, double a, double b, double c, double q0,
+__device__ __forceinline__ void tu_prec(double sig, double t, double u, double a, double b, double c, double q0,
                         double q1, double& r0, double& r1) {
   double su, cu, st, ctt;
   sincos(u, &su, &cu);
@@ -1380,7 +1385,7 @@ __device__ __forceinline__ void to_cart(bool h, double px, double py, double d0,
 // H_t x = -g_c (g_c the coordinate gradient at z) from x = 0, with the
 // block-Jacobi preconditioner of apply_prec.  The step ends when the
 // residual's inf-norm falls below max(cg_eta |g_c|inf, gtol / 10).
-__device__ void cg_start(RelaxDev& R, PState& s, int p, double gi, WgRed& red) {
+__device__ __forceinline__ void cg_start(RelaxDev& R, PState& s, int p, double gi, WgRed& red) {
   const int a0 = R.ptr[p], a1 = R.ptr[p + 1];
   double rz = 0.0, gm = 0.0;
   for (int a = a0 + threadIdx.x; a < a1; a += kUpd) {
@@ -1430,7 +1435,7 @@ __device__ void cg_start(RelaxDev& R, PState& s, int p, double gi, WgRed& red) {
 // iteration cap, or when d has non-positive curvature (the step then follows
 // the iterate x, a descent direction, or d itself at the first iteration).
 // Its largest displacement is capped at step0, as for L-BFGS steps.
-__device__ void cg_iteration(RelaxDev& R, PState& s, int p, WgRed& red) {
+__device__ __forceinline__ void cg_iteration(RelaxDev& R, PState& s, int p, WgRed& red) {
   const int a0 = R.ptr[p], a1 = R.ptr[p + 1];
   double dq = 0.0;
   for (int a = a0 + threadIdx.x; a < a1; a += kUpd) dq += R.cdx[a] * R.cqx[a] + R.cdy[a] * R.cqy[a];
@@ -1489,15 +1494,19 @@ __device__ void cg_iteration(RelaxDev& R, PState& s, int p, WgRed& red) {
   }
 }
 
+// One active's part of a stored secant pair, side by side: one load.
+template <class HT>
+struct alignas(4 * sizeof(HT)) Hist {
+  HT sx, sy, yx, yy;
+};
+
 // HT: storage type of the L-BFGS history (FP32 on the mixed path, where it
 // halves the kernel's dominant memory traffic; FP64 on the plain path).  The
 // recursion itself runs in FP64.  RJ: actives per thread held in registers.
 template <class HT, bool TU, int RJ>
 __global__ __launch_bounds__(kUpd) void k_update(RelaxDev R) {
-  HT* const Sx = reinterpret_cast<HT*>(R.Sx);
-  HT* const Sy = reinterpret_cast<HT*>(R.Sy);
-  HT* const Yx = reinterpret_cast<HT*>(R.Yx);
-  HT* const Yy = reinterpret_cast<HT*>(R.Yy);
+  Hist<HT>* const H = reinterpret_cast<Hist<HT>*>(R.hist);
+  const size_t hs = (size_t)R.ntot + 1;
   WG_RED_LDS(red);
   __shared__ double s_alf[kMaxMem];
   __shared__ double s_rho[kMaxMem];  // rho of the patch: the recursion reads it from LDS
@@ -1598,11 +1607,7 @@ __global__ __launch_bounds__(kUpd) void k_update(RelaxDev R) {
         cgrad_t<TU>(R, a, hgx, hgy, n0, n1);
         // the pair as stored (rounded to HT), so that rho matches the vectors
         const HT hs0 = (HT)s0, hs1 = (HT)s1, hy0 = (HT)(n0 - c0), hy1 = (HT)(n1 - c1);
-        const size_t q = (size_t)k * R.ntot + a;
-        Sx[q] = hs0;
-        Sy[q] = hs1;
-        Yx[q] = hy0;
-        Yy[q] = hy1;
+        H[(size_t)k * hs + a] = Hist<HT>{hs0, hs1, hy0, hy1};
         const double u0 = hs0, u1 = hs1;
         const double y0 = hy0, y1 = hy1;
         syp += u0 * y0 + u1 * y1;
@@ -1653,18 +1658,15 @@ __global__ __launch_bounds__(kUpd) void k_update(RelaxDev R) {
           const double r = sqrt(px * px + py * py);
           const double ux = -py / r, uy = px / r;
           for (int k = 0; k < m; ++k) {
-            const size_t q = (size_t)k * R.ntot + a;
-            const double s0 = Sx[q], s1 = Sy[q], y0 = Yx[q], y1 = Yy[q];
-            if (h) {
-              Sx[q] = (HT)((ux * s0 + uy * s1) / r);
-              Yx[q] = (HT)(r * (ux * y0 + uy * y1));
-              Sy[q] = Yy[q] = (HT)0;
-            } else {
-              Sx[q] = (HT)(r * s0 * ux);
-              Sy[q] = (HT)(r * s0 * uy);
-              Yx[q] = (HT)(y0 / r * ux);
-              Yy[q] = (HT)(y0 / r * uy);
-            }
+            const size_t q = (size_t)k * hs + a;
+            const Hist<HT> o = H[q];
+            const double s0 = o.sx, s1 = o.sy, y0 = o.yx, y1 = o.yy;
+            if (h)
+              H[q] = Hist<HT>{(HT)((ux * s0 + uy * s1) / r), (HT)0, (HT)(r * (ux * y0 + uy * y1)),
+                              (HT)0};
+            else
+              H[q] = Hist<HT>{(HT)(r * s0 * ux), (HT)(r * s0 * uy), (HT)(y0 / r * ux),
+                              (HT)(y0 / r * uy)};
           }
         }
         s_flag = 1;
@@ -1689,8 +1691,8 @@ __global__ __launch_bounds__(kUpd) void k_update(RelaxDev R) {
           for (int j = 0; j < 8; ++j) {
             sk = sk == 0 ? m - 1 : sk - 1;
             if (8 * h + j < M) {
-              const size_t q = (size_t)sk * R.ntot + a;
-              v[j] += (double)Sx[q] * (double)Yx[q] + (double)Sy[q] * (double)Yy[q];
+              const Hist<HT> o = H[(size_t)sk * hs + a];
+              v[j] += (double)o.sx * (double)o.yx + (double)o.sy * (double)o.yy;
             }
           }
         }
@@ -1795,143 +1797,124 @@ __global__ __launch_bounds__(kUpd) void k_update(RelaxDev R) {
     }
   }
 
-  // new direction: two-loop recursion on the coordinate gradient.  A
-  // thread's first RJ actives (a0 + t + j kUpd) keep the vector in
-  // registers; any further ones (patches above RJ * kUpd actives) keep it
-  // in R.dx, R.dy, touched only by their own thread, inside the same steps.
-  // Each thread sums its actives in increasing order, then the workgroup sum.
+  // new direction: two-loop recursion on the coordinate gradient, by the
+  // first nw waves, which hold RJ actives per thread (a0 + t + j T, T = 64 nw)
+  // in registers; the other waves of a smaller patch only keep the barriers
+  // company: every wave repeats the reductions' instructions, and the step is
+  // bound by what the CU's SIMDs issue.  32 patches of 200 to 2000 actives: 44 us
+  // a call, 61 with all 16 waves in the loops, their sums added up from LDS and
+  // the pairs' four components in arrays of their own.  Any further actives (patches above
+  // RJ x 1024) keep the vector in R.dx, R.dy, touched only by their own
+  // thread, inside the same steps.  Each thread sums its actives in increasing
+  // order, then the workgroup sum.
   __syncthreads();
-  const int tail0 = a0 + t + RJ * kUpd;
+  const int na = a1 - a0;
+  red.nw = min(kUpdWaves, (na + 64 * RJ - 1) / (64 * RJ));
+  const int T = 64 * red.nw;
+  if (t >= T) {  // whole waves: two loops of s.mem steps, then the descent test
+    for (int k = 0; k < 2 * s.mem + 1; ++k) __syncthreads();
+    // (the fallback's maximum: the descent test's outcome is in LDS)
+    __syncthreads();
+    if (s_flag) __syncthreads();
+    return;
+  }
+  const int tail0 = a0 + t + RJ * T;
   double dxr[RJ], dyr[RJ];  // the direction of the register-held elements
   {
     double qx[RJ], qy[RJ];
+    int off[RJ];  // place in a row of the history; past the patch end its zero column
 #pragma unroll
     for (int j = 0; j < RJ; ++j) {
-      const int a = a0 + t + j * kUpd;
+      const int l = t + j * T;
+      off[j] = l < na ? l : R.ntot - a0;
       qx[j] = qy[j] = 0.0;
-      if (a < a1) cgrad_z<TU>(R, a, R.gx[a], R.gy[a], qx[j], qy[j]);
+      if (l < na) cgrad_z<TU>(R, a0 + l, R.gx[a0 + l], R.gy[a0 + l], qx[j], qy[j]);
     }
-    for (int a = tail0; a < a1; a += kUpd) {
+    for (int a = tail0; a < a1; a += T) {
       double c0, c1;
       cgrad_z<TU>(R, a, R.gx[a], R.gy[a], c0, c1);
       R.dx[a] = c0;
       R.dy[a] = c1;
     }
-    // FP32 history: pair k + 1 is loaded while pair k is reduced (FP64
-    // history has no registers to spare for it)
+    // slot of pair k, counted from the newest
+    auto slot = [&](int k) {
+      const int kk = s.head - 1 - k;
+      return kk < 0 ? kk + m : kk;
+    };
+    auto load = [&](int k, Hist<HT>(&v)[RJ]) {  // a pair outside the memory: any, never used
+      const Hist<HT>* row = H + (size_t)slot(k >= 0 && k < s.mem ? k : 0) * hs + a0;
+#pragma unroll
+      for (int j = 0; j < RJ; ++j) v[j] = row[off[j]];
+    };
+    auto step1 = [&](int k, const Hist<HT>(&c)[RJ]) {
+      const int kk = slot(k);
+      const Hist<HT>* row = H + (size_t)kk * hs;
+      double v = 0.0;
+#pragma unroll
+      for (int j = 0; j < RJ; ++j) v += (double)c[j].sx * qx[j] + (double)c[j].sy * qy[j];
+      for (int a = tail0; a < a1; a += T)
+        v += (double)row[a].sx * R.dx[a] + (double)row[a].sy * R.dy[a];
+      const double rk = s_rho[kk];  // read ahead of the reduction's barrier
+      const double al = rk * block_sum(v, red);
+      if (t == 0) s_alf[kk] = al;
+#pragma unroll
+      for (int j = 0; j < RJ; ++j) {
+        qx[j] -= al * (double)c[j].yx;
+        qy[j] -= al * (double)c[j].yy;
+      }
+      for (int a = tail0; a < a1; a += T) {
+        R.dx[a] -= al * (double)row[a].yx;
+        R.dy[a] -= al * (double)row[a].yy;
+      }
+    };
+    auto step2 = [&](int k, const Hist<HT>(&c)[RJ]) {
+      const int kk = slot(k);
+      const Hist<HT>* row = H + (size_t)kk * hs;
+      double v = 0.0;
+#pragma unroll
+      for (int j = 0; j < RJ; ++j) v += (double)c[j].yx * qx[j] + (double)c[j].yy * qy[j];
+      for (int a = tail0; a < a1; a += T)
+        v += (double)row[a].yx * R.dx[a] + (double)row[a].yy * R.dy[a];
+      const double rk = s_rho[kk];
+      const double be = rk * block_sum(v, red);
+      const double coef = s_alf[kk] - be;
+#pragma unroll
+      for (int j = 0; j < RJ; ++j) {
+        qx[j] += coef * (double)c[j].sx;
+        qy[j] += coef * (double)c[j].sy;
+      }
+      for (int a = tail0; a < a1; a += T) {
+        R.dx[a] += coef * (double)row[a].sx;
+        R.dy[a] += coef * (double)row[a].sy;
+      }
+    };
+    // FP32 history: pair k + 1 is loaded while pair k is reduced, two steps per
+    // loop trip with the buffers' roles swapped, so no register copy waits on
+    // a load in flight.  FP64 history has no registers to spare for it.
     constexpr bool kPre = sizeof(HT) == 4;
-    HT ux[RJ], uy[RJ], wx[RJ], wy[RJ];
-    auto load_pair = [&](int k, HT* u0, HT* u1, HT* w0, HT* w1) {
-      const bool kin = k >= 0 && k < s.mem;  // pairs outside the memory read as zero
-      const int sk = s.head - 1 - (kin ? k : 0);
-      const size_t base = (size_t)(sk < 0 ? sk + m : sk) * R.ntot;
-#pragma unroll
-      for (int j = 0; j < RJ; ++j) {
-        const int a = a0 + t + j * kUpd;
-        const bool ok = kin && a < a1;
-        const size_t q = base + (size_t)min(a, a1 - 1);
-        const HT x0 = Sx[q], x1 = Sy[q], x2 = Yx[q], x3 = Yy[q];
-        u0[j] = ok ? x0 : (HT)0;
-        u1[j] = ok ? x1 : (HT)0;
-        w0[j] = ok ? x2 : (HT)0;
-        w1[j] = ok ? x3 : (HT)0;
-      }
-    };
-    // FP32 history: step k reduces pair k while pair k + 1 loads.  Two steps
-    // per loop trip, with the buffers' roles swapped, so no register copy
-    // waits on a load in flight.
-    // Raw loads at clamped, in-patch addresses (stored, finite values): no
-    // branch or select stands between a load and its use.  A pair outside
-    // the memory is loaded but never used; the elements past the patch end
-    // meet q = 0 in the sums and are masked (mk = 0) in the updates, so q
-    // stays 0 there.
-    auto load_vec = [&](const HT* A0, const HT* A1, int k, HT* v0, HT* v1) {
-      const bool kin = k >= 0 && k < s.mem;
-      const int sk = s.head - 1 - (kin ? k : 0);
-      const size_t base = (size_t)(sk < 0 ? sk + m : sk) * R.ntot;
-#pragma unroll
-      for (int j = 0; j < RJ; ++j) {
-        const size_t q = base + (size_t)min(a0 + t + j * kUpd, a1 - 1);
-        v0[j] = A0[q];
-        v1[j] = A1[q];
-      }
-    };
-    double mk[RJ];
-#pragma unroll
-    for (int j = 0; j < RJ; ++j) mk[j] = a0 + t + j * kUpd < a1 ? 1.0 : 0.0;
+    Hist<HT> A[RJ];
     if constexpr (kPre) {
-      HT a0s[RJ], a1s[RJ], a0y[RJ], a1y[RJ];
-      HT b0s[RJ], b1s[RJ], b0y[RJ], b1y[RJ];
-      auto step1 = [&](int k, HT* c0s, HT* c1s, HT* c0y, HT* c1y, HT* n0s, HT* n1s, HT* n0y,
-                       HT* n1y) {
-        const int kk = s.head - 1 - k < 0 ? s.head - 1 - k + m : s.head - 1 - k;
-        const size_t base = (size_t)kk * R.ntot;
-        load_vec(Sx, Sy, k + 1, n0s, n1s);
-        load_vec(Yx, Yy, k + 1, n0y, n1y);
-        double v = 0.0;
-#pragma unroll
-        for (int j = 0; j < RJ; ++j) v += (double)c0s[j] * qx[j] + (double)c1s[j] * qy[j];
-        for (int a = tail0; a < a1; a += kUpd)
-          v += (double)Sx[base + a] * R.dx[a] + (double)Sy[base + a] * R.dy[a];
-        const double rk = s_rho[kk];  // read ahead of the reduction's barrier
-        const double al = rk * block_sum(v, red);
-        if (t == 0) s_alf[kk] = al;
-#pragma unroll
-        for (int j = 0; j < RJ; ++j) {
-          qx[j] -= al * (mk[j] * (double)c0y[j]);
-          qy[j] -= al * (mk[j] * (double)c1y[j]);
-        }
-        for (int a = tail0; a < a1; a += kUpd) {
-          R.dx[a] -= al * (double)Yx[base + a];
-          R.dy[a] -= al * (double)Yy[base + a];
-        }
-      };
-      load_vec(Sx, Sy, 0, a0s, a1s);
-      load_vec(Yx, Yy, 0, a0y, a1y);
+      Hist<HT> B[RJ];
+      load(0, A);
       for (int k = 0; k < s.mem; k += 2) {
-        step1(k, a0s, a1s, a0y, a1y, b0s, b1s, b0y, b1y);
-        if (k + 1 < s.mem) step1(k + 1, b0s, b1s, b0y, b1y, a0s, a1s, a0y, a1y);
+        load(k + 1, B);
+        step1(k, A);
+        if (k + 1 < s.mem) {
+          load(k + 2, A);
+          step1(k + 1, B);
+        }
       }
     } else {
-      if (kPre) load_pair(0, ux, uy, wx, wy);
       for (int k = 0; k < s.mem; ++k) {
-        const int kk = s.head - 1 - k < 0 ? s.head - 1 - k + m : s.head - 1 - k;
-        const size_t base = (size_t)kk * R.ntot;
-        HT nux[RJ], nuy[RJ], nwx[RJ], nwy[RJ];
-        if (kPre)
-          load_pair(k + 1, nux, nuy, nwx, nwy);
-        else
-          load_pair(k, ux, uy, wx, wy);
-        double v = 0.0;
-  #pragma unroll
-        for (int j = 0; j < RJ; ++j) v += (double)ux[j] * qx[j] + (double)uy[j] * qy[j];
-        for (int a = tail0; a < a1; a += kUpd)
-          v += (double)Sx[base + a] * R.dx[a] + (double)Sy[base + a] * R.dy[a];
-        const double rk = s_rho[kk];  // read ahead of the reduction's barrier
-        const double al = rk * block_sum(v, red);
-        if (t == 0) s_alf[kk] = al;
-  #pragma unroll
-        for (int j = 0; j < RJ; ++j) {
-          qx[j] -= al * (double)wx[j];
-          qy[j] -= al * (double)wy[j];
-          if (kPre) {
-            ux[j] = nux[j];
-            uy[j] = nuy[j];
-            wx[j] = nwx[j];
-            wy[j] = nwy[j];
-          }
-        }
-        for (int a = tail0; a < a1; a += kUpd) {
-          R.dx[a] -= al * (double)Yx[base + a];
-          R.dy[a] -= al * (double)Yy[base + a];
-        }
+        load(k, A);
+        step1(k, A);
       }
     }
     // the preconditioner, in registers for the register-held elements and
     // in memory for the tail
 #pragma unroll
     for (int j = 0; j < RJ; ++j) {
-      const int a = a0 + t + j * kUpd;
+      const int a = a0 + t + j * T;
       if (a < a1) {
         double r0, r1;
         prec_z<TU>(R, a, qx[j], qy[j], r0, r1);
@@ -1939,78 +1922,27 @@ __global__ __launch_bounds__(kUpd) void k_update(RelaxDev R) {
         qy[j] = r1;
       }
     }
-    for (int a = tail0; a < a1; a += kUpd) {
+    for (int a = tail0; a < a1; a += T) {
       double r0, r1;
       prec_z<TU>(R, a, R.dx[a], R.dy[a], r0, r1);
       R.dx[a] = r0;
       R.dy[a] = r1;
     }
     if constexpr (kPre) {
-      HT a0s[RJ], a1s[RJ], a0y[RJ], a1y[RJ];
-      HT b0s[RJ], b1s[RJ], b0y[RJ], b1y[RJ];
-      auto step2 = [&](int k, HT* c0s, HT* c1s, HT* c0y, HT* c1y, HT* n0s, HT* n1s, HT* n0y,
-                       HT* n1y) {
-        const int kk = s.head - 1 - k < 0 ? s.head - 1 - k + m : s.head - 1 - k;
-        const size_t base = (size_t)kk * R.ntot;
-        load_vec(Sx, Sy, k - 1, n0s, n1s);
-        load_vec(Yx, Yy, k - 1, n0y, n1y);
-        double v = 0.0;
-#pragma unroll
-        for (int j = 0; j < RJ; ++j) v += (double)c0y[j] * qx[j] + (double)c1y[j] * qy[j];
-        for (int a = tail0; a < a1; a += kUpd)
-          v += (double)Yx[base + a] * R.dx[a] + (double)Yy[base + a] * R.dy[a];
-        const double rk = s_rho[kk];
-        const double be = rk * block_sum(v, red);
-        const double coef = s_alf[kk] - be;
-#pragma unroll
-        for (int j = 0; j < RJ; ++j) {
-          qx[j] += coef * (mk[j] * (double)c0s[j]);
-          qy[j] += coef * (mk[j] * (double)c1s[j]);
-        }
-        for (int a = tail0; a < a1; a += kUpd) {
-          R.dx[a] += coef * (double)Sx[base + a];
-          R.dy[a] += coef * (double)Sy[base + a];
-        }
-      };
-      load_vec(Sx, Sy, s.mem - 1, a0s, a1s);
-      load_vec(Yx, Yy, s.mem - 1, a0y, a1y);
+      Hist<HT> B[RJ];
+      load(s.mem - 1, A);
       for (int k = s.mem - 1; k >= 0; k -= 2) {
-        step2(k, a0s, a1s, a0y, a1y, b0s, b1s, b0y, b1y);
-        if (k - 1 >= 0) step2(k - 1, b0s, b1s, b0y, b1y, a0s, a1s, a0y, a1y);
+        load(k - 1, B);
+        step2(k, A);
+        if (k - 1 >= 0) {
+          load(k - 2, A);
+          step2(k - 1, B);
+        }
       }
     } else {
-      if (kPre) load_pair(s.mem - 1, ux, uy, wx, wy);
       for (int k = s.mem - 1; k >= 0; --k) {
-        const int kk = s.head - 1 - k < 0 ? s.head - 1 - k + m : s.head - 1 - k;
-        const size_t base = (size_t)kk * R.ntot;
-        HT nux[RJ], nuy[RJ], nwx[RJ], nwy[RJ];
-        if (kPre)
-          load_pair(k - 1, nux, nuy, nwx, nwy);
-        else
-          load_pair(k, ux, uy, wx, wy);
-        double v = 0.0;
-  #pragma unroll
-        for (int j = 0; j < RJ; ++j) v += (double)wx[j] * qx[j] + (double)wy[j] * qy[j];
-        for (int a = tail0; a < a1; a += kUpd)
-          v += (double)Yx[base + a] * R.dx[a] + (double)Yy[base + a] * R.dy[a];
-        const double rk = s_rho[kk];
-        const double be = rk * block_sum(v, red);
-        const double coef = s_alf[kk] - be;
-  #pragma unroll
-        for (int j = 0; j < RJ; ++j) {
-          qx[j] += coef * (double)ux[j];
-          qy[j] += coef * (double)uy[j];
-          if (kPre) {
-            ux[j] = nux[j];
-            uy[j] = nuy[j];
-            wx[j] = nwx[j];
-            wy[j] = nwy[j];
-          }
-        }
-        for (int a = tail0; a < a1; a += kUpd) {
-          R.dx[a] += coef * (double)Sx[base + a];
-          R.dy[a] += coef * (double)Sy[base + a];
-        }
+        load(k, A);
+        step2(k, A);
       }
     }
 #pragma unroll
@@ -2026,7 +1958,7 @@ __global__ __launch_bounds__(kUpd) void k_update(RelaxDev R) {
   double dg = 0.0, dm = 0.0;
 #pragma unroll
   for (int j = 0; j < RJ; ++j) {
-    const int a = a0 + t + j * kUpd;
+    const int a = a0 + t + j * T;
     if (a < a1) {
       double c0, c1;
       cgrad_z<TU>(R, a, R.gx[a], R.gy[a], c0, c1);
@@ -2037,7 +1969,7 @@ __global__ __launch_bounds__(kUpd) void k_update(RelaxDev R) {
       dm = fmax(dm, step_len<TU>(R, a, d0, d1));
     }
   }
-  for (int a = tail0; a < a1; a += kUpd) {
+  for (int a = tail0; a < a1; a += T) {
     double c0, c1;
     cgrad_z<TU>(R, a, R.gx[a], R.gy[a], c0, c1);
     const double d0 = -R.dx[a], d1 = -R.dy[a];
@@ -2048,9 +1980,11 @@ __global__ __launch_bounds__(kUpd) void k_update(RelaxDev R) {
   }
   block_sum_max(dg, dm, red);
   const bool steep = !(dg < 0.0);
+  if (t == 0) s_flag = steep;  // for the waves that only wait
+  __syncthreads();
   if (steep) {
     dm = 0.0;
-    for (int a = a0 + t; a < a1; a += kUpd) {
+    for (int a = a0 + t; a < a1; a += T) {
       double c0, c1, r0, r1;
       cgrad_z<TU>(R, a, R.gx[a], R.gy[a], c0, c1);
       prec_z<TU>(R, a, c0, c1, r0, r1);
@@ -2061,7 +1995,7 @@ __global__ __launch_bounds__(kUpd) void k_update(RelaxDev R) {
     dm = block_max(dm, red);
 #pragma unroll
     for (int j = 0; j < RJ; ++j) {
-      const int a = a0 + t + j * kUpd;
+      const int a = a0 + t + j * T;
       if (a < a1) {
         dxr[j] = R.dx[a];
         dyr[j] = R.dy[a];
@@ -2072,10 +2006,10 @@ __global__ __launch_bounds__(kUpd) void k_update(RelaxDev R) {
   s.alpha = 1.0;
 #pragma unroll
   for (int j = 0; j < RJ; ++j) {
-    const int a = a0 + t + j * kUpd;
+    const int a = a0 + t + j * T;
     if (a < a1) set_trial<TU>(R, s, a, dxr[j] * sc, dyr[j] * sc);
   }
-  for (int a = tail0; a < a1; a += kUpd) set_trial<TU>(R, s, a, R.dx[a] * sc, R.dy[a] * sc);
+  for (int a = tail0; a < a1; a += T) set_trial<TU>(R, s, a, R.dx[a] * sc, R.dy[a] * sc);
   if (t == 0) R.st[p] = s;
 }
 
@@ -2295,10 +2229,7 @@ static bool rplan(int64_t n64, int P, int64_t ntot64, int precision, int m, char
   D.pkyy = cv.take<double>(pcap);
   D.dx = cv.take<double>(nt);
   D.dy = cv.take<double>(nt);
-  D.Sx = cv.take<double>(nt * m);
-  D.Sy = cv.take<double>(nt * m);
-  D.Yx = cv.take<double>(nt * m);
-  D.Yy = cv.take<double>(nt * m);
+  D.hist = cv.take<double>(4 * (nt + 1) * m);
   D.rho = cv.take<double>((size_t)P * m);
   D.held = cv.take<int32_t>(nt);
   D.pin = cv.take<int32_t>(nt);
@@ -2682,6 +2613,7 @@ int relax_subdomains(const double* x, const double* y, int64_t n, int32_t n_patc
   D.noise_rel = 1e-14;
   D.max_iter = o.max_iter;
   D.bflag = o.boundary;
+  D.hist32 = o.precision != CD_FP64;
   D.sigma = o.sigma > 0.0 ? o.sigma : 1.0;
   D.eval_all = 0;
   D.tol = o.gtol;
