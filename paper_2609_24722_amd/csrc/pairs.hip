@@ -915,7 +915,7 @@ __global__ __launch_bounds__(256) void k_one64_reduce(OneReduceArgs a) {
       }
     }
     ve *= 0.5;  // ordered pairs: e_i = 1/2 sum_{j != i} 1/r_ij
-    const int p = a.perm[s];
+    const int p = a.perm ? a.perm[s] : s;
     if (MODE == kEnergy) {
       if (a.out0) a.out0[p] = ve;
     } else {
@@ -1259,7 +1259,7 @@ __global__ __launch_bounds__(256) void k_sym64_reduce(Sym64ReduceArgs a) {
     const double* ip = comp ? a.ip1 : a.ip0;
     const double* jp = comp ? a.jp1 : a.jp0;
     double* out = comp ? a.out1 : a.out0;
-    const int p = s < a.n ? a.perm[s] : -1;
+    const int p = s < a.n ? (a.perm ? a.perm[s] : s) : -1;
     if (a.first) v = (comp ? a.dp1 : a.dp0)[s];
     else if (p >= 0) v = out[p];
     // chunk by chunk, four chunks' loads at a time
@@ -1759,22 +1759,6 @@ static void run_sym64(const Plan& P, hipStream_t st, double* out0, double* out1,
   else run_sym64n<MODE, LOCAL, 2>(P, st, out0, out1, e_total);
 }
 
-// v in caller order -> sorted, padded copies (pads carry v = 0)
-__global__ void k_gather_v(const double* __restrict__ vx, const double* __restrict__ vy,
-                           const int32_t* __restrict__ perm, int n, int npad,
-                           double* __restrict__ vxs, double* __restrict__ vys) {
-  int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= npad) return;
-  if (s < n) {
-    const int p = perm[s];
-    vxs[s] = vx[p];
-    vys[s] = vy[p];
-  } else {
-    vxs[s] = 0.0;
-    vys[s] = 0.0;
-  }
-}
-
 size_t hvp64_bytes(int64_t n) {
   Plan P;
   return make_plan(CD_OP_HVP, n, CD_FP64, nullptr, P) ? P.total : 0;
@@ -1786,12 +1770,19 @@ int hvp64_stage(Plan& P, char* base, int64_t n, const double* x, const double* y
   return stage(P, x, y, nullptr, nullptr, st);
 }
 
-int hvp64_apply(const Plan& P, const double* vx, const double* vy, double* hx, double* hy,
-                hipStream_t st) {
-  hipLaunchKernelGGL(k_gather_v, dim3((P.npad + 255) / 256), dim3(256), 0, st, vx, vy, P.perm,
-                     P.n, P.npad, P.vxs, P.vys);
-  if (P.ni) run_sym64<kHvp, false>(P, st, hx, hy, nullptr);
-  else run_one64<kHvp>(P, st, hx, hy);
+int hvp64_npad(int64_t n) {
+  Plan P;
+  return make_plan(CD_OP_HVP, n, CD_FP64, nullptr, P) ? P.npad : 0;
+}
+
+int hvp64_sorted(const Plan& P, const double* vx, const double* vy, double* hx, double* hy,
+                 hipStream_t st) {
+  Plan Q = P;
+  Q.perm = nullptr;  // the results stay in sorted order
+  Q.vxs = const_cast<double*>(vx);
+  Q.vys = const_cast<double*>(vy);
+  if (Q.ni) run_sym64<kHvp, false>(Q, st, hx, hy, nullptr);
+  else run_one64<kHvp>(Q, st, hx, hy);
   return hip_status(hipGetLastError());
 }
 

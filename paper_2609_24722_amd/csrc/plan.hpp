@@ -97,7 +97,11 @@ int stage(const Plan& P, const double* x, const double* y, const double* vx, con
 // FP64 Hessian-vector products on positions staged once
 size_t hvp64_bytes(int64_t n);
 int hvp64_stage(Plan& P, char* base, int64_t n, const double* x, const double* y, hipStream_t st);
-int hvp64_apply(const Plan& P, const double* vx, const double* vy, double* hx, double* hy,
-                hipStream_t st);
+// padded length of the sorted arrays
+int hvp64_npad(int64_t n);
+// v and the result in the staged (sorted) order: vx, vy [npad] with zeros in
+// the pads; hx, hy: places below n are written
+int hvp64_sorted(const Plan& P, const double* vx, const double* vy, double* hx, double* hy,
+                 hipStream_t st);
 
 }  // namespace cd
