@@ -541,6 +541,15 @@ __global__ void k_geom_commit(RelaxDev R, const double* __restrict__ geom) {
 enum ExactMode { kGrad = 0, kFar = 1, kDelta = 2 };
 constexpr int kEW = 4;
 
+// 1/|d| - 1/|o| for d = o - s (kDelta)
+__device__ __forceinline__ double delta_pair(double dx, double dy, double ox, double oy,
+                                             double sx, double sy) {
+  const double u = rsqrt64(__builtin_fma(dx, dx, dy * dy));
+  const double o = rsqrt64(__builtin_fma(ox, ox, oy * oy));
+  const double m = u * o;
+  return __builtin_fma(sx, ox + dx, sy * (oy + dy)) * m * m * rcp64(u + o);
+}
+
 // Whether a patch takes part in a pass (uniform over its actives).
 template <int MODE>
 __device__ __forceinline__ bool exact_takes(const RelaxDev& R, const PState& s) {
@@ -611,17 +620,11 @@ __global__ __launch_bounds__(64 * kEW) void k_exact(RelaxDev R) {
           const bool skip = M && ((m >> jj) & 1ull);
           const double xj = xb[jj], yj = yb[jj];
           const double dx = xi - xj, dy = yi - yj;
-          const double r2 = __builtin_fma(dx, dx, dy * dy);
           if (MODE == kDelta) {
-            const double ox = xo - xj, oy = yo - yj;
-            const double ro2 = __builtin_fma(ox, ox, oy * oy);
-            const double s = rsqrt64(r2), o = rsqrt64(ro2);
-            const double mm = s * o;
-            const double num = __builtin_fma(sx, ox + dx, sy * (oy + dy));
-            const double v = num * mm * mm * rcp64(s + o);
+            const double v = delta_pair(dx, dy, xo - xj, yo - yj, sx, sy);
             eb += skip ? 0.0 : v;
           } else {
-            double inv = rsqrt64(r2);
+            double inv = rsqrt64(__builtin_fma(dx, dx, dy * dy));
             inv = skip ? 0.0 : inv;
             if (MODE == kGrad) eb += inv;
             add(dx, dy, inv);
@@ -642,17 +645,12 @@ __global__ __launch_bounds__(64 * kEW) void k_exact(RelaxDev R) {
       for (int b = b0; b < b1; ++b) {
         const double xj = R.tx[b], yj = R.ty[b];
         const double dx = xi - xj, dy = yi - yj;
-        const double r2 = __builtin_fma(dx, dx, dy * dy);
         double v;
         if (MODE == kDelta) {
           const double ox = xo - R.z0x[b], oy = yo - R.z0y[b];
-          const double ro2 = __builtin_fma(ox, ox, oy * oy);
-          const double s = rsqrt64(r2), o = rsqrt64(ro2);
-          const double mm = s * o;
-          const double num = __builtin_fma(ox - dx, ox + dx, (oy - dy) * (oy + dy));
-          v = b == ac ? 0.0 : 0.5 * (num * mm * mm * rcp64(s + o));
+          v = b == ac ? 0.0 : 0.5 * delta_pair(dx, dy, ox, oy, ox - dx, oy - dy);
         } else {
-          double inv = rsqrt64(r2);
+          double inv = rsqrt64(__builtin_fma(dx, dx, dy * dy));
           inv = (b == ac) ? 0.0 : inv;
           v = 0.5 * inv;
           add(dx, dy, inv);
@@ -2550,16 +2548,6 @@ int build_patches(const double* x, const double* y, int64_t n, int32_t n_patches
   return herr ? CD_ERR_INVALID_ARG : CD_OK;
 }
 
-// scatter of committed positions: x[idx[a]] = xr[a]
-__global__ void k_scatter(double* __restrict__ x, double* __restrict__ y,
-                          const int32_t* __restrict__ idx, const double* __restrict__ xr,
-                          const double* __restrict__ yr, int m) {
-  const int a = blockIdx.x * blockDim.x + threadIdx.x;
-  if (a >= m) return;
-  x[idx[a]] = xr[a];
-  y[idx[a]] = yr[a];
-}
-
 int relax_subdomains(const double* x, const double* y, int64_t n, int32_t n_patches,
                      const int32_t* patch_ptr, const int32_t* active_idx, const double* x_start,
                      const double* y_start, const cd_relax_opts* opts, double* x_out,
@@ -2869,6 +2857,146 @@ int relax_autotune(const double* x, const double* y, int64_t n, int32_t n_patche
   return CD_OK;
 }
 
+}  // extern "C"
+
+namespace cd {
+
+// waves of a candidate's pass: 8 rounds of the chip at 4 waves per SIMD
+constexpr int kCommitWaves = 32768;
+
+// ------------------------------------------------------------------- commit --
+struct CommitArgs {
+  double* x;
+  double* y;
+  int n, nbN;
+  const int32_t* idx;  // packed, as the positions
+  const double* xr;
+  const double* yr;
+  uint64_t* mask;   // [nbN] the candidate's charges
+  uint64_t* taken;  // [nbN] charges of committed candidates
+  int32_t* clash;   // [1] the candidate shares a charge with a committed one
+  double* part;     // [blocks][splits] its energy change
+  int a0, a1;       // the candidate's packed range
+  int splits, jb;   // j blocks of 64 per wave, kEW waves per workgroup
+};
+
+// Exact energy change of candidate [a0, a1) against the configuration (x, y):
+// as k_exact<kDelta>, on the positions a relax would start from (projected
+// into the disk).  One sum per workgroup of 64 actives and one split.
+__global__ __launch_bounds__(64 * kEW) void k_commit_delta(CommitArgs c) {
+  __shared__ double red[kEW];
+  if (*c.clash) return;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int a = c.a0 + blockIdx.x * 64 + lane;
+  const bool ok = a < c.a1;
+  const int ac = ok ? a : c.a1 - 1;
+  double xi = c.xr[ac], yi = c.yr[ac];
+  project_wall(xi, yi, 0, 1.0);
+  const double xo = c.x[c.idx[ac]], yo = c.y[c.idx[ac]];
+  const double sx = xo - xi, sy = yo - yi;
+  double Ee = 0.0, Ec = 0.0;
+  auto fold = [&](double v) {  // Neumaier
+    const double t = Ee + v;
+    Ec += fabs(Ee) >= fabs(v) ? (Ee - t) + v : (v - t) + Ee;
+    Ee = t;
+  };
+  const int range = blockIdx.y * kEW + w;
+  const int J0 = min(c.nbN, range * c.jb), J1 = min(c.nbN, J0 + c.jb);
+  const double* const gx = c.x;
+  const double* const gy = c.y;
+  for (int J = J0; J < J1; ++J) {
+    const uint64_t m = c.mask[J];
+    const int jn = min(64, c.n - J * 64);
+    const double* xb = gx + (size_t)J * 64;
+    const double* yb = gy + (size_t)J * 64;
+    double eb = 0.0;
+    auto block = [&](auto masked_tag) {
+      constexpr bool M = decltype(masked_tag)::value;
+#pragma unroll 4
+      for (int jj = 0; jj < jn; ++jj) {
+        const double xj = xb[jj], yj = yb[jj];
+        const double v = delta_pair(xi - xj, yi - yj, xo - xj, yo - yj, sx, sy);
+        eb += M && ((m >> jj) & 1ull) ? 0.0 : v;
+      }
+    };
+    if (m)
+      block(std::true_type{});
+    else
+      block(std::false_type{});
+    fold(eb);
+  }
+  // pairs of the candidate's own charges, an equal share for every wave
+  const int na = c.a1 - c.a0, share = (na + c.splits * kEW - 1) / (c.splits * kEW);
+  const int b0 = min(c.a1, c.a0 + range * share), b1 = min(c.a1, b0 + share);
+  for (int b = b0; b < b1; ++b) {
+    double xj = c.xr[b], yj = c.yr[b];
+    project_wall(xj, yj, 0, 1.0);
+    const int ib = c.idx[b];
+    const double dx = xi - xj, dy = yi - yj, ox = xo - gx[ib], oy = yo - gy[ib];
+    fold(b == ac ? 0.0 : 0.5 * delta_pair(dx, dy, ox, oy, ox - dx, oy - dy));
+  }
+  const double v = wave_sum(ok ? Ee + Ec : 0.0);
+  if (lane == 0) red[w] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double t = 0.0;
+    for (int q = 0; q < kEW; ++q) t += red[q];
+    c.part[(size_t)blockIdx.x * c.splits + blockIdx.y] = t;
+  }
+}
+
+// Ends a candidate (c; none if a0 = a1): its energy change, the decision, its
+// positions; then marks the next one's charges [n0, n1) and tests them.  One
+// workgroup.  res[0], res[1]: the energy change and whether it was committed.
+__global__ __launch_bounds__(1024) void k_commit_step(CommitArgs c, int n0, int n1,
+                                                      double* __restrict__ res) {
+  __shared__ double red[16];
+  __shared__ double dE;
+  const int t = threadIdx.x;
+  if (c.a1 > c.a0) {
+    const bool clash = *c.clash;  // uniform; written again below, after a barrier
+    double v = 0.0;
+    const int m = clash ? 0 : (c.a1 - c.a0 + 63) / 64 * c.splits;
+#pragma unroll 4
+    for (int q = t; q < m; q += 1024) v += c.part[q];
+    v = wave_sum(v);
+    if ((t & 63) == 0) red[t >> 6] = v;
+    __syncthreads();
+    if (t == 0) {
+      double e = 0.0;
+      for (int q = 0; q < 16; ++q) e += red[q];
+      dE = e;
+      res[0] = e;
+      res[1] = e < 0.0 ? 1.0 : 0.0;
+    }
+    __syncthreads();
+    const bool com = dE < 0.0;
+    for (int a = c.a0 + t; a < c.a1; a += 1024) {
+      const int i = c.idx[a];
+      c.mask[i >> 6] = 0;
+      if (com) {
+        c.x[i] = c.xr[a];
+        c.y[i] = c.yr[a];
+        atomicOr((unsigned long long*)&c.taken[i >> 6], 1ull << (i & 63));
+      }
+    }
+    __threadfence();  // the cleared words and taken bits, before the next candidate's
+    __syncthreads();
+  }
+  bool hit = false;
+  for (int a = n0 + t; a < n1; a += 1024) {
+    const int i = c.idx[a];
+    const unsigned long long bit = 1ull << (i & 63);
+    hit |= (__hip_atomic_load(&c.taken[i >> 6], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit) != 0;
+    atomicOr((unsigned long long*)&c.mask[i >> 6], bit);
+  }
+  const int any = __syncthreads_or(hit);
+  if (t == 0) *c.clash = any;
+}
+
+}  // namespace cd
+
 // Greedy commit of relaxed candidates.  Candidates with a negative energy
 // change at the snapshot are visited in increasing order of that change
 // (ties by index); one that shares a charge with an already committed
@@ -2876,7 +3004,13 @@ int relax_autotune(const double* x, const double* y, int64_t n, int32_t n_patche
 // exactly, against the current configuration (earlier commits included,
 // since the 1/r coupling makes changes non-additive) and it is committed --
 // its positions written into x, y -- iff that change is negative.
-int commit_patches(double* x, double* y, int64_t n, int32_t n_patches, const int32_t* patch_ptr,
+//
+// The whole sequence runs on the device: a candidate's pass (k_commit_delta)
+// and a step that takes the decision, writes the positions and marks the next
+// candidate (k_commit_step); the results come back in groups.  One call of the
+// relax per candidate took 12 launches and three waits, 135 us each where the
+// pairs take 48 (1000 actives at N = 4e4).
+extern "C" int commit_patches(double* x, double* y, int64_t n, int32_t n_patches, const int32_t* patch_ptr,
                    const int32_t* active_idx, const double* x_rel, const double* y_rel,
                    const double* order_key, int32_t* committed, double* dE_commit, void* ws,
                    size_t ws_bytes, void* stream) {
@@ -2910,37 +3044,61 @@ int commit_patches(double* x, double* y, int64_t n, int32_t n_patches, const int
   }
   std::stable_sort(order.begin(), order.end(),
                    [&](int a, int b) { return order_key[a] < order_key[b]; });
-  std::vector<unsigned char> taken(n, 0);
+  if (order.empty()) return CD_OK;
   char* base = reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(ws) + 255) & ~uintptr_t(255));
-  double* dEd = reinterpret_cast<double*>(base);
-  char* rws = base + 256;
-  cd_relax_opts o = {};
-  o.precision = CD_FP64;
-  o.max_iter = 0;  // evaluation only: energy change of the given positions
-  o.gtol = 1e300;
-  for (int p : order) {
-    const int a0 = patch_ptr[p], a1 = patch_ptr[p + 1];
-    bool clash = false;
-    for (int a = a0; a < a1 && !clash; ++a) clash = taken[idx[a]];
-    if (clash) continue;
-    const int32_t pp[2] = {0, a1 - a0};
-    rc = relax_subdomains(x, y, n, 1, pp, active_idx + a0, x_rel + a0, y_rel + a0, &o, nullptr,
-                          nullptr, dEd, nullptr, nullptr, nullptr, nullptr, rws, need, stream);
-    if (rc) return rc;
-    double d = 0.0;
-    if ((rc = hip_status(hipMemcpyAsync(&d, dEd, sizeof(double), hipMemcpyDeviceToHost, st))))
-      return rc;
-    if ((rc = hip_status(hipStreamSynchronize(st)))) return rc;
-    dE_commit[p] = d;
-    if (d < 0.0) {
-      hipLaunchKernelGGL(k_scatter, dim3((a1 - a0 + 255) / 256), dim3(256), 0, st, x, y,
-                         active_idx + a0, x_rel + a0, y_rel + a0, a1 - a0);
-      if ((rc = hip_status(hipGetLastError()))) return rc;
-      committed[p] = 1;
-      for (int a = a0; a < a1; ++a) taken[idx[a]] = 1;
+  // the pieces of a relax workspace for the largest candidate: its masks, its
+  // partial sums (larger than what the launches below write) and, for the
+  // results of a group of candidates, the 256 bytes before it or px
+  RPlan R;
+  if (!rplan(n, 1, maxp, CD_FP64, kMaxMem, base + 256, R)) return CD_ERR_INVALID_ARG;
+  const size_t roomy = std::min((size_t)kExactWaves * 64 / kEW + maxp,
+                                (size_t)maxp * ((R.nbN + kEW - 1) / kEW)) / 2;
+  double* res = roomy > 16 ? R.D.px : reinterpret_cast<double*>(base);
+  const size_t group = std::min<size_t>(256, std::max<size_t>(16, roomy));
+  CommitArgs c;
+  c.x = x;
+  c.y = y;
+  c.n = (int)n;
+  c.nbN = R.nbN;
+  c.idx = active_idx;
+  c.xr = x_rel;
+  c.yr = y_rel;
+  c.mask = R.D.maskA;
+  c.taken = R.D.maskAH;
+  c.clash = R.D.err;
+  c.part = R.D.pe;
+  if ((rc = hip_status(hipMemsetAsync(c.mask, 0, sizeof(uint64_t) * R.nbN, st)))) return rc;
+  if ((rc = hip_status(hipMemsetAsync(c.taken, 0, sizeof(uint64_t) * R.nbN, st)))) return rc;
+  std::vector<double> host(2 * group);
+  const int M = (int)order.size();
+  c.a0 = c.a1 = 0;
+  c.splits = c.jb = 1;
+  for (int q = 0, got = 0; q <= M; ++q) {
+    // the step ends candidate q - 1 and marks candidate q
+    const int n0 = q < M ? patch_ptr[order[q]] : 0, n1 = q < M ? patch_ptr[order[q] + 1] : 0;
+    hipLaunchKernelGGL(k_commit_step, dim3(1), dim3(1024), 0, st, c, n0, n1,
+                       res + 2 * (q - 1 - got));
+    if (q == M || q - got == (int)group) {
+      const int cnt = q - got;
+      if ((rc = hip_status(hipMemcpyAsync(host.data(), res, sizeof(double) * 2 * cnt,
+                                          hipMemcpyDeviceToHost, st))))
+        return rc;
+      if ((rc = hip_status(hipStreamSynchronize(st)))) return rc;
+      for (int e = 0; e < cnt; ++e) {
+        dE_commit[order[got + e]] = host[2 * e];
+        committed[order[got + e]] = host[2 * e + 1] != 0.0;
+      }
+      got = q;
     }
+    if (q == M) break;
+    c.a0 = n0;
+    c.a1 = n1;
+    const int nblk = (n1 - n0 + 63) / 64;
+    int sp = (kCommitWaves + nblk - 1) / nblk;
+    sp = sp > R.nbN ? R.nbN : sp;
+    c.jb = (R.nbN + sp - 1) / sp;
+    c.splits = (R.nbN + c.jb * kEW - 1) / (c.jb * kEW);
+    hipLaunchKernelGGL(k_commit_delta, dim3(nblk, c.splits), dim3(64 * kEW), 0, st, c);
   }
-  return hip_status(hipStreamSynchronize(st));
+  return hip_status(hipGetLastError());
 }
-
-}  // extern "C"
