@@ -482,7 +482,7 @@ __device__ __forceinline__ void sym_diag(const SymArgs& a, int I, int w, int lan
 template <int MODE, bool LOCAL>
 __global__ __launch_bounds__(64 * kSymWaves) __attribute__((amdgpu_waves_per_eu(
     MODE == kHvp ? 1 : kSymWavesPerSimd))) void k_sym(SymArgs a) {
-  extern __shared__ double lds[];  // [S][NJ][SB]
+  extern __shared__ __align__(16) double lds[];  // [S][NJ][SB]
   constexpr int NJ = (MODE == kEnergy) ? 1 : 2;
   constexpr bool JSIDE = MODE != kEnergy || LOCAL;  // j-side sums are kept
   __shared__ double ered[16];
@@ -1046,7 +1046,7 @@ __global__ __launch_bounds__(64 * kSym64Waves) __attribute__((amdgpu_waves_per_e
 k_sym64(Sym64Args a) {
   using T = Sym64<MODE, LOCAL>;
   constexpr int SBN = NI * kBlk;
-  extern __shared__ double lds[];  // [W][128] positions (, v), then the ring [W + 1][NJ][SBN]
+  extern __shared__ __align__(16) double lds[];  // [W][128] positions (, v), then the ring [W + 1][NJ][SBN]
   __shared__ double ered[kSym64Waves];
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
@@ -1210,7 +1210,7 @@ struct Sym64ReduceArgs {
 
 template <int MODE, bool LOCAL, int NI>
 __global__ __launch_bounds__(256) void k_sym64_reduce(Sym64ReduceArgs a) {
-  extern __shared__ int32_t lst[];  // [nc][mj]
+  extern __shared__ __align__(16) int32_t lst[];  // [nc][mj]
   constexpr int SBN = NI * kBlk;
   __shared__ double red[4];
   const int t = threadIdx.x;

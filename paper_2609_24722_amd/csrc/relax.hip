@@ -57,26 +57,48 @@ constexpr double kBlockNear = 2.0;
 
 // ------------------------------------------------------ patch construction --
 __device__ __forceinline__ double dist2_rn(double ax, double ay, double bx, double by) {
+#pragma clang fp contract(off)  // the same value in every pass, each operation rounded once
   const double dx = ax - bx, dy = ay - by;
-  return __dadd_rn(__dmul_rn(dx, dx), __dmul_rn(dy, dy));
+  const double a = dx * dx, b = dy * dy;
+  return a + b;
 }
 
-// One workgroup per patch: the size-th smallest squared distance (as the bit
-// pattern of a non-negative double, which orders like the value) is found by
-// an exact 8-pass radix select; the patch is then every charge below that
-// key plus, among charges equal to it, the lowest indices -- listed in
-// increasing index order.
+// One workgroup per patch.  The patch is every charge whose squared distance
+// is below the size-th smallest one, T, plus, among those at exactly T, the
+// lowest indices -- listed in increasing index order.  Distances are compared
+// by the bit pattern of a non-negative double, which orders like the value.
+//
+// T is found in a histogram of kSelBins bins over [0, range), range three
+// times the size-th distance at the mean density (twice at the centre of a
+// conducting disk; charges beyond it are not counted); the few charges of T's
+// bin are then ranked exactly.  If the histogram holds fewer than size charges,
+// or T's bin more than kSelList (clustered charges), an exact 8-pass radix
+// select finds T instead.  Each wave reads a contiguous sixteenth of the
+// charges, so that the index order needs no barrier inside a pass, and the
+// first pass lists its charges in range (in LDS, in order): the two passes
+// after it read only those (a wave with more than kSelCand: its range again).
+// Bound: issue of the first pass (a workgroup per CU, about 30 instructions a
+// charge).  256 patches at N = 1e5: 768 us with the radix select's ten passes,
+// whose first ones counted nearly all charges into one bin; 95 with three
+// passes over all charges; 56 with the lists.
+constexpr int kSelBins = 4096;
+constexpr int kSelList = 1024;
+constexpr int kSelCand = 1280;
 __global__ __launch_bounds__(1024) void k_patch_select(const double* __restrict__ x,
                                                        const double* __restrict__ y, int n,
                                                        const int32_t* __restrict__ centres,
                                                        const int32_t* __restrict__ ptr,
                                                        int32_t* __restrict__ out,
                                                        int32_t* __restrict__ err) {
-  __shared__ uint32_t hist[256];
-  __shared__ uint64_t s_prefix, s_mask;
-  __shared__ uint32_t s_need;
-  __shared__ uint32_t lt_cnt[1024], eq_cnt[1024];
-  const int p = blockIdx.x, t = threadIdx.x;
+  __shared__ __align__(16) uint32_t hist[kSelBins];  // read four at a time
+  __shared__ uint64_t lkey[kSelList];
+  __shared__ uint8_t lwave[kSelList];
+  __shared__ uint32_t wsum[16], lt_w[16], eq_w[16], s_need, s_cnt;
+  __shared__ int s_bin;
+  __shared__ uint64_t s_T, s_mask;
+  __shared__ int32_t cand[16][kSelCand];
+  const int p = blockIdx.x, t = threadIdx.x, lane = t & 63;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
   const int size = ptr[p + 1] - ptr[p];
   const int ctr = centres[p];
   if (ctr < 0 || ctr >= n) {  // invalid centre: report, write nothing
@@ -84,63 +106,202 @@ __global__ __launch_bounds__(1024) void k_patch_select(const double* __restrict_
     return;
   }
   const double cx = x[ctr], cy = y[ctr];
+  const double scale = (double)kSelBins * (double)n / (3.0 * (double)size);
+  const int per = (n + 1023) / 1024 * 64, j0 = min(n, w * per), j1 = min(n, j0 + per);
+  auto bin_of = [&](double d) {
+    const double f = d * scale;
+    return f < (double)kSelBins ? (int)f : kSelBins;  // also beyond the range, or NaN
+  };
+  // the wave's range, 64 charges at a time: f(index, distance, lane in range)
+  auto sweep = [&](auto f) {
+    // eight blocks' loads go out together
+    int b = j0;
+    for (; b + 512 <= j1; b += 512) {
+      const double *px = x + b + lane, *py = y + b + lane;
+      double vx[8], vy[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        vx[q] = px[q * 64];
+        vy[q] = py[q * 64];
+      }
+#pragma unroll
+      for (int q = 0; q < 8; ++q) f(b + q * 64 + lane, dist2_rn(vx[q], vy[q], cx, cy), true);
+    }
+    for (; b < j1; b += 512) {
+      double vx[8], vy[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int j = min(b + q * 64 + lane, j1 - 1);
+        vx[q] = x[j];
+        vy[q] = y[j];
+      }
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int j = b + q * 64 + lane;
+        if (b + q * 64 < j1) f(j, dist2_rn(vx[q], vy[q], cx, cy), j < j1);
+      }
+    }
+  };
+  for (int q = t; q < kSelBins; q += 1024) hist[q] = 0;
+  if (t < 16) lt_w[t] = eq_w[t] = 0;
   if (t == 0) {
-    s_prefix = 0;
-    s_mask = 0;
-    s_need = (uint32_t)size;
+    s_bin = -1;
+    s_cnt = 0;
   }
   __syncthreads();
-  for (int pass = 0; pass < 8; ++pass) {
-    const int shift = 56 - 8 * pass;
-    if (t < 256) hist[t] = 0;
+  const uint64_t below_me = lane ? (~0ull >> (64 - lane)) : 0ull;
+  int nc = 0;  // charges in range of the wave
+  const double beyond = (double)kSelBins / scale * (1.0 + 1e-12);  // no bin from here on
+  sweep([&](int j, double d, bool in) {
+    if (!__ballot(in && d < beyond)) return;
+    const int q = bin_of(d);
+    const bool hit = in && q < kSelBins;
+    const uint64_t m = __ballot(hit);
+    const int e = nc + __popcll(m & below_me);
+    if (hit) {
+      atomicAdd(&hist[q], 1u);
+      if (e < kSelCand) cand[w][e] = j;
+    }
+    nc += __popcll(m);
+  });
+  // the wave's listed charges, in order
+  auto sweep_cand = [&](auto f) {
+    for (int b = 0; b < nc; b += 256) {
+      int j[4];
+      double vx[4], vy[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) j[q] = cand[w][min(b + q * 64 + lane, nc - 1)];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        vx[q] = x[j[q]];
+        vy[q] = y[j[q]];
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (b + q * 64 < nc) f(j[q], dist2_rn(vx[q], vy[q], cx, cy), b + q * 64 + lane < nc);
+    }
+  };
+  __syncthreads();
+  {
+    // the bin where the running count reaches size (thread: four bins)
+    const uint4 c = reinterpret_cast<const uint4*>(hist)[t];
+    const uint32_t own = c.x + c.y + c.z + c.w;
+    uint32_t v = own;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t u = __shfl_up(v, off, 64);
+      if (lane >= off) v += u;
+    }
+    if (lane == 63) wsum[w] = v;
     __syncthreads();
-    const uint64_t pre = s_prefix, msk = s_mask;
-    for (int j = t; j < n; j += blockDim.x) {
-      const uint64_t key = __double_as_longlong(dist2_rn(x[j], y[j], cx, cy));
-      if ((key & msk) == pre) atomicAdd(&hist[(key >> shift) & 255u], 1u);
+    for (int q = 0; q < w; ++q) v += wsum[q];
+    uint32_t before = v - own;
+    const uint32_t need = (uint32_t)size;
+    if (before < need && v >= need) {
+      int q = 4 * t;
+      const uint32_t cc[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+      for (int r = 0; r < 3; ++r)
+        if (q == 4 * t + r && before + cc[r] < need) {
+          before += cc[r];
+          ++q;
+        }
+      s_bin = q;
+      s_need = need - before;  // T is the s_need-th smallest of the bin
+    }
+  }
+  __syncthreads();
+  const int bin = s_bin;
+  const bool ranked = bin >= 0 && hist[bin] <= (uint32_t)kSelList, listed = ranked && nc <= kSelCand;
+  if (ranked) {
+    uint32_t lt = 0;
+    auto rank = [&](int, double d, bool in) {
+      const int q = bin_of(d);
+      lt += __popcll(__ballot(in && q < bin));
+      if (in && q == bin) {
+        const uint32_t e = atomicAdd(&s_cnt, 1u);
+        lkey[e] = __double_as_longlong(d);
+        lwave[e] = (uint8_t)w;
+      }
+    };
+    if (listed) sweep_cand(rank);
+    else sweep(rank);
+    if (lane == 0) lt_w[w] = lt;
+    __syncthreads();
+    const uint32_t m = s_cnt, need = s_need;
+    uint64_t key = 0;
+    uint32_t below = 0, same = 0;
+    if ((uint32_t)t < m) {
+      key = lkey[t];
+      for (uint32_t e = 0; e < m; ++e) {
+        below += lkey[e] < key;
+        same += lkey[e] == key;
+      }
+      if (below < need && below + same >= need) s_T = key;  // the same key from every such thread
     }
     __syncthreads();
+    if ((uint32_t)t < m) {
+      if (key < s_T) atomicAdd(&lt_w[lwave[t]], 1u);
+      else if (key == s_T) atomicAdd(&eq_w[lwave[t]], 1u);
+    }
+  } else {
     if (t == 0) {
-      uint32_t need = s_need, b = 0;
-      while (b < 255 && hist[b] < need) need -= hist[b++];
-      s_need = need;
-      s_prefix = pre | ((uint64_t)b << shift);
-      s_mask = msk | ((uint64_t)255 << shift);
+      s_T = 0;
+      s_mask = 0;
+      s_need = (uint32_t)size;
     }
     __syncthreads();
+    for (int pass = 0; pass < 8; ++pass) {
+      const int shift = 56 - 8 * pass;
+      if (t < 256) hist[t] = 0;
+      __syncthreads();
+      const uint64_t pre = s_T, msk = s_mask;
+      sweep([&](int, double d, bool in) {
+        const uint64_t key = __double_as_longlong(d);
+        if (in && (key & msk) == pre) atomicAdd(&hist[(key >> shift) & 255u], 1u);
+      });
+      __syncthreads();
+      if (t == 0) {
+        uint32_t need = s_need, b = 0;
+        while (b < 255 && hist[b] < need) need -= hist[b++];
+        s_need = need;
+        s_T = pre | ((uint64_t)b << shift);
+        s_mask = msk | ((uint64_t)255 << shift);
+      }
+      __syncthreads();
+    }
+    const uint64_t T = s_T;
+    uint32_t lt = 0, eq = 0;
+    sweep([&](int, double d, bool in) {
+      const uint64_t key = __double_as_longlong(d);
+      lt += __popcll(__ballot(in && key < T));
+      eq += __popcll(__ballot(in && key == T));
+    });
+    if (lane == 0) {
+      lt_w[w] = lt;
+      eq_w[w] = eq;
+    }
   }
-  const uint64_t T = s_prefix;
-  const uint32_t need_eq = s_need;  // how many charges at exactly T belong to the patch
-  const int chunk = (n + blockDim.x - 1) / blockDim.x;
-  const int j0 = min(n, t * chunk), j1 = min(n, j0 + chunk);
-  uint32_t lt = 0, eq = 0;
-  for (int j = j0; j < j1; ++j) {
-    const uint64_t key = __double_as_longlong(dist2_rn(x[j], y[j], cx, cy));
-    lt += key < T;
-    eq += key == T;
-  }
-  lt_cnt[t] = lt;
-  eq_cnt[t] = eq;
   __syncthreads();
-  for (int off = 1; off < (int)blockDim.x; off <<= 1) {
-    const uint32_t a = t >= off ? lt_cnt[t - off] : 0u, b = t >= off ? eq_cnt[t - off] : 0u;
-    __syncthreads();
-    lt_cnt[t] += a;
-    eq_cnt[t] += b;
-    __syncthreads();
+  const uint64_t T = s_T;
+  uint32_t lt_all = 0, lt_before = 0, eq_before = 0;
+  for (int q = 0; q < 16; ++q) {
+    lt_all += lt_w[q];
+    lt_before += q < w ? lt_w[q] : 0u;
+    eq_before += q < w ? eq_w[q] : 0u;
   }
-  uint32_t lt_before = lt_cnt[t] - lt, eq_before = eq_cnt[t] - eq;
+  const uint32_t need_eq = (uint32_t)size - lt_all;  // how many charges at exactly T belong to it
   int32_t* dst = out + ptr[p];
-  for (int j = j0; j < j1; ++j) {
-    const uint64_t key = __double_as_longlong(dist2_rn(x[j], y[j], cx, cy));
-    if (key < T) {
-      dst[lt_before + min(eq_before, need_eq)] = j;
-      ++lt_before;
-    } else if (key == T) {
-      if (eq_before < need_eq) dst[lt_before + eq_before] = j;
-      ++eq_before;
-    }
-  }
+  auto list = [&](int j, double d, bool in) {
+    const uint64_t key = __double_as_longlong(d);
+    const uint64_t ml = __ballot(in && key < T), me = __ballot(in && key == T);
+    const uint32_t l = lt_before + __popcll(ml & below_me), e = eq_before + __popcll(me & below_me);
+    if (in && (key < T || (key == T && e < need_eq))) dst[l + min(e, need_eq)] = j;
+    lt_before += __popcll(ml);
+    eq_before += __popcll(me);
+  };
+  if (listed) sweep_cand(list);
+  else sweep(list);
 }
 
 // ------------------------------------------------------------- relax state --

@@ -63,7 +63,7 @@ __device__ __forceinline__ uint32_t morton_key(double x, double y) {
 __global__ __launch_bounds__(kRankThreads) void k_rank(const double* __restrict__ x,
                                                        const double* __restrict__ y, int n,
                                                        int32_t* __restrict__ perm) {
-  extern __shared__ uint32_t key[];  // n rounded up to 4 * 16 keys, then the waves' counts
+  extern __shared__ __align__(16) uint32_t key[];  // n rounded up to 4 * 16 keys, then the waves' counts
   const int t = threadIdx.x, lane = t & 63;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
   constexpr int NW = kRankThreads / 64;
