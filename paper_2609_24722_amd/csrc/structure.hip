@@ -47,6 +47,21 @@ __host__ __device__ inline Grid make_grid(int64_t n) {
   return q;
 }
 
+constexpr int kScanE = 4 * kScanT;  // counts per workgroup of the scan
+// Convex-hull candidates: extreme charges in kHullDirs directions, one row of
+// them per wave of kHullPer charges; the candidates' copies.
+constexpr int kHullDirs = 64;
+constexpr int kHullPer = 128;
+struct HullRow {
+  double v[kHullDirs];
+  int32_t i[kHullDirs];
+};
+struct HullPoint {
+  double x, y;
+  int64_t i;  // entry 0 holds the count
+};
+static int hull_rows(int64_t n) { return (int)((n + kHullPer - 1) / kHullPer); }
+
 size_t structure_workspace_bytes(int64_t n) {
   const Grid g = make_grid(n);
   const size_t cells = (size_t)g.G * g.G;
@@ -56,6 +71,9 @@ size_t structure_workspace_bytes(int64_t n) {
   cv.take<int32_t>((size_t)n);  // cell of each charge
   cv.take<int32_t>((size_t)n);  // charges by cell
   cv.take<int32_t>((size_t)n);  // convex-hull flags
+  cv.take<int32_t>(cells / kScanE + 1);  // scan sums
+  cv.take<HullRow>((size_t)hull_rows(n) + 1);
+  cv.take<HullPoint>((size_t)n + 1);
   return cv.off + 256;
 }
 
@@ -78,32 +96,58 @@ __global__ void k_cell_count(const double* __restrict__ x, const double* __restr
   atomicAdd(&count[c], 1);
 }
 
-// Exclusive scan of m counts in place (one workgroup, chunks of kScanT with a
-// running carry); a[m] receives the total.
-__global__ __launch_bounds__(kScanT) void k_cell_scan(int32_t* __restrict__ a, int m) {
-  __shared__ int32_t ws[kScanT / 64];
-  int carry = 0;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  for (int c0 = 0; c0 < m; c0 += kScanT) {
-    const int i = c0 + threadIdx.x;
-    const int v = i < m ? a[i] : 0;
-    int s = v;
-    for (int off = 1; off < 64; off <<= 1) {
-      const int u = __shfl_up(s, off, 64);
-      if (lane >= off) s += u;
-    }
-    if (lane == 63) ws[w] = s;
-    __syncthreads();
-    int before = 0, total = 0;
-    for (int q = 0; q < kScanT / 64; ++q) {
-      before += q < w ? ws[q] : 0;
-      total += ws[q];
-    }
-    __syncthreads();
-    if (i < m) a[i] = carry + before + s - v;
-    carry += total;
+// Exclusive scan of m counts in place, a[m] = the total: one workgroup per
+// kScanE counts; the first launch writes each workgroup's sum, the second adds
+// up the sums before its own (4096 of them at most: 2 passes over the counts
+// instead of one workgroup's 98 rounds at m = 1e5, 104 us).
+__device__ __forceinline__ int wg_total(int v, int* ws) {
+  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+  if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = v;
+  __syncthreads();
+  int t = 0;
+  for (int q = 0; q < kScanT / 64; ++q) t += ws[q];
+  __syncthreads();
+  return t;
+}
+__global__ __launch_bounds__(kScanT) void k_scan_sums(const int32_t* __restrict__ a, int m,
+                                                      int32_t* __restrict__ sums) {
+  __shared__ int ws[kScanT / 64];
+  int v = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int i = blockIdx.x * kScanE + q * kScanT + threadIdx.x;
+    v += i < m ? a[i] : 0;
   }
-  if (threadIdx.x == 0) a[m] = carry;
+  v = wg_total(v, ws);
+  if (threadIdx.x == 0) sums[blockIdx.x] = v;
+}
+__global__ __launch_bounds__(kScanT) void k_scan_write(int32_t* __restrict__ a, int m,
+                                                       const int32_t* __restrict__ sums) {
+  __shared__ int ws[kScanT / 64];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  int before = 0;
+  for (int q = t; q < (int)blockIdx.x; q += kScanT) before += sums[q];
+  before = wg_total(before, ws);
+  const int i0 = blockIdx.x * kScanE + 4 * t;
+  int v[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) v[q] = i0 + q < m ? a[i0 + q] : 0;
+  const int own = (v[0] + v[1]) + (v[2] + v[3]);
+  int s = own;
+  for (int off = 1; off < 64; off <<= 1) {
+    const int u = __shfl_up(s, off, 64);
+    if (lane >= off) s += u;
+  }
+  if (lane == 63) ws[w] = s;
+  __syncthreads();
+  for (int q = 0; q < w; ++q) s += ws[q];
+  int e = before + s - own;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    if (i0 + q < m) a[i0 + q] = e;
+    e += v[q];
+    if (i0 + q == m - 1) a[m] = e;
+  }
 }
 
 __global__ void k_cell_fill(int n, const int32_t* __restrict__ cell,
@@ -130,6 +174,103 @@ __global__ void k_cell_sort(int m, const int32_t* __restrict__ start, int32_t* _
     }
     slot[q + 1] = v;
   }
+}
+
+// Hull candidates.  The extreme charges of kHullDirs directions span a convex
+// polygon inside the hull; a charge clearly inside the polygon is no hull
+// vertex.  What is left (the outermost rings) goes to the host, whose monotone
+// chain decides exactly as it would among all charges (sorting all 1e5 of them
+// there took 7 of the call's 11 ms).
+// One wave per kHullPer charges, one direction per lane.
+__global__ __launch_bounds__(256) void k_hull_rows(const double* __restrict__ x,
+                                                   const double* __restrict__ y, int n, int rows,
+                                                   HullRow* __restrict__ out) {
+  const int r = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+  const int lane = threadIdx.x & 63;
+  if (r >= rows) return;
+  double c, sn;
+  sincospi(2.0 * lane / kHullDirs, &sn, &c);
+  const int j0 = r * kHullPer, j1 = min(n, j0 + kHullPer);
+  double best = -1e300;
+  int bi = j0;
+#pragma unroll 8
+  for (int j = j0; j < j1; ++j) {
+    const double v = c * x[j] + sn * y[j];
+    if (v > best) {
+      best = v;
+      bi = j;
+    }
+  }
+  out[r].v[lane] = best;
+  out[r].i[lane] = bi;
+}
+// rows[0] gets the extreme of all rows; the candidate count is cleared.
+__global__ __launch_bounds__(1024) void k_hull_extremes(HullRow* __restrict__ rows, int m,
+                                                        HullPoint* __restrict__ pts) {
+  __shared__ double v[16][kHullDirs];
+  __shared__ int32_t i[16][kHullDirs];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  double best = -1e300;
+  int bi = 0;
+#pragma unroll 4
+  for (int r = w; r < m; r += 16) {
+    const double q = rows[r].v[lane];
+    const int qi = rows[r].i[lane];
+    if (q > best) {
+      best = q;
+      bi = qi;
+    }
+  }
+  v[w][lane] = best;
+  i[w][lane] = bi;
+  __syncthreads();
+  if (w > 0) return;
+  for (int q = 1; q < 16; ++q)
+    if (v[q][lane] > best) {
+      best = v[q][lane];
+      bi = i[q][lane];
+    }
+  rows[m].i[lane] = bi;  // row m: the result
+  if (lane == 0) pts[0].i = 0;
+}
+// Lists the charges not clearly inside the polygon (in any order).
+__global__ __launch_bounds__(256) void k_hull_candidates(const double* __restrict__ x,
+                                                         const double* __restrict__ y, int n,
+                                                         const HullRow* __restrict__ ext,
+                                                         HullPoint* __restrict__ pts) {
+  __shared__ double ex[kHullDirs], ey[kHullDirs];
+  if (threadIdx.x < kHullDirs) {
+    const int e = ext->i[threadIdx.x];
+    ex[threadIdx.x] = x[e];
+    ey[threadIdx.x] = y[e];
+  }
+  __syncthreads();
+  const int j = blockIdx.x * 256 + threadIdx.x;
+  if (j >= n) return;
+  const double px = x[j], py = y[j];
+  // left of every edge by more than rounding (NaN: not inside); repeated
+  // extremes have no edge, and fewer than three of them enclose nothing
+  bool inside = true;
+  int edges = 0;
+  for (int k = 0; k < kHullDirs && inside; ++k) {
+    const double ax = ex[k], ay = ey[k];
+    const double bx = ex[(k + 1) % kHullDirs], by = ey[(k + 1) % kHullDirs];
+    const double dx = bx - ax, dy = by - ay;
+    if (dx == 0.0 && dy == 0.0) continue;
+    ++edges;
+    inside = dx * (py - ay) - dy * (px - ax) > 1e-9 * (fabs(dx) + fabs(dy));
+  }
+  if (inside && edges >= 3) return;
+  const unsigned long long e = atomicAdd((unsigned long long*)&pts[0].i, 1ull);
+  HullPoint q;
+  q.x = px;
+  q.y = py;
+  q.i = j;
+  pts[e + 1] = q;
+}
+__global__ void k_set_flags(const int32_t* __restrict__ list, int m, int32_t* __restrict__ flags) {
+  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+  if (k < m) flags[list[k]] = 1;
 }
 
 // Clip the square of half-width B around r_i by the bisectors of the charges
@@ -352,19 +493,32 @@ __global__ __launch_bounds__(kScanT) void k_structure_stats(const int32_t* __res
   const int t = threadIdx.x;
   int32_t c[8] = {0, 0, 0, 0, 0, 0, 0, 0};  // z = 4..8, bounded, hull, unresolved
   double a = 0.0;
-  for (int i = t; i < n; i += kScanT) {
-    const int zi = z[i];
-    if (zi >= 0) {
-      ++c[5];
-      if (zi >= 4 && zi <= 8) ++c[zi - 4];
-      if (psi6) {
-        const double re = psi6[2 * i], im = psi6[2 * i + 1];
-        a += sqrt(re * re + im * im);
+  // eight charges' loads go out together (one at a time the pass waited 98
+  // times on memory at n = 1e5: 84 us)
+  for (int i0 = t; i0 < n; i0 += 8 * kScanT) {
+    int zq[8];
+    double2 pq[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int i = min(i0 + q * kScanT, n - 1);
+      zq[q] = z[i];
+      pq[q] = psi6 ? make_double2(psi6[2 * (size_t)i], psi6[2 * (size_t)i + 1])
+                   : make_double2(0.0, 0.0);
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      if (i0 + q * kScanT >= n) continue;
+      const int zi = zq[q];
+      if (zi >= 0) {
+        ++c[5];
+#pragma unroll
+        for (int k = 0; k < 5; ++k) c[k] += zi == k + 4;
+        if (psi6) a += sqrt(pq[q].x * pq[q].x + pq[q].y * pq[q].y);
+      } else if (zi == -2) {
+        ++c[6];
+      } else {
+        ++c[7];
       }
-    } else if (zi == -2) {
-      ++c[6];
-    } else {
-      ++c[7];
     }
   }
   s_abs[t] = a;
@@ -389,16 +543,33 @@ __global__ __launch_bounds__(kScanT) void k_structure_stats(const int32_t* __res
 }
 
 #pragma clang fp contract(off)
-__global__ void k_radial(const double* __restrict__ x, const double* __restrict__ y, int n,
-                         int nbins, int32_t* __restrict__ counts) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const double a = x[i] * x[i], b = y[i] * y[i];
-  const double r = sqrt(a + b);
-  const double f = floor(r * (double)nbins);
-  int k = f < 0.0 ? 0 : (f >= (double)nbins ? nbins - 1 : (int)f);
-  if (!(r == r)) k = nbins - 1;  // NaN
-  atomicAdd(&counts[k], 1);
+// Up to kRadLds bins: counted per workgroup in LDS, one global add per bin and
+// workgroup that has any (every charge adding to global memory took 681 us for
+// 50 bins and 1e5 charges, which are few addresses).
+constexpr int kRadLds = 8192, kRadT = 1024;
+template <bool LDS>
+__global__ __launch_bounds__(kRadT) void k_radial(const double* __restrict__ x,
+                                                  const double* __restrict__ y, int n, int nbins,
+                                                  int32_t* __restrict__ counts) {
+  extern __shared__ int32_t loc[];
+  if (LDS) {
+    for (int k = threadIdx.x; k < nbins; k += kRadT) loc[k] = 0;
+    __syncthreads();
+  }
+  int32_t* const to = LDS ? loc : counts;
+  for (int i = blockIdx.x * kRadT + threadIdx.x; i < n; i += gridDim.x * kRadT) {
+    const double a = x[i] * x[i], b = y[i] * y[i];
+    const double r = sqrt(a + b);
+    const double f = floor(r * (double)nbins);
+    int k = f < 0.0 ? 0 : (f >= (double)nbins ? nbins - 1 : (int)f);
+    if (!(r == r)) k = nbins - 1;  // NaN
+    atomicAdd(&to[k], 1);
+  }
+  if (LDS) {
+    __syncthreads();
+    for (int k = threadIdx.x; k < nbins; k += kRadT)
+      if (loc[k]) atomicAdd(&counts[k], loc[k]);
+  }
 }
 #pragma clang fp contract(on)
 
@@ -409,28 +580,28 @@ using namespace cd;
 namespace {
 
 // Vertices of the convex hull (Andrew's monotone chain; points on an edge
-// between two vertices are not vertices).  flags[i] = 1 for a vertex.
-void hull_flags(const std::vector<double>& x, const std::vector<double>& y,
-                std::vector<int32_t>& flags) {
-  const int n = (int)x.size();
-  std::vector<int> o(n);
-  for (int i = 0; i < n; ++i) o[i] = i;
-  std::sort(o.begin(), o.end(), [&](int a, int b) { return x[a] < x[b] || (x[a] == x[b] && y[a] < y[b]); });
+// between two vertices are not vertices) among p; their indices.
+std::vector<int32_t> hull_of(std::vector<HullPoint>& p) {
+  std::sort(p.begin(), p.end(), [](const HullPoint& a, const HullPoint& b) {
+    return a.x != b.x ? a.x < b.x : a.y != b.y ? a.y < b.y : a.i < b.i;
+  });
+  const int n = (int)p.size();
   auto cross = [&](int a, int b, int c) {
-    return (x[b] - x[a]) * (y[c] - y[a]) - (y[b] - y[a]) * (x[c] - x[a]);
+    return (p[b].x - p[a].x) * (p[c].y - p[a].y) - (p[b].y - p[a].y) * (p[c].x - p[a].x);
   };
   std::vector<int> h(2 * (size_t)n + 2);
   int k = 0;
   for (int t = 0; t < n; ++t) {  // lower hull
-    while (k >= 2 && cross(h[k - 2], h[k - 1], o[t]) <= 0.0) --k;
-    h[k++] = o[t];
+    while (k >= 2 && cross(h[k - 2], h[k - 1], t) <= 0.0) --k;
+    h[k++] = t;
   }
   for (int t = n - 2, lo = k + 1; t >= 0; --t) {  // upper hull
-    while (k >= lo && cross(h[k - 2], h[k - 1], o[t]) <= 0.0) --k;
-    h[k++] = o[t];
+    while (k >= lo && cross(h[k - 2], h[k - 1], t) <= 0.0) --k;
+    h[k++] = t;
   }
-  flags.assign(n, 0);
-  for (int t = 0; t < k; ++t) flags[h[t]] = 1;
+  std::vector<int32_t> out(k);
+  for (int t = 0; t < k; ++t) out[t] = (int32_t)p[h[t]].i;
+  return out;
 }
 
 }  // namespace
@@ -450,28 +621,53 @@ int voronoi_coordination(const double* x, const double* y, int64_t n, int32_t* z
   int32_t* cell = cv.take<int32_t>((size_t)n);
   int32_t* slot = cv.take<int32_t>((size_t)n);
   int32_t* hullf = cv.take<int32_t>((size_t)n);
+  int32_t* sums = cv.take<int32_t>((size_t)cells / kScanE + 1);
+  HullRow* rows = cv.take<HullRow>((size_t)hull_rows(n) + 1);
+  HullPoint* pts = cv.take<HullPoint>((size_t)n + 1);
   hipStream_t st = (hipStream_t)stream;
   const int nn = (int)n;
   double Rb = 0.0;  // radius of a disk about the origin that holds every charge
   {
-    std::vector<double> hx(n), hy(n);
-    std::vector<int32_t> hf;
-    int rc = hip_status(hipMemcpyAsync(hx.data(), x, sizeof(double) * n, hipMemcpyDeviceToHost, st));
-    if (!rc) rc = hip_status(hipMemcpyAsync(hy.data(), y, sizeof(double) * n, hipMemcpyDeviceToHost, st));
-    if (!rc) rc = hip_status(hipStreamSynchronize(st));
-    if (rc) return rc;
-    hull_flags(hx, hy, hf);
-    for (int64_t i = 0; i < n; ++i) Rb = fmax(Rb, sqrt(hx[i] * hx[i] + hy[i] * hy[i]));
+    const int m = hull_rows(n);
+    hipLaunchKernelGGL(k_hull_rows, dim3((m + 3) / 4), dim3(256), 0, st, x, y, nn, m, rows);
+    hipLaunchKernelGGL(k_hull_extremes, dim3(1), dim3(1024), 0, st, rows, m, pts);
+    hipLaunchKernelGGL(k_hull_candidates, dim3((nn + 255) / 256), dim3(256), 0, st, x, y, nn,
+                       rows + m, pts);
+    hipLaunchKernelGGL(k_fill_int, dim3((nn + 255) / 256), dim3(256), 0, st, hullf, nn, 0);
+    // the count and, in most cases, all candidates in one copy
+    const size_t first = std::min<size_t>((size_t)n, 8192);
+    std::vector<HullPoint> p(first + 1);
+    auto fetch = [&](size_t at, size_t cnt) {
+      int e = hip_status(hipMemcpyAsync(p.data() + at, pts + at, sizeof(HullPoint) * cnt,
+                                        hipMemcpyDeviceToHost, st));
+      return e ? e : hip_status(hipStreamSynchronize(st));
+    };
+    int rc = hip_status(hipGetLastError());
+    if (rc || (rc = fetch(0, first + 1))) return rc;
+    const size_t cnt = (size_t)p[0].i;
+    p.resize(cnt + 1);
+    if (cnt > first && (rc = fetch(first + 1, cnt - first))) return rc;
+    p.erase(p.begin());
+    for (const HullPoint& q : p) Rb = fmax(Rb, sqrt(q.x * q.x + q.y * q.y));
     Rb = Rb * (1.0 + 1e-12) + 1e-300;
-    rc = hip_status(hipMemcpyAsync(hullf, hf.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice, st));
-    if (!rc) rc = hip_status(hipStreamSynchronize(st));  // hf is released on return
+    const std::vector<int32_t> hull = hull_of(p);
+    // the candidates' room holds the list of vertices
+    int32_t* list = reinterpret_cast<int32_t*>(pts);
+    rc = hip_status(hipMemcpyAsync(list, hull.data(), sizeof(int32_t) * hull.size(),
+                                   hipMemcpyHostToDevice, st));
+    if (!rc) rc = hip_status(hipStreamSynchronize(st));  // hull is released on return
     if (rc) return rc;
+    hipLaunchKernelGGL(k_set_flags, dim3((unsigned)((hull.size() + 255) / 256)), dim3(256), 0, st,
+                       list, (int)hull.size(), hullf);
   }
   hipLaunchKernelGGL(k_fill_int, dim3((cells + 256) / 256), dim3(256), 0, st, start, cells + 1, 0);
   hipLaunchKernelGGL(k_fill_int, dim3((cells + 255) / 256), dim3(256), 0, st, cursor, cells, 0);
   hipLaunchKernelGGL(k_cell_count, dim3((nn + 255) / 256), dim3(256), 0, st, x, y, nn, g, start,
                      cell);
-  hipLaunchKernelGGL(k_cell_scan, dim3(1), dim3(kScanT), 0, st, start, cells);
+  hipLaunchKernelGGL(k_scan_sums, dim3((cells + kScanE - 1) / kScanE), dim3(kScanT), 0, st, start,
+                     cells, sums);
+  hipLaunchKernelGGL(k_scan_write, dim3((cells + kScanE - 1) / kScanE), dim3(kScanT), 0, st, start,
+                     cells, sums);
   hipLaunchKernelGGL(k_cell_fill, dim3((nn + 255) / 256), dim3(256), 0, st, nn, cell, start,
                      cursor, slot);
   hipLaunchKernelGGL(k_cell_sort, dim3((cells + 255) / 256), dim3(256), 0, st, cells, start, slot);
@@ -486,8 +682,14 @@ int radial_histogram(const double* x, const double* y, int64_t n, int32_t nbins,
     return CD_ERR_INVALID_ARG;
   hipStream_t st = (hipStream_t)stream;
   hipLaunchKernelGGL(k_fill_int, dim3((nbins + 255) / 256), dim3(256), 0, st, counts, nbins, 0);
-  hipLaunchKernelGGL(k_radial, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, x, y, (int)n,
-                     nbins, counts);
+  if (nbins <= kRadLds) {
+    const unsigned wg = (unsigned)std::min<int64_t>((n + kRadT - 1) / kRadT, 256);
+    hipLaunchKernelGGL(k_radial<true>, dim3(wg), dim3(kRadT), sizeof(int32_t) * nbins, st, x, y,
+                       (int)n, nbins, counts);
+  } else {
+    hipLaunchKernelGGL(k_radial<false>, dim3((unsigned)((n + kRadT - 1) / kRadT)), dim3(kRadT), 0,
+                       st, x, y, (int)n, nbins, counts);
+  }
   return hip_status(hipGetLastError());
 }
 
