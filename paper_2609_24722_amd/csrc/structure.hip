@@ -3,7 +3,7 @@
 //
 // Voronoi cells.  The charges are binned on a uniform grid of cells about
 // one mean spacing wide (counting sort; each cell's list is then put in
-// index order, so everything downstream is deterministic).  One thread per
+// index order, so everything downstream is deterministic).  One wave per
 // charge i clips a large square around r_i by the bisector half-plane of
 // every charge j in the (2R+1)^2 cells around its own (Sutherland-Hodgman in
 // coordinates relative to r_i, FP64); each polygon edge remembers the charge
@@ -12,8 +12,8 @@
 // unbounded where the block reaches the grid's edge); it can cut a vertex v
 // only if |r_j - r_i| < 2|v|.  So a bounded cell is final when every vertex
 // satisfies 2|v| <= D; otherwise the search widens (k_voronoi).  Charges on
-// the convex hull (host code, monotone chain) have unbounded cells and report
-// z = -2.
+// the convex hull (host code, monotone chain among the charges outside a
+// polygon of extreme ones) have unbounded cells and report z = -2.
 // z_i = number of bisector edges = Voronoi (Delaunay) neighbours;
 // psi_6(i) = (1/z_i) sum_j u_ij^6, u_ij = (r_j - r_i)/|r_j - r_i| as a complex
 // number.
@@ -273,59 +273,6 @@ __global__ void k_set_flags(const int32_t* __restrict__ list, int m, int32_t* __
   if (k < m) flags[list[k]] = 1;
 }
 
-// Clip the square of half-width B around r_i by the bisectors of the charges
-// in cells [x0, x1] x [y0, y1], taken ring by ring around the home cell
-// (cx, cy) so that near charges cut first; a charge of ring k >= 1 lies at
-// least (k - 1) c from r_i and can cut only vertices farther than half that,
-// so the rings stop once (k - 1) c >= 2 max|v|.  Returns the vertex count
-// (kVorMaxV + 1 on overflow) with the polygon in buffer `cur`.
-__device__ __forceinline__ bool clip_one(double dx, double dy, int j, int& nv, int& cur,
-                                         double (&px)[2][kVorMaxV], double (&py)[2][kVorMaxV],
-                                         int (&lab)[2][kVorMaxV]) {
-  const double hd = 0.5 * (dx * dx + dy * dy);
-  if (!(hd > 0.0)) return true;  // a coincident charge has no bisector
-  // f(v) = v.d - |d|^2/2 <= 0 keeps v
-  bool any_out = false;
-  for (int q = 0; q < nv; ++q) any_out |= px[cur][q] * dx + py[cur][q] * dy - hd > 0.0;
-  if (!any_out) return true;
-  const int nx = cur ^ 1;
-  int m = 0;
-  for (int q = 0; q < nv; ++q) {
-    const int r = q + 1 == nv ? 0 : q + 1;
-    const double ax = px[cur][q], ay = py[cur][q], bx = px[cur][r], by = py[cur][r];
-    const double fa = ax * dx + ay * dy - hd, fb = bx * dx + by * dy - hd;
-    if (fa <= 0.0) {
-      if (m < kVorMaxV) {
-        px[nx][m] = ax;
-        py[nx][m] = ay;
-        lab[nx][m] = lab[cur][q];
-      }
-      ++m;
-      if (fb > 0.0) {
-        const double t = fa / (fa - fb);
-        if (m < kVorMaxV) {
-          px[nx][m] = ax + t * (bx - ax);
-          py[nx][m] = ay + t * (by - ay);
-          lab[nx][m] = j;
-        }
-        ++m;
-      }
-    } else if (fb <= 0.0) {
-      const double t = fa / (fa - fb);
-      if (m < kVorMaxV) {
-        px[nx][m] = ax + t * (bx - ax);
-        py[nx][m] = ay + t * (by - ay);
-        lab[nx][m] = lab[cur][q];
-      }
-      ++m;
-    }
-  }
-  cur = nx;
-  if (m > kVorMaxV) return false;
-  nv = m;
-  return true;
-}
-
 // Farthest distance from r_i of a point that could cut vertex v (relative to
 // r_i): such a charge lies in the disk about V = r_i + v through r_i (radius
 // |v|) and in the disk of radius Rb about the origin that holds every
@@ -363,78 +310,166 @@ __device__ double lens_reach(double cx, double cy, double vx, double vy, double 
   }
   return M;
 }
-// lens_reach with slack for rounding, over the polygon's vertices
-__device__ double poly_reach(double xi, double yi, const double* px, const double* py, int nv,
-                             double Rb) {
-  double M = 0.0;
-  for (int q = 0; q < nv; ++q) M = fmax(M, lens_reach(xi, yi, px[q], py[q], Rb));
-  return M * (1.0 + 1e-9) + 1e-12;
-}
-
-__device__ int clip_cell(const double* __restrict__ x, const double* __restrict__ y, int i,
-                         double xi, double yi, const Grid& g, const int32_t* __restrict__ start,
-                         const int32_t* __restrict__ slot, int cx, int cy, int x0, int x1,
-                         int y0, int y1, double B, double Rb, double (&px)[2][kVorMaxV],
-                         double (&py)[2][kVorMaxV], int (&lab)[2][kVorMaxV], int& cur) {
-  cur = 0;
-  int nv = 4;
-  px[0][0] = -B; py[0][0] = -B; lab[0][0] = -1;
-  px[0][1] = B;  py[0][1] = -B; lab[0][1] = -1;
-  px[0][2] = B;  py[0][2] = B;  lab[0][2] = -1;
-  px[0][3] = -B; py[0][3] = B;  lab[0][3] = -1;
-  const int kmax = max(max(cx - x0, x1 - cx), max(cy - y0, y1 - cy));
-  for (int k = 0; k <= kmax; ++k) {
-    if (k >= 2 && (k - 1) * g.c >= poly_reach(xi, yi, px[cur], py[cur], nv, Rb)) break;
-    for (int qy = max(y0, cy - k); qy <= min(y1, cy + k); ++qy) {
-      const bool edge_row = qy == cy - k || qy == cy + k;
-      for (int qx = max(x0, cx - k); qx <= min(x1, cx + k); ++qx) {
-        if (!edge_row && qx != cx - k && qx != cx + k) continue;  // ring k only
-        const int c = qy * g.G + qx;
-        for (int t = start[c]; t < start[c + 1]; ++t) {
-          const int j = slot[t];
-          if (j == i) continue;
-          if (!clip_one(x[j] - xi, y[j] - yi, j, nv, cur, px, py, lab)) return kVorMaxV + 1;
-        }
-      }
-    }
-  }
-  return nv;
-}
-
-// Charges on the convex hull (found on the host) have unbounded cells:
-// z = -2, psi_6 = 0.  For the others the search widens (2, 6, 18, .. cells
-// on each side, then the whole grid) until every vertex's reach (lens_reach)
-// is within the block's margin: no charge outside can cut the polygon.  A
-// certified polygon with an edge on the square belongs to a cell that
-// extends beyond it (a charge next to the hull can have far vertices): the
-// square grows to 1e4 once, at the same range; z = -1 if even that does not
-// hold it, or if the polygon outgrows its vertex arrays.
-__global__ __launch_bounds__(64) void k_voronoi(const double* __restrict__ x,
-                                                const double* __restrict__ y, int n, Grid g,
-                                                const int32_t* __restrict__ start,
-                                                const int32_t* __restrict__ slot,
-                                                const int32_t* __restrict__ hullf,
-                                                double Rb, int32_t* __restrict__ zout,
-                                                double* __restrict__ psi) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
+// Charges on the convex hull have unbounded cells: z = -2, psi_6 = 0.  The cell
+// of any other charge is clipped by one wave, its polygon in LDS.
+//
+// The charges around r_i are taken ring by ring of cells around its own, so
+// that near charges cut first, 64 of a ring at a time, one per lane.  Each lane
+// tests its charge's bisector against the polygon's vertices; the first charge
+// that cuts clips the polygon (one vertex per lane, their places by ballots),
+// the lanes after it that did cut test again (a charge that left the larger
+// polygon whole cuts no part of it), and so on.  A charge of ring k >= 1 lies
+// at least (k - 1) c from r_i, so the rings stop once that is beyond every
+// vertex's reach (lens_reach).
+// The search widens (2, 6, 18, .. cells on each side, then the whole grid) until
+// every vertex's reach is within the block's margin: no charge outside can
+// cut the polygon.  A certified polygon with an edge on the square belongs to a
+// cell that extends beyond it (a charge next to the hull can have far
+// vertices): the square grows to 1e4 once, at the same range; z = -1 if even
+// that does not hold it, or if the polygon outgrows its vertex arrays.
+// Bound: the cuts' chain of LDS reads.  One thread per charge, its polygon in
+// scratch memory, took 2.54 ms at n = 1e5, most of it in the few threads next
+// to the hull whose search widens; a wave per charge takes 0.46 ms.
+constexpr int kVorW = 4;
+__global__ __launch_bounds__(64 * kVorW) void k_voronoi(const double* __restrict__ x,
+                                                        const double* __restrict__ y, int n, Grid g,
+                                                        const int32_t* __restrict__ start,
+                                                        const int32_t* __restrict__ slot,
+                                                        const int32_t* __restrict__ hullf,
+                                                        double Rb, int32_t* __restrict__ zout,
+                                                        double* __restrict__ psi) {
+  __shared__ double s_px[kVorW][2][kVorMaxV], s_py[kVorW][2][kVorMaxV];
+  __shared__ int32_t s_lab[kVorW][2][kVorMaxV], s_pre[kVorW][64], s_st[kVorW][64];
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int sl = blockIdx.x * kVorW + w;  // in cell order: neighbours share the caches
+  if (sl >= n) return;
+  const int i = __builtin_amdgcn_readfirstlane(slot[sl]);
   if (hullf[i]) {  // on the convex hull: unbounded cell
-    zout[i] = -2;
-    if (psi) psi[2 * (size_t)i] = psi[2 * (size_t)i + 1] = 0.0;
+    if (lane == 0) {
+      zout[i] = -2;
+      if (psi) psi[2 * (size_t)i] = psi[2 * (size_t)i + 1] = 0.0;
+    }
     return;
   }
+  auto fence = [] {  // the other lanes' LDS writes before this lane's reads
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
   const double xi = x[i], yi = y[i];
-  double px[2][kVorMaxV], py[2][kVorMaxV];
-  int lab[2][kVorMaxV];
   const int cx = cell_coord(xi, g), cy = cell_coord(yi, g);
   int R = kVorR, cur = 0, nv = 0, z = -1;
   double B = kVorBox;
+  // lens_reach with slack for rounding, over the polygon's vertices
+  auto reach = [&] {
+    const double m = lane < nv ? lens_reach(xi, yi, s_px[w][cur][lane], s_py[w][cur][lane], Rb) : 0.0;
+    return wave_max(m) * (1.0 + 1e-9) + 1e-12;
+  };
   for (;;) {
     const int x0 = max(0, cx - R), x1 = min(g.G - 1, cx + R);
     const int y0 = max(0, cy - R), y1 = min(g.G - 1, cy + R);
-    nv = clip_cell(x, y, i, xi, yi, g, start, slot, cx, cy, x0, x1, y0, y1, B, Rb, px, py, lab,
-                   cur);
-    if (nv > kVorMaxV) break;  // z = -1: more vertices than the polygon holds
+    // the square of half-width B around r_i
+    cur = 0;
+    nv = 4;
+    if (lane < 4) {
+      s_px[w][0][lane] = lane == 1 || lane == 2 ? B : -B;
+      s_py[w][0][lane] = lane >= 2 ? B : -B;
+      s_lab[w][0][lane] = -1;
+    }
+    fence();
+    const int kmax = max(max(cx - x0, x1 - cx), max(cy - y0, y1 - cy));
+    bool over = false;
+    for (int k = 0; k <= kmax && !over; ++k) {
+      if (k >= 2 && (k - 1) * g.c >= reach()) break;
+      // the ring's cells row by row: its first row, two cells of each row
+      // between, its last row
+      const int row = 2 * k + 1, cells = k ? 8 * k : 1;
+      for (int u0 = 0; u0 < cells && !over; u0 += 64) {
+        const int u = u0 + lane;
+        int qx = cx, qy = cy;
+        if (k) {
+          const int v = u - row;
+          qy = u < row ? cy - k : v < 4 * k - 2 ? cy - k + 1 + (v >> 1) : cy + k;
+          qx = u < row ? cx - k + u : v < 4 * k - 2 ? ((v & 1) ? cx + k : cx - k)
+                                                    : cx - k + v - (4 * k - 2);
+        }
+        int st = 0, cnt = 0;
+        if (u < cells && qx >= x0 && qx <= x1 && qy >= y0 && qy <= y1) {
+          const int c = qy * g.G + qx;
+          st = start[c];
+          cnt = start[c + 1] - st;
+        }
+        int pre = cnt;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+          const int q = __shfl_up(pre, off, 64);
+          if (lane >= off) pre += q;
+        }
+        const int total = __builtin_amdgcn_readlane(pre, 63);
+        s_pre[w][lane] = pre - cnt;
+        s_st[w][lane] = st;
+        fence();
+        for (int e0 = 0; e0 < total && !over; e0 += 64) {
+          const int e = e0 + lane;
+          int l = 0;  // the last cell whose first charge is not beyond e
+#pragma unroll
+          for (int b = 32; b >= 1; b >>= 1)
+            if (s_pre[w][l + b] <= e) l += b;
+          const int j = e < total ? slot[s_st[w][l] + e - s_pre[w][l]] : i;
+          const double dx = x[j] - xi, dy = y[j] - yi;
+          const double hd = 0.5 * (dx * dx + dy * dy);
+          // f(v) = v.d - |d|^2/2 <= 0 keeps v; a coincident charge has no bisector
+          auto cuts = [&] {
+            bool out = false;
+            for (int q = 0; q < nv; ++q) out |= s_px[w][cur][q] * dx + s_py[w][cur][q] * dy - hd > 0.0;
+            return out;
+          };
+          uint64_t m = __ballot(j != i && hd > 0.0 && cuts());
+          while (m) {
+            const int f = __builtin_ctzll(m);
+            const double ex = lane_f64(dx, f), ey = lane_f64(dy, f), eh = lane_f64(hd, f);
+            const int ej = __builtin_amdgcn_readlane(j, f);
+            // Sutherland-Hodgman, one vertex per lane: an inside vertex stays,
+            // an edge that crosses gives its crossing
+            const int q = max(min(lane, nv - 1), 0), r = q + 1 >= nv ? 0 : q + 1;
+            const double ax = s_px[w][cur][q], ay = s_py[w][cur][q];
+            const double bx = s_px[w][cur][r], by = s_py[w][cur][r];
+            const int la = s_lab[w][cur][q];
+            const double fa = ax * ex + ay * ey - eh, fb = bx * ex + by * ey - eh;
+            const bool in = lane < nv, keep = in && fa <= 0.0;
+            const bool cross = in && (fa <= 0.0) != (fb <= 0.0);
+            const uint64_t mk = __ballot(keep), mc = __ballot(cross);
+            const int nn = __popcll(mk) + __popcll(mc);
+            if (nn > kVorMaxV) {
+              over = true;
+              break;
+            }
+            int pos = __popcll(mk & lt) + __popcll(mc & lt);
+            const int nx = cur ^ 1;
+            if (keep) {
+              s_px[w][nx][pos] = ax;
+              s_py[w][nx][pos] = ay;
+              s_lab[w][nx][pos] = la;
+              ++pos;
+            }
+            if (cross) {
+              const double t = fa / (fa - fb);
+              s_px[w][nx][pos] = ax + t * (bx - ax);
+              s_py[w][nx][pos] = ay + t * (by - ay);
+              s_lab[w][nx][pos] = keep ? ej : la;
+            }
+            cur = nx;
+            nv = nn;
+            fence();
+            m &= ~((2ull << f) - 1);
+            if (m) m = __ballot(((m >> lane) & 1) && cuts());
+          }
+        }
+        fence();  // s_pre and s_st are written again
+      }
+    }
+    if (over) break;  // z = -1: more vertices than the polygon holds
     // the searched block's margin around r_i (unbounded where it reaches the grid's edge)
     const double inf = 1e300;
     const double ml = x0 == 0 ? inf : xi - (-kGridL + x0 * g.c);
@@ -442,10 +477,9 @@ __global__ __launch_bounds__(64) void k_voronoi(const double* __restrict__ x,
     const double mb = y0 == 0 ? inf : yi - (-kGridL + y0 * g.c);
     const double mt = y1 == g.G - 1 ? inf : (-kGridL + (y1 + 1) * g.c) - yi;
     const double D = fmin(fmin(ml, mr), fmin(mb, mt));
-    bool box = false;
-    for (int q = 0; q < nv; ++q) box |= lab[cur][q] < 0;
+    const bool box = __ballot(lane < nv && s_lab[w][cur][min(lane, kVorMaxV - 1)] < 0) != 0;
     const bool full = x0 == 0 && y0 == 0 && x1 == g.G - 1 && y1 == g.G - 1;
-    if (full || poly_reach(xi, yi, px[cur], py[cur], nv, Rb) <= D) {
+    if (full || reach() <= D) {
       if (!box) {
         z = 0;
         break;
@@ -460,23 +494,28 @@ __global__ __launch_bounds__(64) void k_voronoi(const double* __restrict__ x,
   }
   double sre = 0.0, sim = 0.0;
   if (z == 0) {
-    for (int q = 0; q < nv; ++q) {
-      const int j = lab[cur][q];
-      if (j < 0) continue;
-      ++z;
-      const double dx = x[j] - xi, dy = y[j] - yi;
-      const double r = sqrt(dx * dx + dy * dy);
-      const double ur = dx / r, ui = dy / r;
-      const double u2r = ur * ur - ui * ui, u2i = 2.0 * ur * ui;
-      const double u4r = u2r * u2r - u2i * u2i, u4i = 2.0 * u2r * u2i;
-      sre += u4r * u2r - u4i * u2i;
-      sim += u4r * u2i + u4i * u2r;
+    const int j = lane < nv ? s_lab[w][cur][lane] : -1;
+    z = __popcll(__ballot(j >= 0));
+    if (psi) {
+      if (j >= 0) {
+        const double dx = x[j] - xi, dy = y[j] - yi;
+        const double r = sqrt(dx * dx + dy * dy);
+        const double ur = dx / r, ui = dy / r;
+        const double u2r = ur * ur - ui * ui, u2i = 2.0 * ur * ui;
+        const double u4r = u2r * u2r - u2i * u2i, u4i = 2.0 * u2r * u2i;
+        sre = u4r * u2r - u4i * u2i;
+        sim = u4r * u2i + u4i * u2r;
+      }
+      sre = wave_sum(sre);
+      sim = wave_sum(sim);
     }
   }
-  zout[i] = z;
-  if (psi) {
-    psi[2 * (size_t)i] = z > 0 ? sre / z : 0.0;
-    psi[2 * (size_t)i + 1] = z > 0 ? sim / z : 0.0;
+  if (lane == 0) {
+    zout[i] = z;
+    if (psi) {
+      psi[2 * (size_t)i] = z > 0 ? sre / z : 0.0;
+      psi[2 * (size_t)i + 1] = z > 0 ? sim / z : 0.0;
+    }
   }
 }
 
@@ -671,8 +710,8 @@ int voronoi_coordination(const double* x, const double* y, int64_t n, int32_t* z
   hipLaunchKernelGGL(k_cell_fill, dim3((nn + 255) / 256), dim3(256), 0, st, nn, cell, start,
                      cursor, slot);
   hipLaunchKernelGGL(k_cell_sort, dim3((cells + 255) / 256), dim3(256), 0, st, cells, start, slot);
-  hipLaunchKernelGGL(k_voronoi, dim3((nn + 63) / 64), dim3(64), 0, st, x, y, nn, g, start, slot,
-                     hullf, Rb, z, psi6);
+  hipLaunchKernelGGL(k_voronoi, dim3((nn + kVorW - 1) / kVorW), dim3(64 * kVorW), 0, st, x, y, nn,
+                     g, start, slot, hullf, Rb, z, psi6);
   return hip_status(hipGetLastError());
 }
 
