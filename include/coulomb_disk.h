@@ -283,7 +283,7 @@ int relax_subdomains(const double* x, const double* y, int64_t n, int32_t n_patc
 /* Schedule tuning of relax_subdomains (not an operation of the paper; a
  * performance setting).  Relaxes the given batch once with each candidate
  * schedule -- the running-block count below which the model evaluation
- * spreads a 64-active block over 16 waves instead of 8 (0, 256, 512, 1024,
+ * spreads a tile of actives over 16 waves instead of 8 (0, 64, 128, 512,
  * always), lock-step rounds per HIP graph replay (4, 8, 16, 32), and, for a
  * call that leaves polish at CD_POLISH_DEFAULT, the path's other polish
  * (Newton on CD_MIXED, L-BFGS on CD_FP64) -- outputs discarded, timed on the

@@ -924,101 +924,155 @@ __global__ __launch_bounds__(64 * kESW) void k_exact_sum(RelaxDev R) {
 //   E_i = 1/2 sum_A 1/r + sum_halo 1/r + f.d + 1/2 d.H d,  d = z_i - zr_i
 // Per patch either FP32 pairs (coordinates relative to the patch centre,
 // partials of at most 64 terms folded into FP64) or FP64 pairs.
-// SELF: the j range holds the actives, and every lane's own index lies in
-// [diag, diag + 64) (its 64-active block); only the 64-term chunks that meet
-// that range test j against the lane's index, the others need no test.
-template <bool SELF, bool WK>
-__device__ __forceinline__ void pairs32(const float* __restrict__ xs, const float* __restrict__ ys,
-                                        int b0, int b1, int self, int diag, float xf, float yf,
-                                        double& G0, double& G1, double& E, double* K, double w) {
-  for (int c0 = b0; c0 < b1; c0 += 64) {
-    const int c1 = min(b1, c0 + 64);
-    float g0 = 0.f, g1 = 0.f, e = 0.f, k0 = 0.f, k1 = 0.f, k2 = 0.f;
-    auto chunk = [&](auto self_tag) {
-      constexpr bool S = decltype(self_tag)::value;
-#pragma unroll 8
-      for (int b = c0; b < c1; ++b) {
-        const float dx = xf - xs[b], dy = yf - ys[b];
-        const float r2 = __builtin_fmaf(dx, dx, dy * dy);
-        float inv = __builtin_amdgcn_rsqf(r2);
-        if (S) inv = (b == self) ? 0.f : inv;
-        const float i3 = inv * inv * inv;
-        e += inv;
-        g0 = __builtin_fmaf(-dx, i3, g0);
-        g1 = __builtin_fmaf(-dy, i3, g1);
-        if (WK) {
-          const float t3 = 3.0f * i3 * inv * inv;
-          k0 += __builtin_fmaf(t3 * dx, dx, -i3);
-          k1 += t3 * dx * dy;
-          k2 += __builtin_fmaf(t3 * dy, dy, -i3);
-        }
-      }
-    };
-    if (SELF && c0 < diag + 64 && c1 > diag)
-      chunk(std::true_type{});
-    else
-      chunk(std::false_type{});
-    G0 += g0;
-    G1 += g1;
-    E += w * (double)e;
-    K[0] += k0;
-    K[1] += k1;
-    K[2] += k2;
-  }
-}
-
-template <bool SELF, bool WK>
-__device__ __forceinline__ void pairs64(const double* __restrict__ xs,
-                                        const double* __restrict__ ys, int b0, int b1, int self,
-                                        int diag, double xi, double yi, double& G0, double& G1,
-                                        double& E, double& Ec, double* K, double w) {
-  for (int c0 = b0; c0 < b1; c0 += 64) {
-    const int c1 = min(b1, c0 + 64);
-    double e = 0.0;
-    auto chunk = [&](auto self_tag) {
-      constexpr bool S = decltype(self_tag)::value;
-#pragma unroll 4
-      for (int b = c0; b < c1; ++b) {
-        const double dx = xi - xs[b], dy = yi - ys[b];
-        const double r2 = __builtin_fma(dx, dx, dy * dy);
-        double inv = rsqrt64(r2);
-        if (S) inv = (b == self) ? 0.0 : inv;
-        const double i3 = inv * inv * inv;
-        e += inv;
-        G0 = __builtin_fma(-dx, i3, G0);
-        G1 = __builtin_fma(-dy, i3, G1);
-        if (WK) {
-          const double t3 = 3.0 * i3 * inv * inv;
-          K[0] += __builtin_fma(t3 * dx, dx, -i3);
-          K[1] += t3 * dx * dy;
-          K[2] += __builtin_fma(t3 * dy, dy, -i3);
-        }
-      }
-    };
-    if (SELF && c0 < diag + 64 && c1 > diag)
-      chunk(std::true_type{});
-    else
-      chunk(std::false_type{});
-    const double v = w * e;
-    const double tt = E + v;
-    Ec += fabs(E) >= fabs(v) ? (E - tt) + v : (v - tt) + E;
-    E = tt;
-  }
-}
-
-// One workgroup per 64-active block; its MW waves split the patch's j list
-// (actives, then halo) into ranges cut at multiples of 16 (at multiples of
-// 64 the last waves of a workgroup often had little or nothing to do while
-// the others set its time) and the partial sums are combined in LDS in wave
-// order, so a large patch spreads over MW times more waves.  MW = kMW, or kMWWide when few blocks belong to
-// patches still running (the chip would otherwise sit mostly idle).
+//
+// A workgroup takes kTI actives (a tile); its MW waves split the patch's j
+// list (actives, then halo) into ranges cut at multiples of 16, and the
+// kPhases lanes of a wave that share an active take every kPhases-th j of the
+// range.  The j go through the wave's own part of LDS, 64 at a time, the next
+// 64 loaded while these are used.  Sums are combined in a fixed order: the
+// waves, then the lanes of an active.
+// Why tiles this small: the work per workgroup is the patch's actives and
+// halo, 200 to 3000 of them, and the time is that of the fullest CU.  With 64
+// actives a workgroup (j through the scalar cache) 32 patches of 200 to 2000
+// actives gave each CU two or three workgroups: 53 us a call with all of them
+// running (45 with 16 waves a workgroup and fewer running); now 40, with tiles
+// of 32 42, of 8 46, with 4 waves 42.  The FP64 pairs' issue alone takes 32.
+// 16 waves pay below about 128 blocks running (23 us); from 128 to 512 they
+// were slower (39 against 33).
+constexpr int kTI = 16;
+constexpr int kPhases = 64 / kTI;
+constexpr int kTiles = 64 / kTI;  // per entry of the block table
 constexpr int kMW = 8;
-constexpr int kMWWide = 16;
+constexpr int kMWWide = 16;  // when few blocks belong to patches still running
+
+// LDS written by some lanes of a wave and read by others of it: the LDS pipe
+// keeps a wave's order, this keeps the compiler's.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Runs over the j of [b0, b1) in chunks of 64 staged in LDS: load(j) gives the value of one j, chunk(steps, c0, test)
+// takes steps j per phase of the chunk from c0 on, `test` where a j may be
+// past the end or the lane's own index (tile: the tile's first index, or far
+// below any).
+template <class V, class LoadFn, class ChunkFn>
+__device__ __forceinline__ void staged(V* buf, int b0, int b1, int tile, LoadFn load,
+                                       ChunkFn chunk) {
+  const int lane = threadIdx.x & 63;
+  if (b0 >= b1) return;
+  V next = load(min(b0 + lane, b1 - 1));
+  for (int c0 = b0; c0 < b1; c0 += 64) {
+    const int c1 = min(b1, c0 + 64);
+    wave_lds_order();
+    buf[lane] = next;
+    wave_lds_order();
+    if (c1 < b1) next = load(min(c1 + lane, b1 - 1));
+    if (c1 - c0 == 64 && !(c0 < tile + kTI && c1 > tile))
+      chunk(kTI, c0, c1, std::false_type{});
+    else
+      chunk((c1 - c0 + kPhases - 1) / kPhases, c0, c1, std::true_type{});
+  }
+}
+
+template <bool WK>
+__device__ __forceinline__ void pairs32(float2* buf, const float* __restrict__ xs,
+                                        const float* __restrict__ ys, int b0, int b1, int self,
+                                        int tile, float xf, float yf, double& G0, double& G1,
+                                        double& E, double* K, double w) {
+  const int ph = (threadIdx.x & 63) / kTI;
+  staged(
+      buf, b0, b1, tile, [&](int j) { return make_float2(xs[j], ys[j]); },
+      [&](int steps, int c0, int c1, auto test) {
+        constexpr bool T = decltype(test)::value;
+        float g0 = 0.f, g1 = 0.f, e = 0.f, k0 = 0.f, k1 = 0.f, k2 = 0.f;
+#pragma unroll 4
+        for (int k = 0; k < steps; ++k) {
+          const int b = k * kPhases + ph;
+          const float2 q = buf[b];
+          const float dx = xf - q.x, dy = yf - q.y;
+          const float r2 = __builtin_fmaf(dx, dx, dy * dy);
+          float inv = __builtin_amdgcn_rsqf(r2);
+          if (T) inv = (c0 + b >= c1 || c0 + b == self) ? 0.f : inv;
+          const float i3 = inv * inv * inv;
+          e += inv;
+          g0 = __builtin_fmaf(-dx, i3, g0);
+          g1 = __builtin_fmaf(-dy, i3, g1);
+          if (WK) {
+            const float t3 = 3.0f * i3 * inv * inv;
+            k0 += __builtin_fmaf(t3 * dx, dx, -i3);
+            k1 += t3 * dx * dy;
+            k2 += __builtin_fmaf(t3 * dy, dy, -i3);
+          }
+        }
+        G0 += g0;
+        G1 += g1;
+        E += w * (double)e;
+        K[0] += k0;
+        K[1] += k1;
+        K[2] += k2;
+      });
+}
+
+template <bool WK>
+__device__ __forceinline__ void pairs64(double2* buf, const double* __restrict__ xs,
+                                        const double* __restrict__ ys, int b0, int b1, int self,
+                                        int tile, double xi, double yi, double& G0, double& G1,
+                                        double& E, double& Ec, double* K, double w) {
+  const int ph = (threadIdx.x & 63) / kTI;
+  staged(
+      buf, b0, b1, tile, [&](int j) { return make_double2(xs[j], ys[j]); },
+      [&](int steps, int c0, int c1, auto test) {
+        constexpr bool T = decltype(test)::value;
+        double e = 0.0;
+#pragma unroll 4
+        for (int k = 0; k < steps; ++k) {
+          const int b = k * kPhases + ph;
+          const double2 q = buf[b];
+          const double dx = xi - q.x, dy = yi - q.y;
+          const double r2 = __builtin_fma(dx, dx, dy * dy);
+          double inv = rsqrt64(r2);
+          if (T) inv = (c0 + b >= c1 || c0 + b == self) ? 0.0 : inv;
+          const double i3 = inv * inv * inv;
+          e += inv;
+          G0 = __builtin_fma(-dx, i3, G0);
+          G1 = __builtin_fma(-dy, i3, G1);
+          if (WK) {
+            const double t3 = 3.0 * i3 * inv * inv;
+            K[0] += __builtin_fma(t3 * dx, dx, -i3);
+            K[1] += t3 * dx * dy;
+            K[2] += __builtin_fma(t3 * dy, dy, -i3);
+          }
+        }
+        const double v = w * e;
+        const double tt = E + v;
+        Ec += fabs(E) >= fabs(v) ? (E - tt) + v : (v - tt) + E;
+        E = tt;
+      });
+}
+
+// The sum over the kPhases lanes of an active, in every one of them.
+__device__ __forceinline__ double phase_sum(double v) {
+#pragma unroll
+  for (int o = kTI; o < 64; o *= 2) v += __shfl_xor(v, o);
+  return v;
+}
+__device__ __forceinline__ double phase_sum(double v, double& err) {  // and its rounding errors
+#pragma unroll
+  for (int o = kTI; o < 64; o *= 2) {
+    const double u = __shfl_xor(v, o), s = v + u;
+    err += fabs(v) >= fabs(u) ? (v - s) + u : (u - s) + v;
+    v = s;
+  }
+  return v;
+}
 
 template <bool WK, int MW>
 __global__ __launch_bounds__(64 * MW) void k_model(RelaxDev R) {
-  __shared__ double part[MW][7][64];  // G0 G1 E Ec K0 K1 K2 per wave and lane
-  const int wb = blockIdx.x;
+  // the waves' staged j, then their sums G0 G1 E Ec K0 K1 K2 by lane
+  __shared__ double2 buf[MW][64];
+  __shared__ double part[MW - 1][7][64];
+  const int wb = blockIdx.x / kTiles;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (wb >= R.nblk) return;
@@ -1032,48 +1086,63 @@ __global__ __launch_bounds__(64 * MW) void k_model(RelaxDev R) {
     return;
   const bool use32 = st.use32;
   const int a0 = R.ptr[p], a1 = R.ptr[p + 1];
+  const int tile = bk.y + (blockIdx.x % kTiles) * kTI;
+  if (tile >= a1) return;
   const int h0 = R.hptr[p], h1 = R.hptr[p + 1];
   const int na = a1 - a0, nj = na + (h1 - h0);
   const int per = ((nj + MW - 1) / MW + 15) & ~15;
   const int j0 = min(nj, w * per), j1 = min(nj, j0 + per);
-  const int a = bk.y + lane;
-  const bool ok = a < a1;
-  const int ac = ok ? a : a1 - 1;
+  const int a = tile + lane % kTI;
+  const int ac = a < a1 ? a : a1 - 1;
   const double xi = R.tx[ac], yi = R.ty[ac];
   double G0 = 0.0, G1 = 0.0, E = 0.0, Ec = 0.0, K[3] = {0.0, 0.0, 0.0};
+  const int none = -(1 << 30);
+  const int s1 = min(j1, na), u0 = max(j0, na) - na, u1 = max(j1, na) - na;
   if (use32) {
+    float2* const b32 = reinterpret_cast<float2*>(buf[w]);
     const float xf = R.a32x[ac], yf = R.a32y[ac];
-    pairs32<true, WK>(R.a32x, R.a32y, a0 + j0, a0 + min(j1, na), ac, bk.y, xf, yf, G0, G1, E, K,
-                      0.5);
-    pairs32<false, WK>(R.h32x, R.h32y, h0 + max(j0, na) - na, h0 + max(j1, na) - na, -1, 0, xf,
-                       yf, G0, G1, E, K, 1.0);
+    pairs32<WK>(b32, R.a32x, R.a32y, a0 + j0, a0 + s1, ac, tile, xf, yf, G0, G1, E, K, 0.5);
+    pairs32<WK>(b32, R.h32x, R.h32y, h0 + u0, h0 + u1, none, none, xf, yf, G0, G1, E, K, 1.0);
   } else {
-    pairs64<true, WK>(R.tx, R.ty, a0 + j0, a0 + min(j1, na), ac, bk.y, xi, yi, G0, G1, E, Ec, K,
-                      0.5);
-    pairs64<false, WK>(R.h64x, R.h64y, h0 + max(j0, na) - na, h0 + max(j1, na) - na, -1, 0, xi,
-                       yi, G0, G1, E, Ec, K, 1.0);
+    pairs64<WK>(buf[w], R.tx, R.ty, a0 + j0, a0 + s1, ac, tile, xi, yi, G0, G1, E, Ec, K, 0.5);
+    pairs64<WK>(buf[w], R.h64x, R.h64y, h0 + u0, h0 + u1, none, none, xi, yi, G0, G1, E, Ec, K,
+                1.0);
   }
-  part[w][0][lane] = G0;
-  part[w][1][lane] = G1;
-  part[w][2][lane] = E;
-  part[w][3][lane] = Ec;
-  part[w][4][lane] = K[0];
-  part[w][5][lane] = K[1];
-  part[w][6][lane] = K[2];
+  if (w > 0) {
+    double(*const o)[64] = part[w - 1];
+    o[0][lane] = G0;
+    o[1][lane] = G1;
+    o[2][lane] = E;
+    o[3][lane] = Ec;
+    if (WK) {
+      o[4][lane] = K[0];
+      o[5][lane] = K[1];
+      o[6][lane] = K[2];
+    }
+  }
   __syncthreads();
-  if (w != 0 || !ok) return;
-  G0 = G1 = E = Ec = 0.0;
-  K[0] = K[1] = K[2] = 0.0;
-  for (int q = 0; q < MW; ++q) {
+  if (w != 0) return;
+  for (int q = 0; q < MW - 1; ++q) {
     G0 += part[q][0][lane];
     G1 += part[q][1][lane];
     const double v = part[q][2][lane], tt = E + v;  // Neumaier across the waves' sums
     Ec += (fabs(E) >= fabs(v) ? (E - tt) + v : (v - tt) + E) + part[q][3][lane];
     E = tt;
-    K[0] += part[q][4][lane];
-    K[1] += part[q][5][lane];
-    K[2] += part[q][6][lane];
+    if (WK) {
+      K[0] += part[q][4][lane];
+      K[1] += part[q][5][lane];
+      K[2] += part[q][6][lane];
+    }
   }
+  G0 = phase_sum(G0);
+  G1 = phase_sum(G1);
+  Ec = phase_sum(Ec);
+  E = phase_sum(E, Ec);
+  if (WK) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) K[c] = phase_sum(K[c]);
+  }
+  if (lane >= kTI || a >= a1) return;
   E += Ec;
   const double ddx = xi - R.zrx[a], ddy = yi - R.zry[a];
   const double hx = R.fhxx[a] * ddx + R.fhxy[a] * ddy, hy = R.fhxy[a] * ddx + R.fhyy[a] * ddy;
@@ -1125,61 +1194,66 @@ __global__ void k_model_prep(RelaxDev R, int halo_too) {
 // quadratic carries the exact Hessian).  A held charge's coordinate is its
 // angle, with tangent t = (-y, x): its component is t . (H w)_i - (g_i . z_i)
 // d_i (the circle's curvature), a free charge's (H w)_i.  FP64 pairs.
-// Workgroup layout as k_model: MW waves split the patch's actives into
-// ranges cut at multiples of 16; their sums are combined in wave order.
+// Workgroup layout as k_model.  In an FP64 batch of 24 patches of 100 to 520
+// actives 7.1 us a call, 13.2 with 64 actives a workgroup, which left half of
+// the CUs without one.
 template <int MW>
 __global__ __launch_bounds__(64 * MW) void k_cg_hvp(RelaxDev R) {
-  __shared__ double part[MW][2][64];
-  const int wb = blockIdx.x;
+  struct alignas(32) ZW {
+    double x, y, wx, wy;
+  };
+  __shared__ ZW buf[MW][64];
+  __shared__ double part[MW - 1][2][64];
+  const int wb = blockIdx.x / kTiles;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
+  const int lane = threadIdx.x & 63, ph = lane / kTI;
   if (wb >= R.nblk) return;
   const int2 bk = R.blk[wb];
   const int p = bk.x;
   const PState& st = R.st[p];
   if (st.status != kRunning || st.phase != kPhaseCG) return;  // uniform in the workgroup
   const int a0 = R.ptr[p], a1 = R.ptr[p + 1];
+  const int tile = bk.y + (blockIdx.x % kTiles) * kTI;
+  if (tile >= a1) return;
   const int na = a1 - a0;
   const int per = ((na + MW - 1) / MW + 15) & ~15;
   const int j0 = min(na, w * per), j1 = min(na, j0 + per);
-  const int a = bk.y + lane;
-  const bool ok = a < a1;
-  const int ac = ok ? a : a1 - 1;
+  const int a = tile + lane % kTI;
+  const int ac = a < a1 ? a : a1 - 1;
   const double xi = R.zx[ac], yi = R.zy[ac];
   double Q0 = 0.0, Q1 = 0.0;
-  // in 64-term chunks: only the chunk that meets the block's own actives
-  // [bk.y, bk.y + 64) tests j against the lane's index
-  for (int c0 = a0 + j0; c0 < a0 + j1; c0 += 64) {
-    const int c1 = min(a0 + j1, c0 + 64);
-    auto chunk = [&](auto self_tag) {
-      constexpr bool S = decltype(self_tag)::value;
+  staged(
+      buf[w], a0 + j0, a0 + j1, tile,
+      [&](int j) { return ZW{R.zx[j], R.zy[j], R.cwx[j], R.cwy[j]}; },
+      [&](int steps, int c0, int c1, auto test) {
+        constexpr bool T = decltype(test)::value;
 #pragma unroll 4
-      for (int b = c0; b < c1; ++b) {
-        const double dx = xi - R.zx[b], dy = yi - R.zy[b];
-        const double wx = R.cwx[b], wy = R.cwy[b];
-        const double r2 = __builtin_fma(dx, dx, dy * dy);
-        double inv = rsqrt64(r2);
-        if (S) inv = (b == ac) ? 0.0 : inv;
-        const double i3 = inv * inv * inv;
-        const double sc = 3.0 * i3 * inv * inv * __builtin_fma(dx, wx, dy * wy);
-        Q0 += __builtin_fma(dx, sc, -wx * i3);
-        Q1 += __builtin_fma(dy, sc, -wy * i3);
-      }
-    };
-    if (c0 < bk.y + 64 && c1 > bk.y)
-      chunk(std::true_type{});
-    else
-      chunk(std::false_type{});
+        for (int k = 0; k < steps; ++k) {
+          const int b = k * kPhases + ph;
+          const ZW q = buf[w][b];
+          const double dx = xi - q.x, dy = yi - q.y;
+          const double r2 = __builtin_fma(dx, dx, dy * dy);
+          double inv = rsqrt64(r2);
+          if (T) inv = (c0 + b >= c1 || c0 + b == ac) ? 0.0 : inv;
+          const double i3 = inv * inv * inv;
+          const double sc = 3.0 * i3 * inv * inv * __builtin_fma(dx, q.wx, dy * q.wy);
+          Q0 += __builtin_fma(dx, sc, -q.wx * i3);
+          Q1 += __builtin_fma(dy, sc, -q.wy * i3);
+        }
+      });
+  if (w > 0) {
+    part[w - 1][0][lane] = Q0;
+    part[w - 1][1][lane] = Q1;
   }
-  part[w][0][lane] = Q0;
-  part[w][1][lane] = Q1;
   __syncthreads();
-  if (w != 0 || !ok) return;
-  Q0 = Q1 = 0.0;
-  for (int q = 0; q < MW; ++q) {
+  if (w != 0) return;
+  for (int q = 0; q < MW - 1; ++q) {
     Q0 += part[q][0][lane];
     Q1 += part[q][1][lane];
   }
+  Q0 = phase_sum(Q0);
+  Q1 = phase_sum(Q1);
+  if (lane >= kTI || a >= a1) return;
   const double wx = R.cwx[a], wy = R.cwy[a];
   const double hx = R.kxx[a] * wx + R.kxy[a] * wy - Q0;
   const double hy = R.kxy[a] * wx + R.kyy[a] * wy - Q1;
@@ -2317,9 +2391,9 @@ struct RPlan {
   // schedule (relax_autotune chooses among these): lock-step rounds per graph
   // replay (the running count is read back between replays), and the
   // running-block count below which the model evaluation takes 16 waves per
-  // block instead of 8
+  // tile instead of 8
   int graph_rounds = 8;
-  int64_t wide_blocks = 512;
+  int64_t wide_blocks = 128;
   bool use_graphs = true;  // rounds replayed from HIP graphs (else launched one by one)
   int regj = kRegJ;        // actives per thread in registers in the update (kRegJ or kRegJWide)
   size_t total;
@@ -2489,9 +2563,9 @@ struct RelaxSched {
   int polish;
 };
 constexpr int kOtherPolish = 1;
-constexpr RelaxSched kRelaxScheds[] = {{512, 8, -1},  {0, 8, -1},         {1 << 30, 8, -1},
-                                       {256, 8, -1},  {1024, 8, -1},      {512, 4, -1},
-                                       {512, 16, -1}, {512, 32, -1},      {512, 8, kOtherPolish}};
+constexpr RelaxSched kRelaxScheds[] = {{128, 8, -1},  {0, 8, -1},         {1 << 30, 8, -1},
+                                       {64, 8, -1},   {512, 8, -1},       {128, 4, -1},
+                                       {128, 16, -1}, {128, 32, -1},      {128, 8, kOtherPolish}};
 constexpr int kNumRelaxScheds = sizeof(kRelaxScheds) / sizeof(kRelaxScheds[0]);
 static_assert(kNumRelaxScheds == CD_RELAX_SCHEDULES, "the header states the candidate count");
 using RelaxKey = std::tuple<int, int, int, int64_t, int>;  // device, precision, coords, n, log2 total
@@ -2585,9 +2659,9 @@ template <class EvalFn>
 static void launch_round(RPlan& R, hipStream_t s, bool hist32, int shape, EvalFn& eval) {
   if (R.D.polish) {  // CG iterations of patches in a Newton step, then the trial evaluations
     if (shape)
-      hipLaunchKernelGGL((k_cg_hvp<kMWWide>), dim3(R.D.nblk), dim3(64 * kMWWide), 0, s, R.D);
+      hipLaunchKernelGGL((k_cg_hvp<kMWWide>), dim3(R.D.nblk * kTiles), dim3(64 * kMWWide), 0, s, R.D);
     else
-      hipLaunchKernelGGL((k_cg_hvp<kMW>), dim3(R.D.nblk), dim3(64 * kMW), 0, s, R.D);
+      hipLaunchKernelGGL((k_cg_hvp<kMW>), dim3(R.D.nblk * kTiles), dim3(64 * kMW), 0, s, R.D);
   }
   eval(s, shape);
   // the (t, u) variant only when the call asked for it: the (x, y) kernel
@@ -2802,8 +2876,14 @@ int relax_subdomains(const double* x, const double* y, int64_t n, int32_t n_patc
   std::vector<int2> blk;
   blk.reserve(R.nblk);
   int max_na = 0;
-  for (int p = 0; p < n_patches; ++p) {
-    max_na = std::max(max_na, patch_ptr[p + 1] - patch_ptr[p]);
+  // the largest patches' blocks first: theirs take longest
+  std::vector<int> by_size(n_patches);
+  for (int p = 0; p < n_patches; ++p) by_size[p] = p;
+  auto size_of = [&](int p) { return patch_ptr[p + 1] - patch_ptr[p]; };
+  std::stable_sort(by_size.begin(), by_size.end(),
+                   [&](int p, int q) { return size_of(p) > size_of(q); });
+  for (int p : by_size) {
+    max_na = std::max(max_na, size_of(p));
     for (int a = patch_ptr[p]; a < patch_ptr[p + 1]; a += 64) blk.push_back(make_int2(p, a));
   }
   D.nblk = (int)blk.size();
@@ -2894,7 +2974,7 @@ int relax_subdomains(const double* x, const double* y, int64_t n, int32_t n_patc
     bool rebuild = false;
     RelaxDev Df = D;
     Df.eval_all = 1;
-    // 16-wave model blocks when the running patches hold fewer than
+    // 16-wave model tiles when the running patches hold fewer than
     // wide_blocks blocks (estimated from the running count)
     auto wide_shape = [&]() {
       return (int)((int64_t)R.running * D.nblk < R.wide_blocks * n_patches);
@@ -2907,13 +2987,13 @@ int relax_subdomains(const double* x, const double* y, int64_t n, int32_t n_patc
       // the Hessian blocks (preconditioner) are evaluated at the expansion
       // point only and kept for the rest of the round
       if (all && wide)
-        hipLaunchKernelGGL((k_model<true, kMWWide>), dim3(D.nblk), dim3(64 * kMWWide), 0, s, E);
+        hipLaunchKernelGGL((k_model<true, kMWWide>), dim3(D.nblk * kTiles), dim3(64 * kMWWide), 0, s, E);
       else if (all)
-        hipLaunchKernelGGL((k_model<true, kMW>), dim3(D.nblk), dim3(64 * kMW), 0, s, E);
+        hipLaunchKernelGGL((k_model<true, kMW>), dim3(D.nblk * kTiles), dim3(64 * kMW), 0, s, E);
       else if (wide)
-        hipLaunchKernelGGL((k_model<false, kMWWide>), dim3(D.nblk), dim3(64 * kMWWide), 0, s, E);
+        hipLaunchKernelGGL((k_model<false, kMWWide>), dim3(D.nblk * kTiles), dim3(64 * kMWWide), 0, s, E);
       else
-        hipLaunchKernelGGL((k_model<false, kMW>), dim3(D.nblk), dim3(64 * kMW), 0, s, E);
+        hipLaunchKernelGGL((k_model<false, kMW>), dim3(D.nblk * kTiles), dim3(64 * kMW), 0, s, E);
     };
     auto model = [&](int all) { model_on(all, st, wide_shape()); };
     // rounds: expand the far field exactly at z (one O(n_act N) FP64 pass);
