@@ -1727,6 +1727,17 @@ __device__ __forceinline__ void cg_iteration(RelaxDev& R, PState& s, int p, WgRe
   }
 }
 
+// A CG iteration by itself, for the CG products of a round that no evaluation
+// follows.
+__global__ __launch_bounds__(kUpd) void k_cg_update(RelaxDev R) {
+  WG_RED_LDS(red);
+  const int p = blockIdx.x;
+  PState s = R.st[p];
+  if (s.status != kRunning || s.phase != kPhaseCG) return;
+  cg_iteration(R, s, p, red);
+  if (threadIdx.x == 0) R.st[p] = s;
+}
+
 // One active's part of a stored secant pair, side by side: one load.
 template <class HT>
 struct alignas(4 * sizeof(HT)) Hist {
@@ -2655,13 +2666,26 @@ static void launch_update(RPlan& R, hipStream_t s, bool hist32) {
     hipLaunchKernelGGL((k_update<double, false, RJ>), dim3(R.P), dim3(kUpd), 0, s, R.D);
 }
 
+// CG iterations per round.  A Newton step takes tens of them for each
+// evaluation, and an evaluation launched in a round without a trial costs its
+// launches all the same (exact pass and sum, 27 us in a batch of 24 patches,
+// against 18 for a CG iteration).  A patch's own sequence of steps does not
+// depend on it.  That batch takes 11.8 ms with one, 10.4 with two, 10.0 with
+// three, 9.8 with four, 10.0 with eight; a batch of four small patches, where
+// each empty launch and graph node shows, 4.6, 4.9, 5.2, 5.8, 7.5.
+constexpr int kCgPerRound = 3;
+
 template <class EvalFn>
 static void launch_round(RPlan& R, hipStream_t s, bool hist32, int shape, EvalFn& eval) {
   if (R.D.polish) {  // CG iterations of patches in a Newton step, then the trial evaluations
-    if (shape)
-      hipLaunchKernelGGL((k_cg_hvp<kMWWide>), dim3(R.D.nblk * kTiles), dim3(64 * kMWWide), 0, s, R.D);
-    else
-      hipLaunchKernelGGL((k_cg_hvp<kMW>), dim3(R.D.nblk * kTiles), dim3(64 * kMW), 0, s, R.D);
+    for (int k = 1; k <= kCgPerRound; ++k) {
+      if (shape)
+        hipLaunchKernelGGL((k_cg_hvp<kMWWide>), dim3(R.D.nblk * kTiles), dim3(64 * kMWWide), 0, s,
+                           R.D);
+      else
+        hipLaunchKernelGGL((k_cg_hvp<kMW>), dim3(R.D.nblk * kTiles), dim3(64 * kMW), 0, s, R.D);
+      if (k < kCgPerRound) hipLaunchKernelGGL(k_cg_update, dim3(R.P), dim3(kUpd), 0, s, R.D);
+    }
   }
   eval(s, shape);
   // the (t, u) variant only when the call asked for it: the (x, y) kernel
