@@ -928,8 +928,8 @@ __global__ __launch_bounds__(64 * kESW) void k_exact_sum(RelaxDev R) {
 // A workgroup takes kTI actives (a tile); its MW waves split the patch's j
 // list (actives, then halo) into ranges cut at multiples of 16, and the
 // kPhases lanes of a wave that share an active take every kPhases-th j of the
-// range.  The j go through the wave's own part of LDS, 64 at a time, the next
-// 64 loaded while these are used.  Sums are combined in a fixed order: the
+// range.  The j go through the wave's own part of LDS, kStage at a time, the
+// next loaded while these are used.  Sums are combined in a fixed order: the
 // waves, then the lanes of an active.
 // Why tiles this small: the work per workgroup is the patch's actives and
 // halo, 200 to 3000 of them, and the time is that of the fullest CU.  With 64
@@ -952,26 +952,49 @@ __device__ __forceinline__ void wave_lds_order() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// Runs over the j of [b0, b1) in chunks of 64 staged in LDS: load(j) gives the value of one j, chunk(steps, c0, test)
-// takes steps j per phase of the chunk from c0 on, `test` where a j may be
-// past the end or the lane's own index (tile: the tile's first index, or far
-// below any).
+// Runs over the j of [b0, b1) in chunks of kStage staged in LDS: load(j) gives
+// the value of one j, `pad` one whose terms vanish, and chunk(steps) brackets
+// steps(k0, k1, test): the steps k0 ... k1 - 1 of the chunk, each one j per
+// phase.  Where the range holds the tile's own actives [tile, tile + kTI) (or
+// tile far below any index), their steps test j against the lane's; ranges and
+// tiles start at multiples of 16 j of the list, so they are whole steps of one
+// chunk.  kStage: two j a lane; 60 iterations of 256 patches of 200 to 5000
+// actives take 240 ms with it, 241 with 64, 246 with 256 (fewer waves a CU).
+constexpr int kStage = 128;
+static_assert(16 % kTI == 0, "a tile's own actives lie in one range and chunk");
+
 template <class V, class LoadFn, class ChunkFn>
-__device__ __forceinline__ void staged(V* buf, int b0, int b1, int tile, LoadFn load,
+__device__ __forceinline__ void staged(V* buf, int b0, int b1, int tile, V pad, LoadFn load,
                                        ChunkFn chunk) {
   const int lane = threadIdx.x & 63;
   if (b0 >= b1) return;
-  V next = load(min(b0 + lane, b1 - 1));
-  for (int c0 = b0; c0 < b1; c0 += 64) {
-    const int c1 = min(b1, c0 + 64);
+  V next[kStage / 64];
+  auto fetch = [&](int c0) {
+#pragma unroll
+    for (int q = 0; q < kStage / 64; ++q) {
+      const int j = c0 + 64 * q + lane;
+      next[q] = load(min(j, b1 - 1));
+      if (j >= b1) next[q] = pad;
+    }
+  };
+  fetch(b0);
+  for (int c0 = b0; c0 < b1; c0 += kStage) {
     wave_lds_order();
-    buf[lane] = next;
+#pragma unroll
+    for (int q = 0; q < kStage / 64; ++q) buf[64 * q + lane] = next[q];
     wave_lds_order();
-    if (c1 < b1) next = load(min(c1 + lane, b1 - 1));
-    if (c1 - c0 == 64 && !(c0 < tile + kTI && c1 > tile))
-      chunk(kTI, c0, c1, std::false_type{});
+    if (c0 + kStage < b1) fetch(c0 + kStage);
+    // whole groups of 16 j
+    const int n = (min(kStage, b1 - c0) + 15) / 16 * (16 / kPhases);
+    const int own = (tile - c0) / kPhases;
+    if (tile >= c0 && own < n)
+      chunk([&](auto steps) {
+        steps(0, own, std::false_type{});
+        steps(own, own + kTI / kPhases, std::true_type{});
+        steps(own + kTI / kPhases, n, std::false_type{});
+      }, c0);
     else
-      chunk((c1 - c0 + kPhases - 1) / kPhases, c0, c1, std::true_type{});
+      chunk([&](auto steps) { steps(0, n, std::false_type{}); }, c0);
   }
 }
 
@@ -982,29 +1005,32 @@ __device__ __forceinline__ void pairs32(float2* buf, const float* __restrict__ x
                                         double& E, double* K, double w) {
   const int ph = (threadIdx.x & 63) / kTI;
   staged(
-      buf, b0, b1, tile, [&](int j) { return make_float2(xs[j], ys[j]); },
-      [&](int steps, int c0, int c1, auto test) {
-        constexpr bool T = decltype(test)::value;
+      buf, b0, b1, tile, make_float2(1e30f, 0.f),
+      [&](int j) { return make_float2(xs[j], ys[j]); },
+      [&](auto run, int c0) {
         float g0 = 0.f, g1 = 0.f, e = 0.f, k0 = 0.f, k1 = 0.f, k2 = 0.f;
+        run([&](int n0, int n1, auto test) {
+          constexpr bool T = decltype(test)::value;
 #pragma unroll 4
-        for (int k = 0; k < steps; ++k) {
-          const int b = k * kPhases + ph;
-          const float2 q = buf[b];
-          const float dx = xf - q.x, dy = yf - q.y;
-          const float r2 = __builtin_fmaf(dx, dx, dy * dy);
-          float inv = __builtin_amdgcn_rsqf(r2);
-          if (T) inv = (c0 + b >= c1 || c0 + b == self) ? 0.f : inv;
-          const float i3 = inv * inv * inv;
-          e += inv;
-          g0 = __builtin_fmaf(-dx, i3, g0);
-          g1 = __builtin_fmaf(-dy, i3, g1);
-          if (WK) {
-            const float t3 = 3.0f * i3 * inv * inv;
-            k0 += __builtin_fmaf(t3 * dx, dx, -i3);
-            k1 += t3 * dx * dy;
-            k2 += __builtin_fmaf(t3 * dy, dy, -i3);
+          for (int k = n0; k < n1; ++k) {
+            const int b = k * kPhases + ph;
+            const float2 q = buf[b];
+            const float dx = xf - q.x, dy = yf - q.y;
+            const float r2 = __builtin_fmaf(dx, dx, dy * dy);
+            float inv = __builtin_amdgcn_rsqf(r2);
+            if (T) inv = c0 + b == self ? 0.f : inv;
+            const float i3 = inv * inv * inv;
+            e += inv;
+            g0 = __builtin_fmaf(-dx, i3, g0);
+            g1 = __builtin_fmaf(-dy, i3, g1);
+            if (WK) {
+              const float t3 = 3.0f * i3 * inv * inv;
+              k0 += __builtin_fmaf(t3 * dx, dx, -i3);
+              k1 += t3 * dx * dy;
+              k2 += __builtin_fmaf(t3 * dy, dy, -i3);
+            }
           }
-        }
+        });
         G0 += g0;
         G1 += g1;
         E += w * (double)e;
@@ -1021,29 +1047,32 @@ __device__ __forceinline__ void pairs64(double2* buf, const double* __restrict__
                                         double& E, double& Ec, double* K, double w) {
   const int ph = (threadIdx.x & 63) / kTI;
   staged(
-      buf, b0, b1, tile, [&](int j) { return make_double2(xs[j], ys[j]); },
-      [&](int steps, int c0, int c1, auto test) {
-        constexpr bool T = decltype(test)::value;
+      buf, b0, b1, tile, make_double2(1e30, 0.0),
+      [&](int j) { return make_double2(xs[j], ys[j]); },
+      [&](auto run, int c0) {
         double e = 0.0;
+        run([&](int n0, int n1, auto test) {
+          constexpr bool T = decltype(test)::value;
 #pragma unroll 4
-        for (int k = 0; k < steps; ++k) {
-          const int b = k * kPhases + ph;
-          const double2 q = buf[b];
-          const double dx = xi - q.x, dy = yi - q.y;
-          const double r2 = __builtin_fma(dx, dx, dy * dy);
-          double inv = rsqrt64(r2);
-          if (T) inv = (c0 + b >= c1 || c0 + b == self) ? 0.0 : inv;
-          const double i3 = inv * inv * inv;
-          e += inv;
-          G0 = __builtin_fma(-dx, i3, G0);
-          G1 = __builtin_fma(-dy, i3, G1);
-          if (WK) {
-            const double t3 = 3.0 * i3 * inv * inv;
-            K[0] += __builtin_fma(t3 * dx, dx, -i3);
-            K[1] += t3 * dx * dy;
-            K[2] += __builtin_fma(t3 * dy, dy, -i3);
+          for (int k = n0; k < n1; ++k) {
+            const int b = k * kPhases + ph;
+            const double2 q = buf[b];
+            const double dx = xi - q.x, dy = yi - q.y;
+            const double r2 = __builtin_fma(dx, dx, dy * dy);
+            double inv = rsqrt64(r2);
+            if (T) inv = c0 + b == self ? 0.0 : inv;
+            const double i3 = inv * inv * inv;
+            e += inv;
+            G0 = __builtin_fma(-dx, i3, G0);
+            G1 = __builtin_fma(-dy, i3, G1);
+            if (WK) {
+              const double t3 = 3.0 * i3 * inv * inv;
+              K[0] += __builtin_fma(t3 * dx, dx, -i3);
+              K[1] += t3 * dx * dy;
+              K[2] += __builtin_fma(t3 * dy, dy, -i3);
+            }
           }
-        }
+        });
         const double v = w * e;
         const double tt = E + v;
         Ec += fabs(E) >= fabs(v) ? (E - tt) + v : (v - tt) + E;
@@ -1070,7 +1099,7 @@ __device__ __forceinline__ double phase_sum(double v, double& err) {  // and its
 template <bool WK, int MW>
 __global__ __launch_bounds__(64 * MW) void k_model(RelaxDev R) {
   // the waves' staged j, then their sums G0 G1 E Ec K0 K1 K2 by lane
-  __shared__ double2 buf[MW][64];
+  __shared__ double2 buf[MW][kStage];
   __shared__ double part[MW - 1][7][64];
   const int wb = blockIdx.x / kTiles;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1202,7 +1231,7 @@ __global__ __launch_bounds__(64 * MW) void k_cg_hvp(RelaxDev R) {
   struct alignas(32) ZW {
     double x, y, wx, wy;
   };
-  __shared__ ZW buf[MW][64];
+  __shared__ ZW buf[MW][kStage];
   __shared__ double part[MW - 1][2][64];
   const int wb = blockIdx.x / kTiles;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1223,23 +1252,25 @@ __global__ __launch_bounds__(64 * MW) void k_cg_hvp(RelaxDev R) {
   const double xi = R.zx[ac], yi = R.zy[ac];
   double Q0 = 0.0, Q1 = 0.0;
   staged(
-      buf[w], a0 + j0, a0 + j1, tile,
+      buf[w], a0 + j0, a0 + j1, tile, ZW{1e30, 0.0, 0.0, 0.0},
       [&](int j) { return ZW{R.zx[j], R.zy[j], R.cwx[j], R.cwy[j]}; },
-      [&](int steps, int c0, int c1, auto test) {
-        constexpr bool T = decltype(test)::value;
+      [&](auto run, int c0) {
+        run([&](int n0, int n1, auto test) {
+          constexpr bool T = decltype(test)::value;
 #pragma unroll 4
-        for (int k = 0; k < steps; ++k) {
-          const int b = k * kPhases + ph;
-          const ZW q = buf[w][b];
-          const double dx = xi - q.x, dy = yi - q.y;
-          const double r2 = __builtin_fma(dx, dx, dy * dy);
-          double inv = rsqrt64(r2);
-          if (T) inv = (c0 + b >= c1 || c0 + b == ac) ? 0.0 : inv;
-          const double i3 = inv * inv * inv;
-          const double sc = 3.0 * i3 * inv * inv * __builtin_fma(dx, q.wx, dy * q.wy);
-          Q0 += __builtin_fma(dx, sc, -q.wx * i3);
-          Q1 += __builtin_fma(dy, sc, -q.wy * i3);
-        }
+          for (int k = n0; k < n1; ++k) {
+            const int b = k * kPhases + ph;
+            const ZW q = buf[w][b];
+            const double dx = xi - q.x, dy = yi - q.y;
+            const double r2 = __builtin_fma(dx, dx, dy * dy);
+            double inv = rsqrt64(r2);
+            if (T) inv = c0 + b == ac ? 0.0 : inv;
+            const double i3 = inv * inv * inv;
+            const double sc = 3.0 * i3 * inv * inv * __builtin_fma(dx, q.wx, dy * q.wy);
+            Q0 += __builtin_fma(dx, sc, -q.wx * i3);
+            Q1 += __builtin_fma(dy, sc, -q.wy * i3);
+          }
+        });
       });
   if (w > 0) {
     part[w - 1][0][lane] = Q0;
