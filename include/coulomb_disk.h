@@ -432,7 +432,8 @@ int border_spread(double* x, double* y, int64_t n, const int32_t* flags, void* w
  * psi_6(i) = (1/z_i) sum_j ((r_j - r_i)/|r_j - r_i|)^6 over the neighbours
  * (0 for z <= 0).  Charges must be distinct and inside |r| <= 1 + 1e-9.
  * The convex hull is found on the host (monotone chain) from a copy of the
- * positions, so the call synchronises the stream.  ws:
+ * outermost charges, chosen on the device, so the call synchronises the
+ * stream.  ws:
  * coulomb_workspace_bytes(CD_OP_VORONOI, n, 0, 0, 0) bytes. */
 int voronoi_coordination(const double* x, const double* y, int64_t n, int32_t* z, double* psi6,
                          void* ws, size_t ws_bytes, void* stream);
