@@ -690,6 +690,7 @@ __global__ void k_geom_commit(RelaxDev R, const double* __restrict__ geom) {
 //           cancellation: with s = 1/r', o = 1/r and m = s o,
 //           s - o = (r^2 - r'^2) m^2 / (s + o), r^2 - r'^2 from the products
 //           of differences and sums of the coordinates
+//   kFinal: kGrad without blocks and kDelta at once, the change in hkxx
 // Blocks: K = 3 d d^T / r^5 - I / r^3 has trace 1/r^3, so the sums of
 // dx dx / r^5, dx dy / r^5 and 1/r^3 hold all of it.
 // Bound: FP64 issue (v_rsq_f64 and v_rcp_f64 take four slots): 22 slots a pair
@@ -699,16 +700,25 @@ __global__ void k_geom_commit(RelaxDev R, const double* __restrict__ geom) {
 // 4.85 (5.84 with an IEEE division).  In the rounds of a small FP64 batch (24
 // patches, N = 4e4) the evaluation and its sum take 20 + 7 us, 90 + 60 when the
 // partials of every wave were written and all patches' summed each round.
-enum ExactMode { kGrad = 0, kFar = 1, kDelta = 2 };
+enum ExactMode { kGrad = 0, kFar = 1, kDelta = 2, kFinal = 3 };
 constexpr int kEW = 4;
 
-// 1/|d| - 1/|o| for d = o - s (kDelta)
+// 1/|d| - 1/|o| for d = o - s (kDelta), u = 1/|d|
 __device__ __forceinline__ double delta_pair(double dx, double dy, double ox, double oy,
-                                             double sx, double sy) {
-  const double u = rsqrt64(__builtin_fma(dx, dx, dy * dy));
+                                             double sx, double sy, double u) {
   const double o = rsqrt64(__builtin_fma(ox, ox, oy * oy));
   const double m = u * o;
   return __builtin_fma(sx, ox + dx, sy * (oy + dy)) * m * m * rcp64(u + o);
+}
+__device__ __forceinline__ double delta_pair(double dx, double dy, double ox, double oy,
+                                             double sx, double sy) {
+  return delta_pair(dx, dy, ox, oy, sx, sy, rsqrt64(__builtin_fma(dx, dx, dy * dy)));
+}
+
+__device__ __forceinline__ void neumaier(double& sum, double& err, double v) {
+  const double t = sum + v;
+  err += fabs(sum) >= fabs(v) ? (sum - t) + v : (v - t) + sum;
+  sum = t;
 }
 
 // Whether a patch takes part in a pass (uniform over its actives).
@@ -749,6 +759,7 @@ __global__ __launch_bounds__(64 * kEW) void k_exact(RelaxDev R) {
   const double sx = xo - xi, sy = yo - yi;
   const uint64_t* mask = (MODE == kFar ? R.maskAH : R.maskA) + (size_t)p * R.nbN;
   double G0 = 0.0, G1 = 0.0, G2 = 0.0, G3 = 0.0, S3 = 0.0, Ee = 0.0, Ec = 0.0;
+  double De = 0.0, Dc = 0.0;  // kFinal: the energy change beside the energy
   const int range = blockIdx.y * kEW + w;
   const int J0 = min(R.nbN, range * R.jb), J1 = min(R.nbN, J0 + R.jb);
   const int share = (a1 - a0 + R.splits * kEW - 1) / (R.splits * kEW);
@@ -771,12 +782,12 @@ __global__ __launch_bounds__(64 * kEW) void k_exact(RelaxDev R) {
       const int jn = min(64, R.n - J * 64);
       const double* xb = R.x + (size_t)J * 64;
       const double* yb = R.y + (size_t)J * 64;
-      double eb = 0.0;
+      double eb = 0.0, db = 0.0;
       // the skip test only in blocks that hold charges of the patch (or its
       // halo); most blocks of a large N hold none
       auto block = [&](auto masked_tag) {
         constexpr bool M = decltype(masked_tag)::value;
-#pragma unroll(MODE == kDelta ? 4 : 8)
+#pragma unroll(MODE == kDelta || MODE == kFinal ? 4 : 8)
         for (int jj = 0; jj < jn; ++jj) {
           const bool skip = M && ((m >> jj) & 1ull);
           const double xj = xb[jj], yj = yb[jj];
@@ -786,8 +797,12 @@ __global__ __launch_bounds__(64 * kEW) void k_exact(RelaxDev R) {
             eb += skip ? 0.0 : v;
           } else {
             double inv = rsqrt64(__builtin_fma(dx, dx, dy * dy));
+            if (MODE == kFinal) {
+              const double v = delta_pair(dx, dy, xo - xj, yo - yj, sx, sy, inv);
+              db += skip ? 0.0 : v;
+            }
             inv = skip ? 0.0 : inv;
-            if (MODE == kGrad) eb += inv;
+            if (MODE != kFar) eb += inv;
             add(dx, dy, inv);
           }
         }
@@ -796,9 +811,9 @@ __global__ __launch_bounds__(64 * kEW) void k_exact(RelaxDev R) {
         block(std::true_type{});
       else
         block(std::false_type{});
-      const double tt = Ee + eb;  // Neumaier across 64-charge blocks
-      Ec += fabs(Ee) >= fabs(eb) ? (Ee - tt) + eb : (eb - tt) + Ee;
-      Ee = tt;
+      // Neumaier across 64-charge blocks
+      neumaier(Ee, Ec, eb);
+      if (MODE == kFinal) neumaier(De, Dc, db);
     }
     if (MODE != kFar) {
       // active-active pairs at the trial positions (half weight in the energy)
@@ -812,21 +827,24 @@ __global__ __launch_bounds__(64 * kEW) void k_exact(RelaxDev R) {
           v = b == ac ? 0.0 : 0.5 * delta_pair(dx, dy, ox, oy, ox - dx, oy - dy);
         } else {
           double inv = rsqrt64(__builtin_fma(dx, dx, dy * dy));
+          if (MODE == kFinal) {
+            const double ox = xo - R.z0x[b], oy = yo - R.z0y[b];
+            const double d = delta_pair(dx, dy, ox, oy, ox - dx, oy - dy, inv);
+            neumaier(De, Dc, b == ac ? 0.0 : 0.5 * d);
+          }
           inv = (b == ac) ? 0.0 : inv;
           v = 0.5 * inv;
           add(dx, dy, inv);
         }
-        const double tt = Ee + v;
-        Ec += fabs(Ee) >= fabs(v) ? (Ee - tt) + v : (v - tt) + Ee;
-        Ee = tt;
+        neumaier(Ee, Ec, v);
       }
     }
   };
-  if (MODE == kDelta || !wk)
+  if (MODE == kDelta || MODE == kFinal || !wk)
     pairs(std::false_type{});
   else
     pairs(std::true_type{});
-  double v[6] = {G0, G1, Ee + Ec, G2, G3, S3};
+  double v[6] = {G0, G1, Ee + Ec, MODE == kFinal ? De + Dc : G2, G3, S3};
   if (w > 0) {
 #pragma unroll
     for (int c = 0; c < 6; ++c) part[w - 1][c][lane] = v[c];
@@ -841,7 +859,8 @@ __global__ __launch_bounds__(64 * kEW) void k_exact(RelaxDev R) {
   R.px[q] = v[0];
   R.py[q] = v[1];
   if (MODE != kFar) R.pe[q] = v[2];
-  if (MODE != kDelta && wk) {
+  if (MODE == kFinal) R.pkxx[q] = v[3];
+  if ((MODE == kGrad || MODE == kFar) && wk) {
     R.pkxx[q] = 3.0 * v[3] - v[5];
     R.pkxy[q] = 3.0 * v[4];
     R.pkyy[q] = 2.0 * v[5] - 3.0 * v[3];
@@ -881,6 +900,7 @@ __global__ __launch_bounds__(64 * kESW) void k_exact_sum(RelaxDev R) {
         v[1] += R.py[q];
       }
       if (MODE != kFar) v[2] += R.pe[q];
+      if (MODE == kFinal) v[3] += R.pkxx[q];
       if (wk) {
         v[3] += R.pkxx[q];
         v[4] += R.pkxy[q];
@@ -906,7 +926,8 @@ __global__ __launch_bounds__(64 * kESW) void k_exact_sum(RelaxDev R) {
     R.fhyy[a] = v[5];
     return;
   }
-  if (MODE == kGrad) {
+  if (MODE == kFinal) R.hkxx[a] = v[3];  // the blocks are not used again
+  if (MODE == kGrad || MODE == kFinal) {
     R.hgx[a] = v[0];
     R.hgy[a] = v[1];
     if (wk) {  // else the last blocks taken stay (the preconditioner may lag)
@@ -2416,12 +2437,13 @@ __global__ __launch_bounds__(kUpd) void k_finish(RelaxDev R, double tol, int exa
   }
 }
 
-__global__ __launch_bounds__(kUpd) void k_finish_delta(RelaxDev R, double* __restrict__ dE) {
+__global__ __launch_bounds__(kUpd) void k_finish_delta(RelaxDev R, const double* __restrict__ terms,
+                                                       double* __restrict__ dE) {
   WG_RED_LDS(red);
   const int p = blockIdx.x, t = threadIdx.x;
   const int a0 = R.ptr[p], a1 = R.ptr[p + 1];
   double e = 0.0;
-  for (int a = a0 + t; a < a1; a += kUpd) e += R.eterm[a];
+  for (int a = a0 + t; a < a1; a += kUpd) e += terms[a];
   const double d = block_sum(e, red);
   if (t == 0 && dE) dE[p] = d;
 }
@@ -3094,17 +3116,24 @@ int relax_subdomains(const double* x, const double* y, int64_t n, int32_t n_patc
   // exact energy and reduced gradient at the final positions, then the exact
   // energy change from the snapshot
   hipLaunchKernelGGL(k_copy_z_to_t, dim3(tb), dim3(256), 0, st, D);
-  if (x_out || e_sub || gtan_inf || iters || status) {  // a call for dE alone skips them
-    exact_grad(1);
+  const bool state = x_out || e_sub || gtan_inf || iters || status;  // a call for dE alone skips it
+  if (state) {
+    if (dE) {  // one pass over the charges for both
+      hipLaunchKernelGGL(k_exact<kFinal>, eg, eb, 0, st, D);
+      hipLaunchKernelGGL(k_exact_sum<kFinal>, dim3(tb64), dim3(64 * kESW), 0, st, D);
+    } else {
+      exact_grad(1);
+    }
     hipLaunchKernelGGL(k_finish, dim3(n_patches), dim3(kUpd), 0, st, D, o.gtol,
                        o.precision == CD_FP64 ? 1 : 0, x_out, y_out, e_sub, gtan_inf, iters,
                        status);
-  }
-  if (dE) {
+  } else if (dE) {
     hipLaunchKernelGGL(k_exact<kDelta>, eg, eb, 0, st, D);
     hipLaunchKernelGGL(k_exact_sum<kDelta>, dim3(tb64), dim3(64 * kESW), 0, st, D);
-    hipLaunchKernelGGL(k_finish_delta, dim3(n_patches), dim3(kUpd), 0, st, D, dE);
   }
+  if (dE)
+    hipLaunchKernelGGL(k_finish_delta, dim3(n_patches), dim3(kUpd), 0, st, D,
+                       state ? D.hkxx : D.eterm, dE);
   rc = hip_status(hipGetLastError());
   if (rc) return rc;
   return hip_status(hipStreamSynchronize(st));
