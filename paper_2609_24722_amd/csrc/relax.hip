@@ -694,10 +694,10 @@ __global__ void k_geom_commit(RelaxDev R, const double* __restrict__ geom) {
 // Blocks: K = 3 d d^T / r^5 - I / r^3 has trace 1/r^3, so the sums of
 // dx dx / r^5, dx dy / r^5 and 1/r^3 hold all of it.
 // Bound: FP64 issue (v_rsq_f64 and v_rcp_f64 take four slots): 22 slots a pair
-// for kFar, 18 for kGrad (23 with blocks), 43 for kDelta.  32 patches of 200 to
+// for kFar, 18 for kGrad (23 with blocks), 43 for kDelta, 48 for kFinal.  32 patches of 200 to
 // 2000 actives at N = 1e5: kFar 2.27 ms (2.76 with three block sums more a pair,
-// a partial sum per wave), the final kGrad 2.12 (3.10 with the blocks), kDelta
-// 4.85 (5.84 with an IEEE division).  In the rounds of a small FP64 batch (24
+// a partial sum per wave), a final kGrad 2.12 (3.10 with the blocks) and kDelta
+// 4.85 (5.84 with an IEEE division), kFinal in their place 5.3.  In the rounds of a small FP64 batch (24
 // patches, N = 4e4) the evaluation and its sum take 20 + 7 us, 90 + 60 when the
 // partials of every wave were written and all patches' summed each round.
 enum ExactMode { kGrad = 0, kFar = 1, kDelta = 2, kFinal = 3 };
