@@ -1476,6 +1476,8 @@ bool make_plan(int op, int64_t n64, int precision, char* base, Plan& P, int shap
     P.Cb = cb < (size_t)P.C ? (int)cb : P.C;
     P.chunk_bytes = per;
   } else {
+    P.Cb = 0;
+    P.chunk_bytes = 0;
     // enough waves to fill 256 CUs several times over
     int sp = (16384 + P.nb - 1) / P.nb;
     if (sp < 1) sp = 1;
@@ -1914,7 +1916,8 @@ static int plan_fixed(int64_t n, int precision, char* base, size_t cap, Plan& P)
   if (!make_plan(CD_OP_FORCES, n, precision, nullptr, P, shape)) return CD_ERR_INVALID_ARG;
   int cb = P.Cb;
   if (P.total > cap) {
-    const size_t over = P.total - cap;  // chunks to drop, rounded up
+    if (!P.chunk_bytes) return CD_ERR_CAPACITY;  // a one-sided plan: nothing to drop
+    const size_t over = P.total - cap;           // chunks to drop, rounded up
     const size_t drop = (over + P.chunk_bytes - 1) / P.chunk_bytes;
     cb = drop < (size_t)P.Cb ? P.Cb - (int)drop : 0;
     // the carve aligns each piece, so step down until the plan fits

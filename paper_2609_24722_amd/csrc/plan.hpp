@@ -84,9 +84,9 @@ bool make_plan(int op, int64_t n64, int precision, char* base, Plan& P, int shap
 
 // Forces and energy (coulomb_forces) with the scratch carved from a fixed
 // region [base, base + cap) (base 256-byte aligned): the symmetric pass's
-// chunks are batched so that their partial sums fit.  Returns
-// CD_ERR_CAPACITY, before anything is enqueued, when not even one chunk per
-// batch fits.
+// chunks are batched so that their partial sums fit.  When not even one chunk
+// per batch fits, CD_FP64 takes the one-sided pass; returns CD_ERR_CAPACITY,
+// before anything is enqueued, on CD_MIXED and when that pass does not fit.
 int forces_fixed(const double* x, const double* y, int64_t n, int precision, double* fx,
                  double* fy, double* e_total, char* base, size_t cap, hipStream_t st);
 // The same plan test alone (host only): CD_OK if the call fits in cap bytes.
