@@ -935,8 +935,8 @@ __global__ __launch_bounds__(256) void k_one64_reduce(OneReduceArgs a) {
 // The decomposition of the FP32 pass (super-blocks of NI x 64 charges, offsets
 // o = 1..ns/2, a workgroup owning W super-blocks and a chunk of L offsets), in
 // FP64 throughout: every unordered pair once, 20 issue slots for energy and
-// both sides' forces against 18 per ordered pair when each side is summed on
-// its own (v_rsq_f64 takes four).
+// both sides' forces (and the moves below) against 18 per ordered pair when
+// each side is summed on its own (v_rsq_f64 takes four).
 //
 // A pass is the NI x 64 i charges of a wave (NI per lane, in registers)
 // against 64 j charges.  FP64 subtractions take no DPP operand, so the j
@@ -956,7 +956,7 @@ __global__ __launch_bounds__(256) void k_one64_reduce(OneReduceArgs a) {
 // terms of pad charges (MASK).
 //
 // Bound: FP64 issue.  At 1e5 charges energy and forces take 3.14 ms a call, 21
-// slots per unordered pair at the measured 3.75e13 lane instructions/s make
+// slots per unordered pair (20 and a move) at the measured 3.75e13 lane instructions/s make
 // 2.8 (one-sided 5.4 ms); local energies 2.27 ms (3.98 one-sided).
 template <int MODE, bool LOCAL>
 struct Sym64 {
@@ -1189,6 +1189,7 @@ k_sym64(Sym64Args a) {
 // mj, -1 for none), then the chunks in order.  A workgroup takes 128 charges
 // (two components, or one for the energies); workgroup nblk128 sums the
 // total energy, per chunk and then the chunks in order.
+constexpr int kSym64Slots = 3;  // j slots that can hold one super-block (see sym64_shape)
 struct Sym64ReduceArgs {
   const double* ip0;
   const double* ip1;
@@ -1265,22 +1266,15 @@ __global__ __launch_bounds__(256) void k_sym64_reduce(Sym64ReduceArgs a) {
     // chunk by chunk, the loads of eight chunks going out together (32 of
     // them: the pass waits on memory; 14.2 us at 1e4 charges with four)
     for (int c = 0; c < a.nc; c += 8) {
-      double vc[8][4];
+      double vc[8][1 + kSym64Slots];
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
         const int cl = c + q < a.nc ? c + q : -1;
         vc[q][0] = cl >= 0 ? ip[(size_t)cl * a.npad + s] : 0.0;
 #pragma unroll
-        for (int m = 0; m < 3; ++m) {
+        for (int m = 0; m < kSym64Slots; ++m) {
           const int j = cl >= 0 && m < a.mj ? lst[cl * a.mj + m] : -1;
           vc[q][m + 1] = j >= 0 ? jp[(size_t)j * SBN + l] : 0.0;
-        }
-      }
-      for (int m = 3; m < a.mj; ++m) {  // (more slots than the shapes of sym64_shape need)
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          const int j = c + q < a.nc ? lst[(c + q) * a.mj + m] : -1;
-          if (j >= 0) vc[q][3] += jp[(size_t)j * SBN + l];
         }
       }
 #pragma unroll
@@ -1409,9 +1403,18 @@ static int tuned_shape(int op, int64_t n) {
 struct Sym64Shape {
   int ni, W, L;
 };
+// j slots of a chunk that can hold a charge's super-block: S = L + W - 1 slots,
+// W apart for one super-block; S <= ns keeps the window from wrapping onto
+// itself at every size the pass is used for.
+constexpr int kSym64Chunk = 4;
+constexpr int kSym64Window = kSym64Chunk + kSym64Waves - 1;
+static_assert((kSym64Window + kSym64Waves - 1) / kSym64Waves + 1 <= kSym64Slots, "j slots per chunk");
+static_assert(kSym64MinEnergy <= kSym64Min && kSym64MinEnergy / (2 * kBlk) >= kSym64Window &&
+                  kSym64Wide / (4 * kBlk) >= kSym64Window,
+              "the j window fits the smallest sizes of both widths");
 static Sym64Shape sym64_shape(int n) {
-  if (n >= kSym64Wide) return {4, kSym64Waves, 4};
-  return {2, kSym64Waves, n <= 8000 ? 1 : n <= 14000 ? 2 : 4};
+  if (n >= kSym64Wide) return {4, kSym64Waves, kSym64Chunk};
+  return {2, kSym64Waves, n <= 8000 ? 1 : n <= 14000 ? 2 : kSym64Chunk};
 }
 
 // ---------------------------------------------------------------- planning --
@@ -1460,13 +1463,12 @@ bool make_plan(int op, int64_t n64, int precision, char* base, Plan& P, int shap
     P.ns = (n + sb - 1) / sb;
     P.nb = sh.ni * P.ns;
     P.npad = P.nb * kBlk;
-    // S = L + W - 1 <= ns keeps the j window from wrapping onto itself
-    P.W = P.ns < sh.W ? P.ns : sh.W;
-    P.L = sh.L < P.ns + 1 - P.W ? sh.L : P.ns + 1 - P.W;
-    P.C = (P.ns / 2 + P.L - 1) / P.L;  // 0: everything lies in one super-block
+    P.W = sh.W;
+    P.L = sh.L;
+    P.C = (P.ns / 2 + P.L - 1) / P.L;
     P.G = (P.ns + P.W - 1) / P.W;
     P.S = P.L + P.W - 1;
-    P.mj = (P.S + P.W - 1) / P.W + 1;
+    P.mj = (P.S + P.W - 1) / P.W + 1;  // at most kSym64Slots
     const size_t per = ((size_t)P.npad + (size_t)P.G * P.S * sb) * sizeof(double) *
                        (mode == kEnergy ? 1 : 2);
     size_t cb = kSymBatchBytes / per;
@@ -1745,7 +1747,7 @@ static void run_sym64n(const Plan& P, hipStream_t st, double* out0, double* out1
   constexpr bool ESUM = MODE != kHvp && !LOCAL;  // total energy from the per-workgroup sums
   const int parts = T::kJ ? P.nred : 0;
   mark(g_ev_start, st);
-  for (int c0 = 0; c0 == 0 || c0 < P.C; c0 += P.Cb) {
+  for (int c0 = 0; c0 < P.C; c0 += P.Cb) {
     const int nc = P.C - c0 < P.Cb ? P.C - c0 : P.Cb;
     a.c0 = r.c0 = c0;
     a.nc = r.nc = nc;
@@ -1758,7 +1760,6 @@ static void run_sym64n(const Plan& P, hipStream_t st, double* out0, double* out1
     if (grid)
       hipLaunchKernelGGL((k_sym64_reduce<MODE, LOCAL, NI>), dim3(grid), dim3(256),
                          (size_t)nc * P.mj * sizeof(int32_t), st, r);
-    if (r.last) break;
   }
   if (e_total && MODE == kEnergy && LOCAL) sum_blocks(P.eblk, P.nred, e_total, st);
 }
