@@ -204,7 +204,8 @@ __global__ __launch_bounds__(256) void k_hull_rows(const double* __restrict__ x,
   out[r].v[lane] = best;
   out[r].i[lane] = bi;
 }
-// rows[0] gets the extreme of all rows; the candidate count is cleared.
+// Row m, one past the m input rows, gets the indices of the extremes of all of
+// them (not their values); the candidate count is cleared.
 __global__ __launch_bounds__(1024) void k_hull_extremes(HullRow* __restrict__ rows, int m,
                                                         HullPoint* __restrict__ pts) {
   __shared__ double v[16][kHullDirs];
@@ -230,7 +231,7 @@ __global__ __launch_bounds__(1024) void k_hull_extremes(HullRow* __restrict__ ro
       best = v[q][lane];
       bi = i[q][lane];
     }
-  rows[m].i[lane] = bi;  // row m: the result
+  rows[m].i[lane] = bi;
   if (lane == 0) pts[0].i = 0;
 }
 // Lists the charges not clearly inside the polygon (in any order).
