@@ -2459,6 +2459,7 @@ struct RPlan {
   int graph_rounds = 8;
   int64_t wide_blocks = 128;
   bool use_graphs = true;  // rounds replayed from HIP graphs (else launched one by one)
+  int cg_rounds = 1;       // CG iterations per round (cg_per_round)
   int regj = kRegJ;        // actives per thread in registers in the update (kRegJ or kRegJWide)
   size_t total;
   RelaxDev D;
@@ -2720,24 +2721,38 @@ static void launch_update(RPlan& R, hipStream_t s, bool hist32) {
 }
 
 // CG iterations per round.  A Newton step takes tens of them for each
-// evaluation, and an evaluation launched in a round without a trial costs its
-// launches all the same (exact pass and sum, 27 us in a batch of 24 patches,
-// against 18 for a CG iteration).  A patch's own sequence of steps does not
-// depend on it.  That batch takes 11.8 ms with one, 10.4 with two, 10.0 with
-// three, 9.8 with four, 10.0 with eight; a batch of four small patches, where
-// each empty launch and graph node shows, 4.6, 4.9, 5.2, 5.8, 7.5.
-constexpr int kCgPerRound = 3;
+// evaluation.  In a batch on the plain path some patch has a trial in nearly
+// every round, and the evaluation costs its launches and latency whatever the
+// others are doing (exact pass and sum, 27 us in a batch of 24 patches, against
+// 18 for a CG iteration), so more iterations between evaluations pay, the more
+// so the more patches there are; in a batch of few, every further iteration is
+// launched in vain at the end of a CG phase and of the call.  Times with one /
+// two / three, ms, mean over twelve batches started near their minimum (N of 1e4, 2e4
+// and 4e4; four batches where one N is given) and, in brackets, over eight started far from it and relaxed for 60
+// iterations at most:
+//   1 patch of 60 to 180    2.67 / 2.43 / 2.59
+//   4 of 60 to 180          3.52 / 3.35 / 3.39    (4 of 30 to 100: 5.81 / 5.93 / 6.26)
+//   7 of 60 to 300          4.79 / 4.50 / 4.48
+//   8 of 60 to 600          6.68 / 6.22 / 6.19    (22.7 / 21.2 / 21.0)
+//   12 of 60 to 450, 4e4    8.51 / 7.88 / 7.57
+//   24 of 60 to 300, 4e4    8.51 / 7.52 / 7.16    (24 of 30 to 100: 17.0 / 15.9 / 15.9)
+//   64 of 60 to 400         (to 1e-6, three batches: 81.5 / 75.5 / 74.0)
+// The mixed path's evaluation is a pass over the patch's own pairs, no dearer
+// than a CG iteration, and a patch stops after one Newton step: 4 patches of 60
+// to 300 take 28.0 / 29.4 / 32.7 (20.5 / 23.3 / 26.2).
+// A patch's own sequence of steps on the plain path does not depend on it.
+static int cg_per_round(int precision, int P) { return precision != CD_FP64 ? 1 : P < 8 ? 2 : 3; }
 
 template <class EvalFn>
 static void launch_round(RPlan& R, hipStream_t s, bool hist32, int shape, EvalFn& eval) {
   if (R.D.polish) {  // CG iterations of patches in a Newton step, then the trial evaluations
-    for (int k = 1; k <= kCgPerRound; ++k) {
+    for (int k = 1; k <= R.cg_rounds; ++k) {
       if (shape)
         hipLaunchKernelGGL((k_cg_hvp<kMWWide>), dim3(R.D.nblk * kTiles), dim3(64 * kMWWide), 0, s,
                            R.D);
       else
         hipLaunchKernelGGL((k_cg_hvp<kMW>), dim3(R.D.nblk * kTiles), dim3(64 * kMW), 0, s, R.D);
-      if (k < kCgPerRound) hipLaunchKernelGGL(k_cg_update, dim3(R.P), dim3(kUpd), 0, s, R.D);
+      if (k < R.cg_rounds) hipLaunchKernelGGL(k_cg_update, dim3(R.P), dim3(kUpd), 0, s, R.D);
     }
   }
   eval(s, shape);
@@ -2928,6 +2943,7 @@ int relax_subdomains(const double* x, const double* y, int64_t n, int32_t n_patc
   R.graph_rounds = sched.graph_rounds;
   R.wide_blocks = sched.wide_blocks;
   R.use_graphs = o.launch == CD_LAUNCH_GRAPH;
+  R.cg_rounds = cg_per_round(o.precision, n_patches);
   D.tu = o.coords == CD_COORDS_TU;
   D.tu_rmin = 1e-3 * D.sigma;
   // the Newton steps work in (x, y) and angle coordinates: none in (t, u); a
