@@ -71,7 +71,12 @@ enum { CD_FLAG_NONFINITE = 1, CD_FLAG_OUTSIDE = 2, CD_FLAG_COINCIDENT = 4 };
 /* Bytes of device scratch that `op` needs for these sizes (n_patches and
  * total_active matter only for CD_OP_PATCHES / CD_OP_RELAX; lanczos_k is
  * passed in n_patches for CD_OP_LANCZOS; the number of zones in n_patches
- * for CD_OP_ZONES).  Returns 0 for invalid sizes. */
+ * for CD_OP_ZONES).  Returns 0 for invalid sizes.
+ * The sizes of CD_OP_ENERGY, CD_OP_FORCES and CD_OP_HVP do not grow with n
+ * alone: where the launch shape changes, a smaller n can need up to about
+ * twice as much as a larger one (CD_FP64 forces: 152 MiB at 59 999, 79 at
+ * 60 000).  A workspace shared by several n takes the largest of their
+ * sizes, not the size of the largest. */
 size_t coulomb_workspace_bytes(int op, int64_t n, int32_t n_patches, int64_t total_active,
                                int precision);
 
