@@ -318,8 +318,10 @@ __device__ double lens_reach(double cx, double cy, double vx, double vy, double 
 // that near charges cut first, 64 of a ring at a time, one per lane.  Each lane
 // tests its charge's bisector against the polygon's vertices; the first charge
 // that cuts clips the polygon (one vertex per lane, their places by ballots),
-// the lanes after it that did cut test again (a charge that left the larger
-// polygon whole cuts no part of it), and so on.  A charge of ring k >= 1 lies
+// all lanes after it test the new polygon, and so on: the charges act one after
+// the other, each on the polygon the ones before it left.  (A charge that
+// left the larger polygon whole can still cut a corner of rounding's size off
+// the new one, where more than three charges lie on a circle about a vertex.)  A charge of ring k >= 1 lies
 // at least (k - 1) c from r_i, so the rings stop once that is beyond every
 // vertex's reach (lens_reach).
 // The search widens (2, 6, 18, .. cells on each side, then the whole grid) until
@@ -426,7 +428,8 @@ __global__ __launch_bounds__(64 * kVorW) void k_voronoi(const double* __restrict
             for (int q = 0; q < nv; ++q) out |= s_px[w][cur][q] * dx + s_py[w][cur][q] * dy - hd > 0.0;
             return out;
           };
-          uint64_t m = __ballot(j != i && hd > 0.0 && cuts());
+          const bool real = j != i && hd > 0.0;
+          uint64_t m = __ballot(real && cuts());
           while (m) {
             const int f = __builtin_ctzll(m);
             const double ex = lane_f64(dx, f), ey = lane_f64(dy, f), eh = lane_f64(hd, f);
@@ -463,8 +466,7 @@ __global__ __launch_bounds__(64 * kVorW) void k_voronoi(const double* __restrict
             cur = nx;
             nv = nn;
             fence();
-            m &= ~((2ull << f) - 1);
-            if (m) m = __ballot(((m >> lane) & 1) && cuts());
+            m = __ballot(real && lane > f && cuts());
           }
         }
         fence();  // s_pre and s_st are written again
