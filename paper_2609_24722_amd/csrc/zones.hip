@@ -3,8 +3,9 @@
 //
 //  - k_defect_stats: one workgroup.  Mean and population standard deviation
 //    of the local energies (fixed-order FP64 sums) and the threshold
-//    mu + kappa*sigma_e; k_defect_count, k_defect_list: the list of charges
-//    above it in increasing index order.
+//    mu + kappa*sigma_e; k_defect_count, k_defect_list (up to kDefSmall
+//    charges the same workgroup): the list of charges above it in increasing
+//    index order.
 //  - k_zone_pick: one thread per zone.  Centre (a defect charge or the
 //    caller's disk point, by the caller's uniform draws) and the radius of
 //    the triangle wave.
@@ -28,6 +29,11 @@ namespace cd {
 constexpr int kZT = 1024;  // threads of the one-workgroup kernels
 constexpr int kZW = kZT / 64;
 constexpr int kDefE = 4 * kZT;  // charges per workgroup of the defect list
+// Up to this many charges the one-workgroup kernel writes the list itself: the
+// two launches of the spread list cost 4 us (call with 50 zones, us, list in the
+// kernel against spread: 1000 charges 33.3 / 38.8, 5000 35.9 / 39.0, 12 000
+// 39.8 / 41.3, 16 000 41.6 / 41.5, 24 000 46.6 / 43.7).
+constexpr int kDefSmall = 16384;
 constexpr int kZoneS = 4;       // workgroups per zone
 constexpr int kZoneWaves = kZoneS * kZW;
 
@@ -82,25 +88,50 @@ __device__ int block_sum_int(int v, int* ws, int* before = nullptr) {
 
 #pragma clang fp contract(off)
 
-// Sum over the thread's charges t, t + kZT, ... in order, 16 loads going out
-// together (one at a time the two sums and the list took 104 us at n = 1e5).
+// Sum over the thread's charges t, t + kZT, ... in order; up to 16 loads go out
+// together (one at a time the two sums and the list took 104 us at n = 1e5), and
+// two where fewer are left.
+template <int U, class F>
+__device__ __forceinline__ void strided_group(const double* __restrict__ e, int n, int b, F f,
+                                              double& s) {
+  double v[U];
+#pragma unroll
+  for (int q = 0; q < U; ++q) v[q] = e[min(b + q * kZT + (int)threadIdx.x, n - 1)];
+#pragma unroll
+  for (int q = 0; q < U; ++q)
+    if (b + q * kZT + (int)threadIdx.x < n) s += f(v[q]);
+}
 template <class F>
 __device__ __forceinline__ double strided_sum(const double* __restrict__ e, int n, F f) {
   double s = 0.0;
-  for (int j0 = threadIdx.x; j0 < n; j0 += 16 * kZT) {
-    double v[16];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) v[q] = e[min(j0 + q * kZT, n - 1)];
-#pragma unroll
-    for (int q = 0; q < 16; ++q)
-      if (j0 + q * kZT < n) s += f(v[q]);
-  }
+  int b = 0;
+  for (; n - b > 8 * kZT; b += 16 * kZT) strided_group<16>(e, n, b, f, s);
+  for (; n - b > 2 * kZT; b += 8 * kZT) strided_group<8>(e, n, b, f, s);
+  for (; b < n; b += 2 * kZT) strided_group<2>(e, n, b, f, s);
   return s;
 }
 
+// Defects of the thread's four consecutive charges of block `b`, as bits.
+__device__ __forceinline__ int defect_bits(const double* __restrict__ e, int n, double thr, int b) {
+  const int j0 = b * kDefE + 4 * threadIdx.x;
+  int m = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) m |= (j0 + q < n && e[min(j0 + q, n - 1)] > thr) << q;
+  return m;
+}
+__device__ __forceinline__ void defect_write(int m, int b, int pos, int32_t* __restrict__ list) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    if ((m >> q) & 1) list[pos++] = b * kDefE + 4 * threadIdx.x + q;
+}
+
+// LIST: the list too (n up to kDefSmall).
+template <bool LIST>
 __global__ __launch_bounds__(kZT) void k_defect_stats(const double* __restrict__ e, int n,
-                                                      double kappa, double* __restrict__ stats) {
+                                                      double kappa, double* __restrict__ stats,
+                                                      int32_t* __restrict__ list) {
   __shared__ double red[kZW];
+  __shared__ int ws[kZW];
   const double s = strided_sum(e, n, [](double v) { return v; });
   const double mu = block_sum_fixed(s, red) / (double)n;
   const double q = strided_sum(e, n, [mu](double v) {
@@ -110,26 +141,29 @@ __global__ __launch_bounds__(kZT) void k_defect_stats(const double* __restrict__
   const double var = block_sum_fixed(q, red) / (double)n;
   const double sigma = __dsqrt_rn(var);
   const double ks = kappa * sigma;
+  const double thr = mu + ks;
+  int base = 0;
+  if (LIST)
+    for (int b = 0; b * kDefE < n; ++b) {
+      const int m = defect_bits(e, n, thr, b);
+      int before;
+      const int total = block_sum_int(__popc(m), ws, &before);
+      defect_write(m, b, base + before, list);
+      base += total;
+    }
   if (threadIdx.x == 0) {
     stats[0] = mu;
     stats[1] = sigma;
-    stats[2] = mu + ks;
+    stats[2] = thr;
+    if (LIST) stats[3] = (double)base;
   }
 }
 
-// Defects of the thread's four consecutive charges, as bits.
-__device__ __forceinline__ int defect_bits(const double* __restrict__ e, int n, double thr) {
-  const int j0 = blockIdx.x * kDefE + 4 * threadIdx.x;
-  int m = 0;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) m |= (j0 + q < n && e[min(j0 + q, n - 1)] > thr) << q;
-  return m;
-}
 __global__ __launch_bounds__(kZT) void k_defect_count(const double* __restrict__ e, int n,
                                                       const double* __restrict__ stats,
                                                       int32_t* __restrict__ sums) {
   __shared__ int ws[kZW];
-  const int t = block_sum_int(__popc(defect_bits(e, n, stats[2])), ws);
+  const int t = block_sum_int(__popc(defect_bits(e, n, stats[2], blockIdx.x)), ws);
   if (threadIdx.x == 0) sums[blockIdx.x] = t;
 }
 __global__ __launch_bounds__(kZT) void k_defect_list(const double* __restrict__ e, int n,
@@ -140,13 +174,9 @@ __global__ __launch_bounds__(kZT) void k_defect_list(const double* __restrict__ 
   int base = 0, before;
   for (int q = threadIdx.x; q < (int)blockIdx.x; q += kZT) base += sums[q];
   base = block_sum_int(base, ws);
-  const int m = defect_bits(e, n, stats[2]);
+  const int m = defect_bits(e, n, stats[2], blockIdx.x);
   const int total = block_sum_int(__popc(m), ws, &before);
-  int pos = base + before;
-  const int j0 = blockIdx.x * kDefE + 4 * threadIdx.x;
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-    if ((m >> q) & 1) list[pos++] = j0 + q;
+  defect_write(m, blockIdx.x, base + before, list);
   if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) stats[3] = (double)(base + total);
 }
 
@@ -343,9 +373,15 @@ int defect_zones(const double* x, const double* y, const double* e, int64_t n, i
   if (stats) st_d = stats;
   hipStream_t st = (hipStream_t)stream;
   const int nw = ((int)n + kDefE - 1) / kDefE;
-  hipLaunchKernelGGL(k_defect_stats, dim3(1), dim3(kZT), 0, st, e, (int)n, opts->kappa, st_d);
-  hipLaunchKernelGGL(k_defect_count, dim3(nw), dim3(kZT), 0, st, e, (int)n, st_d, sums);
-  hipLaunchKernelGGL(k_defect_list, dim3(nw), dim3(kZT), 0, st, e, (int)n, st_d, sums, list);
+  if (n <= kDefSmall) {
+    hipLaunchKernelGGL(k_defect_stats<true>, dim3(1), dim3(kZT), 0, st, e, (int)n, opts->kappa,
+                       st_d, list);
+  } else {
+    hipLaunchKernelGGL(k_defect_stats<false>, dim3(1), dim3(kZT), 0, st, e, (int)n, opts->kappa,
+                       st_d, list);
+    hipLaunchKernelGGL(k_defect_count, dim3(nw), dim3(kZT), 0, st, e, (int)n, st_d, sums);
+    hipLaunchKernelGGL(k_defect_list, dim3(nw), dim3(kZT), 0, st, e, (int)n, st_d, sums, list);
+  }
   if (n_zones > 0)
     hipLaunchKernelGGL(k_zone_pick, dim3((n_zones + 255) / 256), dim3(256), 0, st, x, y, st_d,
                        list, draws, n_zones, *opts, cx, cy, rz, centre_idx);
