@@ -9,7 +9,7 @@
 //  - k_zone_pick: one thread per zone.  Centre (a defect charge or the
 //    caller's disk point, by the caller's uniform draws) and the radius of
 //    the triangle wave.
-//  - k_zone_count / k_zone_fill: kZoneS workgroups per zone, each wave a
+//  - k_zone_count / k_zone_fill: one to kZoneS workgroups per zone, each wave a
 //    contiguous range of the charges.  Every charge within the radius,
 //    counted, then listed in increasing index order.
 //  - zone_batches: host code.  Greedy assignment of the zones to batches of
@@ -34,7 +34,7 @@ constexpr int kDefE = 4 * kZT;  // charges per workgroup of the defect list
 // kernel against spread: 1000 charges 33.3 / 38.8, 5000 35.9 / 39.0, 12 000
 // 39.8 / 41.3, 16 000 41.6 / 41.5, 24 000 46.6 / 43.7).
 constexpr int kDefSmall = 16384;
-constexpr int kZoneS = 4;       // workgroups per zone
+constexpr int kZoneS = 4;       // workgroups per zone, at most
 constexpr int kZoneWaves = kZoneS * kZW;
 
 size_t zones_workspace_bytes(int op, int64_t n, int32_t n_zones) {
@@ -217,33 +217,40 @@ __device__ __forceinline__ bool in_zone(double xj, double yj, double c0, double 
   return d2 <= r2;
 }
 
-// The calling wave's range of the charges, eight blocks of 64 at a time (their
-// loads go out together): f(index, in the zone).
+// The calling wave's range of the charges, in blocks of 64: f(index, in the
+// zone).  Eight blocks' loads go out together, two where fewer are left.
+template <int U, class F>
+__device__ __forceinline__ void zone_group(const double* __restrict__ x,
+                                           const double* __restrict__ y, double c0, double c1,
+                                           double r2, int b, int j1, F f) {
+  const int lane = threadIdx.x & 63;
+  double vx[U], vy[U];
+#pragma unroll
+  for (int q = 0; q < U; ++q) {
+    const int j = min(b + q * 64 + lane, j1 - 1);
+    vx[q] = x[j];
+    vy[q] = y[j];
+  }
+#pragma unroll
+  for (int q = 0; q < U; ++q) {
+    const int j = b + q * 64 + lane;
+    if (b + q * 64 < j1) f(j, j < j1 && in_zone(vx[q], vy[q], c0, c1, r2));
+  }
+}
 template <class F>
 __device__ __forceinline__ void zone_sweep(const double* __restrict__ x,
                                            const double* __restrict__ y, int n, double c0,
                                            double c1, double r2, int g, F f) {
-  const int lane = threadIdx.x & 63;
-  const int per = (n + 64 * kZoneWaves - 1) / (64 * kZoneWaves) * 64;
+  const int waves = gridDim.y * kZW;
+  const int per = (n + 64 * waves - 1) / (64 * waves) * 64;
   const int j0 = min(n, g * per), j1 = min(n, j0 + per);
-  for (int b = j0; b < j1; b += 512) {
-    double vx[8], vy[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int j = min(b + q * 64 + lane, j1 - 1);
-      vx[q] = x[j];
-      vy[q] = y[j];
-    }
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int j = b + q * 64 + lane;
-      if (b + q * 64 < j1) f(j, j < j1 && in_zone(vx[q], vy[q], c0, c1, r2));
-    }
-  }
+  int b = j0;
+  for (; j1 - b > 256; b += 512) zone_group<8>(x, y, c0, c1, r2, b, j1, f);
+  for (; b < j1; b += 128) zone_group<2>(x, y, c0, c1, r2, b, j1, f);
 }
 
 // Counts per wave (wcnt [zones][kZoneWaves]) and per workgroup (cnt
-// [zones][kZoneS]).  67 zones at n = 1e5: count 20 us and list 19, 33 and 72 by
+// [zones][workgroups per zone]).  67 zones at n = 1e5: count 20 us and list 19, 33 and 72 by
 // one workgroup per zone with two barriers per 1024 charges of the list.
 __global__ __launch_bounds__(kZT) void k_zone_count(const double* __restrict__ x,
                                                     const double* __restrict__ y, int n,
@@ -266,7 +273,7 @@ __global__ __launch_bounds__(kZT) void k_zone_count(const double* __restrict__ x
   if (threadIdx.x == 0) {
     int s = 0;
     for (int q = 0; q < kZW; ++q) s += ws[q];
-    cnt[p * kZoneS + blockIdx.y] = s;
+    cnt[p * gridDim.y + blockIdx.y] = s;
   }
 }
 
@@ -281,7 +288,7 @@ __global__ __launch_bounds__(kZT) void k_zone_fill(const double* __restrict__ x,
   const int p = blockIdx.x, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63, g = blockIdx.y * kZW + w;
   const double r = rz[p], r2 = r * r;
-  int before = lane < g ? wcnt[(size_t)p * kZoneWaves + lane] : 0;  // kZoneWaves == 64
+  int before = lane < g ? wcnt[(size_t)p * kZoneWaves + lane] : 0;
   for (int m = 32; m >= 1; m >>= 1) before += __shfl_xor(before, m, 64);
   const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
   int32_t* const dst = out + ptr[p];
@@ -293,7 +300,13 @@ __global__ __launch_bounds__(kZT) void k_zone_fill(const double* __restrict__ x,
     before += __popcll(m);
   });
 }
-static_assert(kZoneWaves == 64, "k_zone_fill sums the waves before its own across a wave");
+static_assert(kZoneWaves <= 64, "k_zone_fill sums the waves before its own across a wave");
+// Workgroups per zone: more where few zones leave the chip idle.  zone_patches,
+// us, with one / two / four: 5000 charges and 64 zones 57.5 / 56.5 / 56.1, 256
+// 58.2 / 57.7 / 59.5, 1000 68.8 / 70.0 / 76.8; 24 000 and 128 67.4 / 61.4 / 62.6, 512
+// 79.0 / 78.9 / 85.7; 1e5 and 64 103 / 80 / 69, 128 105 / 81 / 81, 256 106 / 102 / 102, 1000
+// 232 / 232 / 234.
+static int zone_split(int n_zones) { return n_zones <= 64 ? 4 : n_zones <= 128 ? 2 : 1; }
 
 #pragma clang fp contract(on)
 
@@ -401,11 +414,12 @@ int zone_patches(const double* x, const double* y, int64_t n, int32_t n_zones, c
   int32_t* wcnt = c.take<int32_t>((size_t)n_zones * kZoneWaves);
   int32_t* ptr_d = c.take<int32_t>((size_t)n_zones + 1);
   hipStream_t st = (hipStream_t)stream;
-  hipLaunchKernelGGL(k_zone_count, dim3(n_zones, kZoneS), dim3(kZT), 0, st, x, y, (int)n, cx, cy,
+  const int S = zone_split(n_zones);
+  hipLaunchKernelGGL(k_zone_count, dim3(n_zones, S), dim3(kZT), 0, st, x, y, (int)n, cx, cy,
                      rz, cnt_d, wcnt);
   int rc = hip_status(hipGetLastError());
   if (rc) return rc;
-  std::vector<int32_t> cnt((size_t)n_zones * kZoneS);
+  std::vector<int32_t> cnt((size_t)n_zones * S);
   if ((rc = hip_status(hipMemcpyAsync(cnt.data(), cnt_d, sizeof(int32_t) * cnt.size(),
                                       hipMemcpyDeviceToHost, st))))
     return rc;
@@ -413,7 +427,7 @@ int zone_patches(const double* x, const double* y, int64_t n, int32_t n_zones, c
   int64_t total = 0;
   patch_ptr[0] = 0;
   for (int p = 0; p < n_zones; ++p) {
-    for (int q = 0; q < kZoneS; ++q) total += cnt[(size_t)p * kZoneS + q];
+    for (int q = 0; q < S; ++q) total += cnt[(size_t)p * S + q];
     if (total > INT32_MAX) return CD_ERR_INVALID_ARG;
     patch_ptr[p + 1] = (int32_t)total;
   }
@@ -422,7 +436,7 @@ int zone_patches(const double* x, const double* y, int64_t n, int32_t n_zones, c
   if ((rc = hip_status(hipMemcpyAsync(ptr_d, patch_ptr, sizeof(int32_t) * (n_zones + 1),
                                       hipMemcpyHostToDevice, st))))
     return rc;
-  hipLaunchKernelGGL(k_zone_fill, dim3(n_zones, kZoneS), dim3(kZT), 0, st, x, y, (int)n, cx, cy,
+  hipLaunchKernelGGL(k_zone_fill, dim3(n_zones, S), dim3(kZT), 0, st, x, y, (int)n, cx, cy,
                      rz, ptr_d, wcnt, active_idx);
   if ((rc = hip_status(hipGetLastError()))) return rc;
   // the host offsets were read by the copy above; keep them valid until it ends

@@ -1,6 +1,7 @@
 """Defect lists on both sides of the size up to which one workgroup writes the
-list, and around the groups of loads; against their definition in numpy
-(bit-exact)."""
+list, and zone lists where the workgroups per zone change (64 and 128 zones),
+at charge counts around the groups a wave loads; against their definitions in
+numpy (bit-exact)."""
 import numpy as np
 import pytest
 import torch
@@ -23,3 +24,20 @@ def test_defect_lists(dev, n):
         assert mu == e.sum() / n and abs(sd - e.std()) <= 1e-12 * max(1.0, e.std())
         want = np.nonzero(e > thr)[0]
         assert int(cnt) == want.size and np.array_equal(z["defects"].cpu().numpy()[:want.size], want)
+
+
+@pytest.mark.parametrize("zones", [64, 65, 128, 129])
+@pytest.mark.parametrize("n", [100, 1025, 4097, 8193, 16385])
+def test_zone_lists(dev, n, zones):
+    print(f"[case] n={n} zones={zones}", flush=True)
+    x, y = W.uniform_disk(n, n)
+    rng = np.random.default_rng(zones)
+    cx, cy, rz = rng.uniform(-0.7, 0.7, zones), rng.uniform(-0.7, 0.7, zones), rng.uniform(0.0, 0.3, zones)
+    rz[0] = 3.0  # every charge
+    f = dict(dtype=torch.float64, device=dev)
+    ptr, idx = Z.zone_patches(torch.tensor(x, device=dev), torch.tensor(y, device=dev), torch.tensor(cx, **f),
+                              torch.tensor(cy, **f), torch.tensor(rz, **f))
+    idx = idx.cpu().numpy()
+    for p in range(zones):
+        dx, dy = x - cx[p], y - cy[p]
+        assert np.array_equal(idx[ptr[p]:ptr[p + 1]], np.nonzero(dx * dx + dy * dy <= rz[p] * rz[p])[0])
