@@ -70,10 +70,15 @@ __device__ __forceinline__ double dist2_rn(double ax, double ay, double bx, doub
 //
 // T is found in a histogram of kSelBins bins over [0, range), range three
 // times the size-th distance at the mean density (twice at the centre of a
-// conducting disk; charges beyond it are not counted); the few charges of T's
-// bin are then ranked exactly.  If the histogram holds fewer than size charges,
-// or T's bin more than kSelList (clustered charges), an exact 8-pass radix
-// select finds T instead.  Each wave reads a contiguous sixteenth of the
+// conducting disk; charges beyond it are not counted), and 4.2, which holds
+// every distance in the disk, for more than a third of the charges (about a
+// centre at the rim the size-th is farther: from half of the charges on the
+// histogram fell short and 64 such patches at N = 1000 took 139 us, now 62); the
+// few charges of T's bin are then ranked exactly.  If the histogram holds fewer than size charges,
+// or T's bin more than kSelList (clustered charges), an exact radix select of
+// 12 bits a pass, its bins scanned as the histogram's, finds T instead (256 patches
+// of 2500 among 1e5 charges, half of them in a cluster: 318 us, 468 with 8 bits a
+// pass and one thread's scan).  Each wave reads a contiguous sixteenth of the
 // charges, so that the index order needs no barrier inside a pass, and the
 // first pass lists its charges in range (in LDS, in order): the two passes
 // after it read only those (a wave with more than kSelCand: its range again).
@@ -91,11 +96,11 @@ __global__ __launch_bounds__(1024) void k_patch_select(const double* __restrict_
                                                        int32_t* __restrict__ out,
                                                        int32_t* __restrict__ err) {
   __shared__ __align__(16) uint32_t hist[kSelBins];  // read four at a time
-  __shared__ uint64_t lkey[kSelList];
+  __shared__ __align__(16) double lkey[kSelList];  // read two at a time
   __shared__ uint8_t lwave[kSelList];
   __shared__ uint32_t wsum[16], lt_w[16], eq_w[16], s_need, s_cnt;
   __shared__ int s_bin;
-  __shared__ uint64_t s_T, s_mask;
+  __shared__ uint64_t s_T;
   __shared__ int32_t cand[16][kSelCand];
   const int p = blockIdx.x, t = threadIdx.x, lane = t & 63;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -106,7 +111,8 @@ __global__ __launch_bounds__(1024) void k_patch_select(const double* __restrict_
     return;
   }
   const double cx = x[ctr], cy = y[ctr];
-  const double scale = (double)kSelBins * (double)n / (3.0 * (double)size);
+  const double range = 3 * size > n ? 4.2 : 3.0 * (double)size / (double)n;
+  const double scale = (double)kSelBins / range;
   const int per = (n + 1023) / 1024 * 64, j0 = min(n, w * per), j1 = min(n, j0 + per);
   auto bin_of = [&](double d) {
     const double f = d * scale;
@@ -114,7 +120,7 @@ __global__ __launch_bounds__(1024) void k_patch_select(const double* __restrict_
   };
   // the wave's range, 64 charges at a time: f(index, distance, lane in range)
   auto sweep = [&](auto f) {
-    // eight blocks' loads go out together
+    // eight blocks' loads go out together, two where fewer are left
     int b = j0;
     for (; b + 512 <= j1; b += 512) {
       const double *px = x + b + lane, *py = y + b + lane;
@@ -127,19 +133,25 @@ __global__ __launch_bounds__(1024) void k_patch_select(const double* __restrict_
 #pragma unroll
       for (int q = 0; q < 8; ++q) f(b + q * 64 + lane, dist2_rn(vx[q], vy[q], cx, cy), true);
     }
-    for (; b < j1; b += 512) {
-      double vx[8], vy[8];
+    auto part = [&](auto blocks) {
+      constexpr int U = decltype(blocks)::value;
+      double vx[U], vy[U];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
+      for (int q = 0; q < U; ++q) {
         const int j = min(b + q * 64 + lane, j1 - 1);
         vx[q] = x[j];
         vy[q] = y[j];
       }
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
+      for (int q = 0; q < U; ++q) {
         const int j = b + q * 64 + lane;
         if (b + q * 64 < j1) f(j, dist2_rn(vx[q], vy[q], cx, cy), j < j1);
       }
+    };
+    if (j1 - b > 256) {
+      part(std::integral_constant<int, 8>{});
+    } else {
+      for (; b < j1; b += 128) part(std::integral_constant<int, 2>{});
     }
   };
   for (int q = t; q < kSelBins; q += 1024) hist[q] = 0;
@@ -147,6 +159,7 @@ __global__ __launch_bounds__(1024) void k_patch_select(const double* __restrict_
   if (t == 0) {
     s_bin = -1;
     s_cnt = 0;
+    s_T = 0;
   }
   __syncthreads();
   const uint64_t below_me = lane ? (~0ull >> (64 - lane)) : 0ull;
@@ -181,9 +194,10 @@ __global__ __launch_bounds__(1024) void k_patch_select(const double* __restrict_
         if (b + q * 64 < nc) f(j[q], dist2_rn(vx[q], vy[q], cx, cy), b + q * 64 + lane < nc);
     }
   };
-  __syncthreads();
-  {
-    // the bin where the running count reaches size (thread: four bins)
+  // the bin where the running count reaches need (thread: four bins), and what
+  // remains of need there; none: s_bin keeps its value.  hist may be written after it.
+  auto find_bin = [&](uint32_t need) {
+    __syncthreads();
     const uint4 c = reinterpret_cast<const uint4*>(hist)[t];
     const uint32_t own = c.x + c.y + c.z + c.w;
     uint32_t v = own;
@@ -196,7 +210,6 @@ __global__ __launch_bounds__(1024) void k_patch_select(const double* __restrict_
     __syncthreads();
     for (int q = 0; q < w; ++q) v += wsum[q];
     uint32_t before = v - own;
-    const uint32_t need = (uint32_t)size;
     if (before < need && v >= need) {
       int q = 4 * t;
       const uint32_t cc[4] = {c.x, c.y, c.z, c.w};
@@ -209,10 +222,12 @@ __global__ __launch_bounds__(1024) void k_patch_select(const double* __restrict_
       s_bin = q;
       s_need = need - before;  // T is the s_need-th smallest of the bin
     }
-  }
-  __syncthreads();
+    __syncthreads();
+  };
+  find_bin((uint32_t)size);
   const int bin = s_bin;
   const bool ranked = bin >= 0 && hist[bin] <= (uint32_t)kSelList, listed = ranked && nc <= kSelCand;
+  __syncthreads();  // hist is written again below
   if (ranked) {
     uint32_t lt = 0;
     auto rank = [&](int, double d, bool in) {
@@ -220,7 +235,7 @@ __global__ __launch_bounds__(1024) void k_patch_select(const double* __restrict_
       lt += __popcll(__ballot(in && q < bin));
       if (in && q == bin) {
         const uint32_t e = atomicAdd(&s_cnt, 1u);
-        lkey[e] = __double_as_longlong(d);
+        lkey[e] = d;
         lwave[e] = (uint8_t)w;
       }
     };
@@ -229,48 +244,46 @@ __global__ __launch_bounds__(1024) void k_patch_select(const double* __restrict_
     if (lane == 0) lt_w[w] = lt;
     __syncthreads();
     const uint32_t m = s_cnt, need = s_need;
-    uint64_t key = 0;
-    uint32_t below = 0, same = 0;
-    if ((uint32_t)t < m) {
-      key = lkey[t];
-      for (uint32_t e = 0; e < m; ++e) {
-        below += lkey[e] < key;
-        same += lkey[e] == key;
+    // T: the largest with fewer than need below it
+    const double key = (uint32_t)t < m ? lkey[t] : -1.0;
+    if ((uint32_t)(t & ~63) < m) {  // whole waves
+      uint32_t below = 0;
+      const double2* l2 = reinterpret_cast<const double2*>(lkey);
+#pragma unroll 4
+      for (uint32_t e = 0; e < m / 2; ++e) {
+        const double2 v = l2[e];
+        below += v.x < key;
+        below += v.y < key;
       }
-      if (below < need && below + same >= need) s_T = key;  // the same key from every such thread
+      if (m & 1) below += lkey[m - 1] < key;
+      const double v = wave_max(below < need ? key : -1.0);
+      if (lane == 0 && v >= 0.0)
+        atomicMax((unsigned long long*)&s_T, (unsigned long long)__double_as_longlong(v));
     }
     __syncthreads();
+    const double T = __longlong_as_double(s_T);
     if ((uint32_t)t < m) {
-      if (key < s_T) atomicAdd(&lt_w[lwave[t]], 1u);
-      else if (key == s_T) atomicAdd(&eq_w[lwave[t]], 1u);
+      if (key < T) atomicAdd(&lt_w[lwave[t]], 1u);
+      else if (key == T) atomicAdd(&eq_w[lwave[t]], 1u);
     }
   } else {
-    if (t == 0) {
-      s_T = 0;
-      s_mask = 0;
-      s_need = (uint32_t)size;
-    }
-    __syncthreads();
-    for (int pass = 0; pass < 8; ++pass) {
-      const int shift = 56 - 8 * pass;
-      if (t < 256) hist[t] = 0;
+    uint64_t T = 0, mask = 0;
+    uint32_t need = (uint32_t)size;
+    for (int top = 64; top > 0;) {  // 12 bits a pass, the last four in one more
+      const int shift = max(top - 12, 0), digits = 1 << (top - shift);
+      for (int q = t; q < kSelBins; q += 1024) hist[q] = 0;
       __syncthreads();
-      const uint64_t pre = s_T, msk = s_mask;
       sweep([&](int, double d, bool in) {
         const uint64_t key = __double_as_longlong(d);
-        if (in && (key & msk) == pre) atomicAdd(&hist[(key >> shift) & 255u], 1u);
+        if (in && (key & mask) == T) atomicAdd(&hist[(key >> shift) & (digits - 1)], 1u);
       });
-      __syncthreads();
-      if (t == 0) {
-        uint32_t need = s_need, b = 0;
-        while (b < 255 && hist[b] < need) need -= hist[b++];
-        s_need = need;
-        s_T = pre | ((uint64_t)b << shift);
-        s_mask = msk | ((uint64_t)255 << shift);
-      }
-      __syncthreads();
+      find_bin(need);
+      T |= (uint64_t)s_bin << shift;
+      mask |= (uint64_t)(digits - 1) << shift;
+      need = s_need;
+      top = shift;
     }
-    const uint64_t T = s_T;
+    if (t == 0) s_T = T;
     uint32_t lt = 0, eq = 0;
     sweep([&](int, double d, bool in) {
       const uint64_t key = __double_as_longlong(d);
