@@ -250,7 +250,7 @@ __device__ __forceinline__ void zone_sweep(const double* __restrict__ x,
 }
 
 // Counts per wave (wcnt [zones][kZoneWaves]) and per workgroup (cnt
-// [zones][workgroups per zone]).  67 zones at n = 1e5: count 20 us and list 19, 33 and 72 by
+// [zones][workgroups per zone]).  67 zones at n = 1e5: count and list 16 us each, 33 and 72 by
 // one workgroup per zone with two barriers per 1024 charges of the list.
 __global__ __launch_bounds__(kZT) void k_zone_count(const double* __restrict__ x,
                                                     const double* __restrict__ y, int n,
@@ -302,11 +302,11 @@ __global__ __launch_bounds__(kZT) void k_zone_fill(const double* __restrict__ x,
 }
 static_assert(kZoneWaves <= 64, "k_zone_fill sums the waves before its own across a wave");
 // Workgroups per zone: more where few zones leave the chip idle.  zone_patches,
-// us, with one / two / four: 5000 charges and 64 zones 57.5 / 56.5 / 56.1, 256
-// 58.2 / 57.7 / 59.5, 1000 68.8 / 70.0 / 76.8; 24 000 and 128 67.4 / 61.4 / 62.6, 512
-// 79.0 / 78.9 / 85.7; 1e5 and 64 103 / 80 / 69, 128 105 / 81 / 81, 256 106 / 102 / 102, 1000
-// 232 / 232 / 234.
-static int zone_split(int n_zones) { return n_zones <= 64 ? 4 : n_zones <= 128 ? 2 : 1; }
+// us, with one / two / four: 5000 charges and 128 zones 57.5 / 56.3 / 56.8, 256
+// 58.2 / 57.7 / 59.5, 1000 68.8 / 70.0 / 76.8; 24 000 and 128 67.4 / 61.4 / 62.6, 256
+// 68.0 / 67.5 / 70.9, 512 79.0 / 78.9 / 85.7; 1e5 and 64 103 / 80 / 69, 128 105 / 81 / 81,
+// 256 106 / 102 / 102, 1000 232 / 232 / 234.
+static int zone_split(int n_zones) { return n_zones <= 128 ? 4 : n_zones <= 256 ? 2 : 1; }
 
 #pragma clang fp contract(on)
 

@@ -1,5 +1,5 @@
 """Defect lists on both sides of the size up to which one workgroup writes the
-list, and zone lists where the workgroups per zone change (64 and 128 zones),
+list, and zone lists where the workgroups per zone change (128 and 256 zones),
 at charge counts around the groups a wave loads; against their definitions in
 numpy (bit-exact)."""
 import numpy as np
@@ -26,7 +26,7 @@ def test_defect_lists(dev, n):
         assert int(cnt) == want.size and np.array_equal(z["defects"].cpu().numpy()[:want.size], want)
 
 
-@pytest.mark.parametrize("zones", [64, 65, 128, 129])
+@pytest.mark.parametrize("zones", [128, 129, 256, 257])
 @pytest.mark.parametrize("n", [100, 1025, 4097, 8193, 16385])
 def test_zone_lists(dev, n, zones):
     print(f"[case] n={n} zones={zones}", flush=True)
