@@ -70,18 +70,20 @@ __device__ __forceinline__ double dist2_rn(double ax, double ay, double bx, doub
 //
 // T is found in a histogram of kSelBins bins over [0, range), range three
 // times the size-th distance at the mean density (twice at the centre of a
-// conducting disk; charges beyond it are not counted), and 4.2, which holds
-// every distance in the disk, for more than a third of the charges (about a
-// centre at the rim the size-th is farther: from half of the charges on the
-// histogram fell short and 64 such patches at N = 1000 took 139 us, now 62); the
-// few charges of T's bin are then ranked exactly.  If the histogram holds fewer than size charges,
-// or T's bin more than kSelList (clustered charges), an exact radix select of
-// 12 bits a pass, its bins scanned as the histogram's, finds T instead (256 patches
-// of 2500 among 1e5 charges, half of them in a cluster: 318 us, 468 with 8 bits a
-// pass and one thread's scan).  Each wave reads a contiguous sixteenth of the
-// charges, so that the index order needs no barrier inside a pass, and the
-// first pass lists its charges in range (in LDS, in order): the two passes
-// after it read only those (a wave with more than kSelCand: its range again).
+// conducting disk; charges beyond it are not counted), and what holds every
+// distance in the disk for more than half of the charges (about a centre at the
+// rim the size-th is farther: the histogram fell short and 64 patches of 1000
+// charges at N = 1000 took 139 us, now 62; with it for a third of the charges the
+// lists below would overflow, 83 us against 77 for one patch of 15 000 at N =
+// 30 000).  The few charges of T's bin are then ranked exactly.  If the histogram
+// holds fewer than size charges, or T's bin more than kSelList (clustered
+// charges), an exact radix select of 12 bits a pass, its bins scanned as the
+// histogram's, finds T instead (256 patches of 2500 among 1e5 charges, half of
+// them in a cluster: 318 us, 468 with 8 bits a pass and one thread's scan).
+// Each wave reads a contiguous sixteenth of the charges, so that the index
+// order needs no barrier inside a pass, and the first pass lists its charges in
+// range (in LDS, in order): the two passes after it read only those (a wave with
+// more than kSelCand: its range again).
 // Bound: issue of the first pass (a workgroup per CU, about 30 instructions a
 // charge).  256 patches at N = 1e5: 768 us with the radix select's ten passes,
 // whose first ones counted nearly all charges into one bin; 95 with three
@@ -111,8 +113,9 @@ __global__ __launch_bounds__(1024) void k_patch_select(const double* __restrict_
     return;
   }
   const double cx = x[ctr], cy = y[ctr];
-  const double range = 3 * size > n ? 4.2 : 3.0 * (double)size / (double)n;
-  const double scale = (double)kSelBins / range;
+  const double rim = 1.0 + sqrt(cx * cx + cy * cy);  // the farthest point of the disk
+  const double scale = 2 * size > n ? (double)kSelBins / (1.05 * rim * rim)
+                                    : (double)kSelBins * (double)n / (3.0 * (double)size);
   const int per = (n + 1023) / 1024 * 64, j0 = min(n, w * per), j1 = min(n, j0 + per);
   auto bin_of = [&](double d) {
     const double f = d * scale;
@@ -120,7 +123,7 @@ __global__ __launch_bounds__(1024) void k_patch_select(const double* __restrict_
   };
   // the wave's range, 64 charges at a time: f(index, distance, lane in range)
   auto sweep = [&](auto f) {
-    // eight blocks' loads go out together, two where fewer are left
+    // eight blocks' loads go out together
     int b = j0;
     for (; b + 512 <= j1; b += 512) {
       const double *px = x + b + lane, *py = y + b + lane;
@@ -133,25 +136,20 @@ __global__ __launch_bounds__(1024) void k_patch_select(const double* __restrict_
 #pragma unroll
       for (int q = 0; q < 8; ++q) f(b + q * 64 + lane, dist2_rn(vx[q], vy[q], cx, cy), true);
     }
-    auto part = [&](auto blocks) {
-      constexpr int U = decltype(blocks)::value;
-      double vx[U], vy[U];
+    for (; b < j1; b += 512) {
+      double vx[8], vy[8];
 #pragma unroll
-      for (int q = 0; q < U; ++q) {
+      for (int q = 0; q < 8; ++q) {
+        if (b + q * 64 >= j1) break;  // the same for the wave
         const int j = min(b + q * 64 + lane, j1 - 1);
         vx[q] = x[j];
         vy[q] = y[j];
       }
 #pragma unroll
-      for (int q = 0; q < U; ++q) {
+      for (int q = 0; q < 8; ++q) {
         const int j = b + q * 64 + lane;
         if (b + q * 64 < j1) f(j, dist2_rn(vx[q], vy[q], cx, cy), j < j1);
       }
-    };
-    if (j1 - b > 256) {
-      part(std::integral_constant<int, 8>{});
-    } else {
-      for (; b < j1; b += 128) part(std::integral_constant<int, 2>{});
     }
   };
   for (int q = t; q < kSelBins; q += 1024) hist[q] = 0;
@@ -227,7 +225,6 @@ __global__ __launch_bounds__(1024) void k_patch_select(const double* __restrict_
   find_bin((uint32_t)size);
   const int bin = s_bin;
   const bool ranked = bin >= 0 && hist[bin] <= (uint32_t)kSelList, listed = ranked && nc <= kSelCand;
-  __syncthreads();  // hist is written again below
   if (ranked) {
     uint32_t lt = 0;
     auto rank = [&](int, double d, bool in) {
@@ -269,6 +266,7 @@ __global__ __launch_bounds__(1024) void k_patch_select(const double* __restrict_
   } else {
     uint64_t T = 0, mask = 0;
     uint32_t need = (uint32_t)size;
+    __syncthreads();  // hist is written again
     for (int top = 64; top > 0;) {  // 12 bits a pass, the last four in one more
       const int shift = max(top - 12, 0), digits = 1 << (top - shift);
       for (int q = t; q < kSelBins; q += 1024) hist[q] = 0;

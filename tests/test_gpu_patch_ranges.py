@@ -1,5 +1,5 @@
 """Patches on both sides of the size from which the histogram of the distances
-spans the whole disk (a third of the charges), about centres at the rim and in
+spans the whole disk (half of the charges), about centres at the rim and in
 the middle, on uniform, lattice and clustered charges; bit-exact against the
 oracle."""
 import numpy as np
@@ -25,12 +25,12 @@ def positions(layout, n):
 
 @pytest.mark.parametrize("layout", ["uniform", "lattice", "cluster"])
 @pytest.mark.parametrize("n", [65, 513, 3000, 12289])
-def test_sizes_around_a_third(dev, layout, n):
+def test_sizes_around_half(dev, layout, n):
     print(f"[case] {layout} n={n}", flush=True)
     x, y = positions(layout, n)
     n = x.size
     r = np.hypot(x, y)
-    sizes = np.array([max(1, n // 3 - 1), n // 3, n // 3 + 1, n // 2, n // 2 + 1, 3 * n // 4, n - 1, n], dtype=np.int32)
+    sizes = np.array([n // 3, n // 2 - 1, n // 2, n // 2 + 1, n // 2 + 2, 3 * n // 4, n - 1, n], dtype=np.int32)
     for c in (int(np.argmax(r)), int(np.argmin(r)), n // 7):
         centres = np.full(sizes.size, c, dtype=np.int32)
         _, idx = R.build_patches(torch.tensor(x, device=dev), torch.tensor(y, device=dev), centres, sizes)
