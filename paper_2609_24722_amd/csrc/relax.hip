@@ -2732,27 +2732,32 @@ static void launch_update(RPlan& R, hipStream_t s, bool hist32) {
 }
 
 // CG iterations per round.  A Newton step takes tens of them for each
-// evaluation.  In a batch on the plain path some patch has a trial in nearly
-// every round, and the evaluation costs its launches and latency whatever the
-// others are doing (exact pass and sum, 27 us in a batch of 24 patches, against
-// 18 for a CG iteration), so more iterations between evaluations pay, the more
-// so the more patches there are; in a batch of few, every further iteration is
-// launched in vain at the end of a CG phase and of the call.  Times with one /
-// two / three, ms, mean over twelve batches started near their minimum (N of 1e4, 2e4
-// and 4e4; four batches where one N is given) and, in brackets, over eight started far from it and relaxed for 60
-// iterations at most:
-//   1 patch of 60 to 180    2.67 / 2.43 / 2.59
-//   4 of 60 to 180          3.52 / 3.35 / 3.39    (4 of 30 to 100: 5.81 / 5.93 / 6.26)
-//   7 of 60 to 300          4.79 / 4.50 / 4.48
-//   8 of 60 to 600          6.68 / 6.22 / 6.19    (22.7 / 21.2 / 21.0)
-//   12 of 60 to 450, 4e4    8.51 / 7.88 / 7.57
-//   24 of 60 to 300, 4e4    8.51 / 7.52 / 7.16    (24 of 30 to 100: 17.0 / 15.9 / 15.9)
-//   64 of 60 to 400         (to 1e-6, three batches: 81.5 / 75.5 / 74.0)
+// evaluation (at most two an active).  In a batch on the plain path some patch
+// has a trial in nearly every round, and the evaluation costs its launches and
+// latency whatever the others are doing (exact pass and sum, 27 us in a batch of
+// 24 patches at N = 4e4, against 18 for a CG iteration), so more iterations
+// between evaluations pay, the more so the more patches and charges there are;
+// with few actives or charges every further iteration is launched in vain at the
+// end of a CG phase and of the call.  Times with one / two / three, ms, started
+// near the minimum (in brackets: gtol 1e-3):
+//   1 patch of 1, N = 5000      0.53 / 0.64 / 0.78   (0.53 / 0.63 / 0.78)
+//   1 of 40, 4e4                1.77 / 1.83 / 1.83   (1.36 / 1.43 / 1.49)
+//   4 of 60, 300                9.59 / 9.63 / 9.92   (2.99 / 3.55 / 4.08)
+//   4 of 20, 5000               1.48 / 1.44 / 1.51   (1.21 / 1.19 / 1.23)
+//   4 of 20, 4e4                2.04 / 1.85 / 1.99   (1.45 / 1.44 / 1.66)
+//   16 of 60, 5000              2.60 / 2.37 / 2.60   (1.99 / 1.95 / 2.13)
+//   7 of 60 to 300, 1e4 to 4e4  4.79 / 4.50 / 4.48
+//   12 of 60 to 450, 1e4        5.43 / 5.07 / 5.00
+//   24 of 60 to 300, 4e4        8.51 / 7.52 / 7.16
+//   64 of 20, 4e4               6.41 / 5.40 / 4.69   (4.19 / 3.69 / 3.72)
 // The mixed path's evaluation is a pass over the patch's own pairs, no dearer
 // than a CG iteration, and a patch stops after one Newton step: 4 patches of 60
-// to 300 take 28.0 / 29.4 / 32.7 (20.5 / 23.3 / 26.2).
+// to 300, 2e4, take 28.0 / 29.4 / 32.7.
 // A patch's own sequence of steps on the plain path does not depend on it.
-static int cg_per_round(int precision, int P) { return precision != CD_FP64 ? 1 : P < 8 ? 2 : 3; }
+static int cg_per_round(int precision, int64_t n, int P, int64_t ntot) {
+  if (precision != CD_FP64 || ntot < 64 || (n <= 1024 && ntot < 320)) return 1;
+  return P < 8 || n < 8192 ? 2 : 3;
+}
 
 template <class EvalFn>
 static void launch_round(RPlan& R, hipStream_t s, bool hist32, int shape, EvalFn& eval) {
@@ -2954,7 +2959,7 @@ int relax_subdomains(const double* x, const double* y, int64_t n, int32_t n_patc
   R.graph_rounds = sched.graph_rounds;
   R.wide_blocks = sched.wide_blocks;
   R.use_graphs = o.launch == CD_LAUNCH_GRAPH;
-  R.cg_rounds = cg_per_round(o.precision, n_patches);
+  R.cg_rounds = cg_per_round(o.precision, n, n_patches, ntot);
   D.tu = o.coords == CD_COORDS_TU;
   D.tu_rmin = 1e-3 * D.sigma;
   // the Newton steps work in (x, y) and angle coordinates: none in (t, u); a
